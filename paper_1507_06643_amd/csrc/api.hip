@@ -960,7 +960,7 @@ int read_status(dpde_handle* h) {
 // array instead of buffers allocated on first use.  In host code `scratch`
 // names a host-side stand-in: its device address on each GPU comes from
 // hipGetSymbolAddress, taken once per device with that device current.
-constexpr int kNoAllocBlocks = 64;  // block partials of k_mlp_fwd_bwd (its grid is capped at 64)
+constexpr int kNoAllocBlocks = kTrainBlocks;  // block partials of k_mlp_fwd_bwd
 constexpr size_t kNoAllocGpart = (size_t)kNoAllocBlocks * kNParam * sizeof(float);
 constexpr size_t kNoAllocLpart = (size_t)kNoAllocBlocks * sizeof(double);
 constexpr size_t kNoAllocGsum = (size_t)kNParam * sizeof(float);
@@ -1483,10 +1483,10 @@ int dpde_mlp_grad_noalloc(dpde_handle* h, const float* x, const float* t, int64_
   float* lsum = reinterpret_cast<float*>(base + kNoAllocGpart + kNoAllocLpart + kNoAllocGsum);
   // the launch shape of dpde_mlp_grad, so both give the same bits; every
   // scratch word read below is written first by this call
-  const int gb = (int)std::min<int64_t>(kNoAllocBlocks, (n + kTrainThreads - 1) / kTrainThreads);
+  const int gb = train_blocks(n);
   hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(gb), dim3(kTrainThreads), 0, h->stream,
                      (const float*)h->mlp.w, x, t, n, (int64_t)0, n, 1.0f / (float)n, gpart, lpart);
-  hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(1), dim3(1024), 0, h->stream, (const float*)gpart,
+  hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kReduceBlocks), dim3(kReduceThreads), 0, h->stream, (const float*)gpart,
                      (const double*)lpart, gb, n, h->mlp.w, h->mlp.adam_m, h->mlp.adam_v,
                      h->mlp.wb, 0.0f, 1.0f, 1.0f, 0, gsum, lsum);
   HIPCHK(hipGetLastError());

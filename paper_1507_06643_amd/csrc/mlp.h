@@ -13,12 +13,14 @@
 // particle, so the output layer is a 16-term dot product plus one cross-half
 // shuffle.
 //
-// Training runs in FP32 on the GPU: forward and backward per sample in
-// registers, per-block gradient sums in a fixed order through LDS, a second
-// kernel adds the block partials in block order and applies Adam.  Samples
+// Training runs in FP32 on the GPU: forward and backward of 16 samples per wave
+// with the 32x32 products on the matrix cores in FP32, per-block gradient sums
+// in a fixed order, a second kernel adds the block partials in block order and
+// applies Adam.  Samples
 // are theta log-uniform in the training range, eps = eps(theta) from the EOS.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <random>
@@ -196,8 +198,19 @@ __global__ __launch_bounds__(256) void k_mlp_eval(const float* __restrict__ wf,
 }
 
 // ---- training ---------------------------------------------------------------------
-constexpr int kTrainThreads = 128;
-constexpr int kLd = kH + 1;  // padded LDS row
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTrainThreads = 256;
+constexpr int kTrainWaves = kTrainThreads / kWave;
+constexpr int kTrainCols = 16;     // samples a wave takes at once: the columns of its products
+constexpr int kTrainBlocks = 64;   // most blocks, and so partial gradients, of one batch
+constexpr int kLd = kH + 1;        // padded LDS row
+
+// Blocks for a batch of n samples: each of a block's four waves takes 16.
+inline int train_blocks(int64_t n) {
+  const int64_t per = kTrainWaves * kTrainCols;
+  return (int)std::min<int64_t>(kTrainBlocks, (n + per - 1) / per);
+}
 
 // Training samples: theta log-uniform in [lo, hi] from Philox words keyed by
 // the seed (counter = sample index), eps = eps(theta).
@@ -216,140 +229,241 @@ __global__ void k_mlp_samples(uint64_t seed, int64_t n, double lnlo, double lnhi
   ts[k] = (float)((lt - out_c) / out_s);
 }
 
-// Forward + backward of nb samples starting at sample `begin` (mod nsamp), in
-// chunks of kTrainThreads per block; block partial gradients of the mean
-// squared error scaled by inv_batch.
+// Forward + backward of nb samples starting at sample `begin` (mod nsamp):
+// block partial gradients of the mean squared error scaled by inv_batch.
+//
+// A batch is three 32 x 32 products per sample (W2 h1, W2^T d2 and the sum of
+// d2 h1^T) between two layers of tanh, so at the usual 4096 samples the launch
+// is bound by the length of one wave's chain, not by its arithmetic.  A wave
+// therefore takes 16 samples, four lanes each, and the products run on the
+// matrix cores in FP32 (v_mfma_f32_16x16x4_f32).  Sample c = lane % 16, group
+// g = lane / 16; a lane holds the units u(q) = 16 (q / 4) + 4 g + q % 4 of its
+// sample, q = 0..7.  That is the accumulator layout of the matrix instruction,
+// and since the order of a product's inner index is free, the same registers
+// are the B operand of the next product; only d2 and h1 go through LDS, for
+// the product summed over samples.  Measured (batch 4096): 57.8 us with one
+// thread per sample and the gradient summed from LDS by the vector units,
+// 7.3 us in this form.
 __global__ __launch_bounds__(kTrainThreads) void k_mlp_fwd_bwd(
     const float* __restrict__ w, const float* __restrict__ xs, const float* __restrict__ ts,
     int64_t nsamp, int64_t begin, int64_t nb, float inv_batch, float* __restrict__ gpart,
     double* __restrict__ lpart) {
-  __shared__ float H1[kTrainThreads * kLd];
-  __shared__ float H2[kTrainThreads * kLd];
-  __shared__ float D1[kTrainThreads * kLd];
-  __shared__ float D2[kTrainThreads * kLd];
-  __shared__ float X[kTrainThreads];
-  __shared__ float DY[kTrainThreads];
-  __shared__ double red[kTrainThreads / kWave];
-  const int tid = threadIdx.x;
-  const float* W1 = w + OFF_W1;
-  const float* B1 = w + OFF_B1;
-  const float* W2 = w + OFF_W2;
-  const float* B2 = w + OFF_B2;
-  const float* W3 = w + OFF_W3;
-  const float b3 = w[OFF_B3];
-  constexpr int kPer = (kNParam + kTrainThreads - 1) / kTrainThreads;
-  float acc[kPer];
+  constexpr int kQ = kH / 4;            // units per lane
+  constexpr int kRow = kWave + 1;       // padded row of the final sums
+  constexpr int kT = kTrainCols * kLd;  // one wave's d2 or h1 by sample
+  // the waves' transposed d2 and h1, then (after the samples) their sums
+  __shared__ float buf[kTrainWaves * 4 * kQ * kRow];
+  static_assert(2 * kT <= 4 * kQ * kRow && kH * kH <= 4 * kQ * kRow, "LDS regions");
+  __shared__ double red[kTrainWaves];
+  __shared__ float red3[kTrainWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  const int c = lane % kTrainCols, g = lane / kTrainCols;
+  auto unit = [g](int q) { return 16 * (q >> 2) + 4 * g + (q & 3); };
+  float w1[kQ], b1[kQ], b2[kQ], w3[kQ];
+  float wf[2][kQ], wt[2][kQ];  // W2 and its transpose as A operands
 #pragma unroll
-  for (int c = 0; c < kPer; ++c) acc[c] = 0.0f;
+  for (int q = 0; q < kQ; ++q) {
+    const int u = unit(q);
+    w1[q] = w[OFF_W1 + u];
+    b1[q] = w[OFF_B1 + u];
+    b2[q] = w[OFF_B2 + u];
+    w3[q] = w[OFF_W3 + u];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      wf[m][q] = w[OFF_W2 + (16 * m + c) * kH + u];
+      wt[m][q] = w[OFF_W2 + u * kH + 16 * m + c];
+    }
+  }
+  const float b3 = w[OFF_B3];
+  f32x4 g2[2][2] = {};                // sum over samples of d2 h1^T, in tiles of 16 x 16
+  float sw1[kQ], sb1[kQ], sb2[kQ], sw3[kQ], sb3 = 0.0f;
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) sw1[q] = sb1[q] = sb2[q] = sw3[q] = 0.0f;
   double lsum = 0.0;
-  // this block's share of the nb samples
-  const int64_t per_block = (nb + gridDim.x - 1) / gridDim.x;
-  const int64_t b0 = (int64_t)blockIdx.x * per_block;
-  const int64_t b1 = b0 + per_block < nb ? b0 + per_block : nb;
-  for (int64_t c0 = b0; c0 < b1; c0 += kTrainThreads) {
-    const int64_t s = c0 + tid;
-    const bool live = s < b1;
+  float* td = buf + wv * 2 * kT;  // d2 by sample
+  float* th = td + kT;            // h1 by sample
+  const int64_t chunks = (nb + kTrainCols - 1) / kTrainCols;
+  for (int64_t q0 = (int64_t)blockIdx.x * kTrainWaves + wv; q0 < chunks;
+       q0 += (int64_t)gridDim.x * kTrainWaves) {  // uniform in the wave
+    const int64_t s = q0 * kTrainCols + c;
+    const bool live = s < nb;
     float x = 0.0f, t = 0.0f;
     if (live) {
-      const int64_t k = (begin + s) % nsamp;
+      int64_t k = begin + s;
+      if (k >= nsamp) k %= nsamp;
       x = xs[k];
       t = ts[k];
     }
-    float h1[kH], h2[kH];
+    float h1[kQ], h2[kQ], d2[kQ];
 #pragma unroll
-    for (int a = 0; a < kH; ++a) h1[a] = tanhf(W1[a] * x + B1[a]);
-    float y = b3;
-#pragma unroll 4
-    for (int a = 0; a < kH; ++a) {
-      float z = B2[a];
+    for (int q = 0; q < kQ; ++q) h1[q] = tanhf(w1[q] * x + b1[q]);
+    float y = 0.0f;
 #pragma unroll
-      for (int b = 0; b < kH; ++b) z += W2[a * kH + b] * h1[b];
-      h2[a] = tanhf(z);
-      y += W3[a] * h2[a];
-    }
-    const float err = live ? (y - t) : 0.0f;
-    lsum += (double)err * (double)err;
-    const float dy = 2.0f * err * inv_batch;
-    float d2[kH];
+    for (int m = 0; m < 2; ++m) {
+      f32x4 z = {b2[4 * m], b2[4 * m + 1], b2[4 * m + 2], b2[4 * m + 3]};
 #pragma unroll
-    for (int a = 0; a < kH; ++a) d2[a] = dy * W3[a] * (1.0f - h2[a] * h2[a]);
-#pragma unroll 4
-    for (int b = 0; b < kH; ++b) {
-      float z = 0.0f;
+      for (int q = 0; q < kQ; ++q) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[m][q], h1[q], z, 0, 0, 0);
 #pragma unroll
-      for (int a = 0; a < kH; ++a) z += W2[a * kH + b] * d2[a];
-      D1[tid * kLd + b] = z * (1.0f - h1[b] * h1[b]);
-    }
-#pragma unroll
-    for (int a = 0; a < kH; ++a) {
-      H1[tid * kLd + a] = live ? h1[a] : 0.0f;
-      H2[tid * kLd + a] = live ? h2[a] : 0.0f;
-      D2[tid * kLd + a] = d2[a];
-    }
-    X[tid] = x;
-    DY[tid] = dy;
-    __syncthreads();
-    const int rows = (int)((b1 - c0) < kTrainThreads ? (b1 - c0) : kTrainThreads);
-#pragma unroll
-    for (int c = 0; c < kPer; ++c) {
-      const int p = tid + c * kTrainThreads;
-      if (p >= kNParam) break;
-      float g = 0.0f;
-      if (p < OFF_B1) {
-        for (int r = 0; r < rows; ++r) g += D1[r * kLd + p] * X[r];
-      } else if (p < OFF_W2) {
-        for (int r = 0; r < rows; ++r) g += D1[r * kLd + (p - OFF_B1)];
-      } else if (p < OFF_B2) {
-        const int a = (p - OFF_W2) / kH, b = (p - OFF_W2) % kH;
-        for (int r = 0; r < rows; ++r) g += D2[r * kLd + a] * H1[r * kLd + b];
-      } else if (p < OFF_W3) {
-        for (int r = 0; r < rows; ++r) g += D2[r * kLd + (p - OFF_B2)];
-      } else if (p < OFF_B3) {
-        for (int r = 0; r < rows; ++r) g += DY[r] * H2[r * kLd + (p - OFF_W3)];
-      } else {
-        for (int r = 0; r < rows; ++r) g += DY[r];
+      for (int r = 0; r < 4; ++r) {
+        h2[4 * m + r] = tanhf(z[r]);
+        y += w3[4 * m + r] * h2[4 * m + r];
       }
-      acc[c] += g;
     }
-    __syncthreads();
+    y += __shfl_xor(y, 16, kWave);
+    y += __shfl_xor(y, 32, kWave);
+    const float err = live ? (y + b3) - t : 0.0f;
+    if (g == 0) lsum += (double)err * (double)err;
+    const float dy = 2.0f * err * inv_batch;
+    sb3 += dy;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      // a lane beyond the batch adds nothing, whatever the weights are
+      d2[q] = live ? dy * w3[q] * (1.0f - h2[q] * h2[q]) : 0.0f;
+      sb2[q] += d2[q];
+      sw3[q] += live ? dy * h2[q] : 0.0f;
+      td[c * kLd + unit(q)] = d2[q];
+      th[c * kLd + unit(q)] = live ? h1[q] : 0.0f;
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      f32x4 z = {};
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) z = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[m][q], d2[q], z, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float h = h1[4 * m + r];
+        const float d1 = live ? z[r] * (1.0f - h * h) : 0.0f;
+        sb1[4 * m + r] += d1;
+        sw1[4 * m + r] += d1 * x;
+      }
+    }
+    // the wave's own LDS rows: a fence orders its writes and reads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+#pragma unroll
+    for (int k = 0; k < kTrainCols / 4; ++k) {
+      const int row = (4 * k + g) * kLd + c;
+      const float a0 = td[row], a1 = td[row + 16], h0 = th[row], hh = th[row + 16];
+      g2[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, h0, g2[0][0], 0, 0, 0);
+      g2[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, hh, g2[0][1], 0, 0, 0);
+      g2[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, h0, g2[1][0], 0, 0, 0);
+      g2[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, hh, g2[1][1], 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();  // the next samples overwrite the rows
+  }
+  // the block's sums, waves in order
+  float* gp = gpart + (int64_t)blockIdx.x * kNParam;
+  lsum = wave_sum(lsum);
+#pragma unroll
+  for (int off = kTrainCols / 2; off > 0; off >>= 1) sb3 += __shfl_xor(sb3, off, kWave);
+  __syncthreads();
+  if (lane == 0) {
+    red[wv] = lsum;
+    red3[wv] = sb3;
   }
 #pragma unroll
-  for (int c = 0; c < kPer; ++c) {
-    const int p = tid + c * kTrainThreads;
-    if (p < kNParam) gpart[(int64_t)blockIdx.x * kNParam + p] = acc[c];
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        buf[wv * kH * kH + (16 * m + 4 * g + r) * kH + 16 * n + c] = g2[m][n][r];
+  __syncthreads();
+  for (int o = tid; o < kH * kH; o += kTrainThreads) {
+    float v = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kTrainWaves; ++k) v += buf[k * kH * kH + o];
+    gp[OFF_W2 + o] = v;
   }
-  double v[1] = {lsum};
-  block_sum<1>(v, red);
-  if (tid == 0) lpart[blockIdx.x] = v[0];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    float* r0 = buf + (wv * 4 * kQ + q) * kRow + lane;
+    r0[0] = sw1[q];
+    r0[kQ * kRow] = sb1[q];
+    r0[2 * kQ * kRow] = sb2[q];
+    r0[3 * kQ * kRow] = sw3[q];
+  }
+  __syncthreads();
+  {
+    // value o / 2 of the 4 x 32 vector gradients, half of the waves each
+    const int o = tid >> 1, type = o / kH, u = o % kH;
+    const int q = 4 * (u >> 4) + (u & 3), gg = (u >> 2) & 3;
+    float v = 0.0f;
+    for (int k = 2 * (tid & 1); k < 2 * (tid & 1) + 2; ++k) {
+      const float* r0 = buf + (k * 4 * kQ + type * kQ + q) * kRow + gg * kTrainCols;
+#pragma unroll
+      for (int j = 0; j < kTrainCols; ++j) v += r0[j];
+    }
+    v += __shfl_xor(v, 1, kWave);
+    const int off = type == 0 ? OFF_W1 : type == 1 ? OFF_B1 : type == 2 ? OFF_B2 : OFF_W3;
+    if ((tid & 1) == 0) gp[off + u] = v;
+  }
+  if (tid == 0) {
+    double l = 0.0;
+    float v = 0.0f;
+    for (int k = 0; k < kTrainWaves; ++k) {
+      l += red[k];
+      v += red3[k];
+    }
+    gp[OFF_B3] = v;
+    lpart[blockIdx.x] = l;
+  }
 }
 
-// Sum the block partials in block order; optionally apply one Adam step
-// (beta1 0.9, beta2 0.999, eps 1e-8) and refresh the BF16 copy.
-__global__ void k_mlp_reduce_adam(const float* __restrict__ gpart, const double* __restrict__ lpart,
-                                  int nblocks, int64_t batch, float* __restrict__ w,
-                                  float* __restrict__ m, float* __restrict__ v,
-                                  uint16_t* __restrict__ wb, float lr, float bc1, float bc2,
-                                  int update, float* __restrict__ gsum, float* __restrict__ loss_out) {
-  for (int p = threadIdx.x; p < kNParam; p += blockDim.x) {
-    float g = 0.0f;
-    for (int b = 0; b < nblocks; ++b) g += gpart[(int64_t)b * kNParam + p];
+// Sum the block partials (at most kTrainBlocks) in block order, one parameter
+// per thread; optionally apply one Adam step (beta1 0.9, beta2 0.999, eps 1e-8)
+// and refresh the BF16 copy.  Bound by the latency of the partials' loads, so
+// thirty-two are in flight and the parameters are spread over five blocks (17.9 us
+// as one block that loaded them one after the other, 4.2 us so).
+constexpr int kReduceThreads = 256;
+constexpr int kReduceBlocks = (kNParam + kWave + kReduceThreads - 1) / kReduceThreads;
+
+__global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce_adam(
+    const float* __restrict__ gpart, const double* __restrict__ lpart, int nblocks, int64_t batch,
+    float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
+    uint16_t* __restrict__ wb, float lr, float bc1, float bc2, int update,
+    float* __restrict__ gsum, float* __restrict__ loss_out) {
+  const int p = blockIdx.x * kReduceThreads + threadIdx.x;
+  if (p < kNParam) {
+    float m0 = 0.0f, v0 = 0.0f, w0 = 0.0f;
+    if (update) {
+      m0 = m[p];
+      v0 = v[p];
+      w0 = w[p];
+    }
+    double sum = 0.0;  // the blocks' parts are added in 64 bits and rounded once
+    constexpr int kAhead = 32;
+    for (int b0 = 0; b0 < nblocks; b0 += kAhead) {
+      float x[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)  // the row clamped, so that no load waits on a branch
+        x[k] = gpart[(int64_t)min(b0 + k, nblocks - 1) * kNParam + p];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) sum += b0 + k < nblocks ? (double)x[k] : 0.0;
+    }
+    const float g = (float)sum;
     if (gsum) gsum[p] = g;
     if (update) {
-      const float mm = 0.9f * m[p] + 0.1f * g;
-      const float vv = 0.999f * v[p] + 0.001f * g * g;
+      const float mm = 0.9f * m0 + 0.1f * g;
+      const float vv = 0.999f * v0 + 0.001f * g * g;
       m[p] = mm;
       v[p] = vv;
-      const float wn = w[p] - lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
+      const float wn = w0 - lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
       w[p] = wn;
       wb[p] = f32_to_bf16_bits(wn);
     }
   }
-  if (threadIdx.x == 0 && loss_out) {
-    double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += lpart[b];
-    *loss_out = (float)(s / (double)batch);
+  // the loss, by the last block's last wave, which has no parameters
+  if (loss_out && blockIdx.x == gridDim.x - 1 && threadIdx.x >= kReduceThreads - kWave) {
+    const int lane = threadIdx.x % kWave;
+    const double s = wave_sum(lane < nblocks ? lpart[lane] : 0.0);
+    if (lane == 0) *loss_out = (float)(s / (double)batch);
   }
 }
+static_assert(kTrainBlocks <= kWave, "one loss partial per lane");
+static_assert(kReduceBlocks * kReduceThreads - kNParam >= kWave, "a wave without parameters");
 
 __global__ void k_to_bf16(const float* __restrict__ w, uint16_t* __restrict__ wb, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -467,11 +581,11 @@ inline int mlp_grad(MlpState& s, hipStream_t st, const float* x, const float* t,
                     float* loss, float* grad, std::string& err) {
   if (!s.w) { err = "the surrogate has no weights"; return DPDE_EINVAL; }
   if (n <= 0) { err = "n must be > 0"; return DPDE_EINVAL; }
-  const int gb = (int)std::min<int64_t>(64, (n + kTrainThreads - 1) / kTrainThreads);
+  const int gb = train_blocks(n);
   if (mlp_ensure_train_buffers(s, gb, 1)) { err = "allocation failed"; return DPDE_ENOMEM; }
   hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(gb), dim3(kTrainThreads), 0, st, (const float*)s.w, x, t,
                      n, (int64_t)0, n, 1.0f / (float)n, s.gpart, s.lpart);
-  hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(1), dim3(1024), 0, st, (const float*)s.gpart,
+  hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, (const float*)s.gpart,
                      (const double*)s.lpart, gb, n, s.w, s.adam_m, s.adam_v, s.wb, 0.0f, 1.0f,
                      1.0f, 0, s.gsum, s.loss);
   if (hipMemcpyAsync(grad, s.gsum, kNParam * sizeof(float), hipMemcpyDeviceToHost, st) !=
@@ -544,7 +658,7 @@ inline int mlp_train(MlpState& s, hipStream_t st, const Phys& P, const Cfg& cfg,
   (void)hipMemsetAsync(s.adam_v, 0, kNParam * sizeof(float), st);
   hipLaunchKernelGGL(k_to_bf16, dim3((kNParam + 255) / 256), dim3(256), 0, st, (const float*)s.w,
                      s.wb, kNParam);
-  const int gb = (int)std::min<int64_t>(64, (cfg.batch + kTrainThreads - 1) / kTrainThreads);
+  const int gb = train_blocks(cfg.batch);
   if (mlp_ensure_train_buffers(s, gb, std::max<int64_t>(1, cfg.iters))) {
     err = "allocation failed";
     return DPDE_ENOMEM;
@@ -560,7 +674,7 @@ inline int mlp_train(MlpState& s, hipStream_t st, const Phys& P, const Cfg& cfg,
     hipLaunchKernelGGL(k_mlp_fwd_bwd, dim3(gb), dim3(kTrainThreads), 0, st, (const float*)s.w,
                        (const float*)s.xs, (const float*)s.ts, (int64_t)cfg.nsamples, begin,
                        (int64_t)cfg.batch, 1.0f / (float)cfg.batch, s.gpart, s.lpart);
-    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(1), dim3(1024), 0, st, (const float*)s.gpart,
+    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, (const float*)s.gpart,
                        (const double*)s.lpart, gb, (int64_t)cfg.batch, s.w, s.adam_m, s.adam_v,
                        s.wb, (float)lr, (float)(1.0 - b1p), (float)(1.0 - b2p), 1,
                        (float*)nullptr, s.loss + it);

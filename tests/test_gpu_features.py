@@ -148,6 +148,32 @@ def test_mlp_gradients_match_oracle(dp, eos_system):
     assert np.abs(g - go).max() < 2e-5 * scale
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 4095, 4096, 4097, 20001])
+def test_mlp_gradients_at_the_edges_of_the_sample_tiles(dp, eos_system, n):
+    """Batches around 16 samples (a wave's), 64 (a block's) and 4096 (one
+    pass of every block).  FP32 sums in at most a few hundred roundings each:
+    2e-5 of the largest entry, as for the whole gradient above."""
+    rng = np.random.default_rng(100 + n)
+    w = rng.normal(0, 0.5, 1153).astype(np.float32)
+    eos_system.mlp_set(w, np.array([3.0, 3.0, 0.0, 2.3]))
+    x = rng.uniform(-1, 1, n).astype(np.float32)
+    t = rng.uniform(-1, 1, n).astype(np.float32)
+    loss, g = eos_system.mlp_grad(x, t)
+    lo, go = O.mlp_loss_grad(w.astype(np.float64), x.astype(np.float64), t.astype(np.float64))
+    assert loss == pytest.approx(lo, rel=1e-5)
+    assert np.abs(g - go).max() < 2e-5 * np.abs(go).max()
+
+
+def test_mlp_training_batch_wraps_around_the_samples(dp, eos_system):
+    """A batch of 103 out of 50 samples takes each twice and the first three
+    once more: from the same start, its mean loss is that of those samples."""
+    kw = dict(nsamples=50, iters=1, lr=3e-3, seed=5)
+    one = eos_system.mlp_train(batch=50, **kw)[0].astype(np.float64)
+    three = eos_system.mlp_train(batch=3, **kw)[0].astype(np.float64)
+    both = eos_system.mlp_train(batch=103, **kw)[0].astype(np.float64)
+    assert both == pytest.approx((2 * 50 * one + 3 * three) / 103, rel=1e-6)
+
+
 def _as_inferred(w):
     """The weights as inference uses them: W2 (the matrix-core layer) rounded
     to BF16, the input and output layers FP32."""

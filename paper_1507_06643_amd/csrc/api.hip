@@ -83,14 +83,13 @@ struct dpde_handle {
   double box_max = 0.0;  // largest box side over the replicas
   uint32_t* slot = nullptr;  // memory index of each identifier row
   BuildCtl* ctl = nullptr;
-  BuildCtl* ctl_next = nullptr;  // maxima of a kick fused into the previous sweep 2
+  NextMax* ctl_next = nullptr;  // maxima of a kick fused into the previous step's end (kNextSlots)
   unsigned long long* builds = nullptr;
   SkinList skin{};
   bool regen = false;  // regenerate the noise in sweep 2 instead of storing dp_ij
   double *Fx = nullptr, *Fy = nullptr, *Fz = nullptr;
   Vec4* dpi = nullptr;  // dp_i of SER sweep 1
   H3* hv = nullptr;   // (p_i + dp_i/2) / m
-  double* deps = nullptr;
   uint32_t* idk = nullptr;
   double* Ui = nullptr;
   uint32_t *key = nullptr, *ticket = nullptr;
@@ -105,7 +104,7 @@ struct dpde_handle {
   int32_t* rep_tile0 = nullptr;
   int ntiles = 0;
   Fix* partials = nullptr;
-  // observables' partial sums added by the tile sweep 2 into slots
+  // observables' partial sums added by a step's last pair pass into slots
   // (nslots_u per replica)
   Fix* partials_u = nullptr;
   int32_t* rep_tile0_u = nullptr;
@@ -342,7 +341,7 @@ int allocate(dpde_handle* h) {
   const int64_t n = h->n;
   if ((rc = alloc_pstate(h, h->cur)) || (rc = alloc_pstate(h, h->alt))) return rc;
   if ((rc = dalloc(h, &h->Fx, n)) || (rc = dalloc(h, &h->Fy, n)) || (rc = dalloc(h, &h->Fz, n)) ||
-      (rc = dalloc(h, &h->dpi, n)) || (rc = dalloc(h, &h->hv, n)) || (rc = dalloc(h, &h->deps, n)) || (rc = dalloc(h, &h->Ui, n)) ||
+      (rc = dalloc(h, &h->dpi, n)) || (rc = dalloc(h, &h->hv, n)) || (rc = dalloc(h, &h->Ui, n)) ||
       (rc = dalloc(h, &h->Li, n)) ||
       (rc = dalloc(h, &h->idk, n)))
     return rc;
@@ -358,7 +357,7 @@ int allocate(dpde_handle* h) {
   if ((rc = dalloc(h, &h->nl.idx, (size_t)h->phys.cap * n)) || (rc = dalloc(h, &h->nl.count, n)))
     return rc;
   if ((rc = dalloc(h, &h->qid, n)) ||
-      (rc = dalloc(h, &h->ctl, 1)) || (rc = dalloc(h, &h->ctl_next, 1)) ||
+      (rc = dalloc(h, &h->ctl, 1)) || (rc = dalloc(h, &h->ctl_next, kNextSlots)) ||
       (rc = dalloc(h, &h->builds, 1)) ||
       (rc = dalloc(h, &h->skin.idx, (size_t)h->phys.cap * n)) ||
       (rc = dalloc(h, &h->slot, n)) ||
@@ -393,7 +392,7 @@ int allocate(dpde_handle* h) {
   }
   HIPCHK(hipMemset(h->qid, 0, n * sizeof(QIdF)));
   HIPCHK(hipMemset(h->ctl, 0, sizeof(BuildCtl)));
-  HIPCHK(hipMemset(h->ctl_next, 0, sizeof(BuildCtl)));
+  HIPCHK(hipMemset(h->ctl_next, 0, kNextSlots * sizeof(NextMax)));
   HIPCHK(hipMemset(h->builds, 0, sizeof(unsigned long long)));
   h->nl.dex = h->nl.dey = h->nl.dez = nullptr;
   if (!h->regen && ((rc = dalloc(h, &h->nl.dex, (size_t)h->phys.cap * n)) ||
@@ -422,7 +421,7 @@ int allocate(dpde_handle* h) {
   HIPCHK(hipMemcpy(h->tile_begin, tb.data(), tb.size() * sizeof(int64_t), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(h->rep_tile0, rt.data(), rt.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   {
-    // slots of the partial sums the tile sweep 2 adds into, zero between steps
+    // slots of the partial sums a step's last pair pass adds into, zero between steps
     h->nslots_u = h->batch ? kTailSlotsPerReplica
                            : (int)std::min<int64_t>(kTailSlots, blocks(n, kUniqTile));
     std::vector<int32_t> first(h->nrep + 1);
@@ -473,18 +472,28 @@ bool uniq_form(const dpde_handle* h) {
          h->phys.potential == DPDE_POT_SOFT && h->phys.a < 1024.0 && h->phys.fix_ok;
 }
 
-// The end of the step in the tile sweep 2 (StepTail): without the
-// projection, whose observables are taken once, from the state the sweep
-// writes; in a batch only when every replica fills a tile (a tile then spans
-// at most two replicas).
-bool fused_tail(const dpde_handle* h) {
-  return uniq_form(h) && !h->phys.project && (!h->batch || h->min_rep_n >= kUniqTile);
+// 1/T from the new energies inside the pass that updates them (not by the
+// surrogate).
+bool eos_inline(const dpde_handle* h) {
+  return h->phys.eos == DPDE_EOS_LINEAR || h->phys.theta_mode == DPDE_THETA_NEWTON;
 }
 
-// What the end of a step's sweep 2 does besides the sweep.
+// The end of the step in its last pair pass (StepTail): not where the
+// surrogate is evaluated in a pass of its own afterwards (SEM, and the
+// projection), whose 1/T the observables need; in a batch only when every
+// replica fills a tile (a block then spans at most two replicas).  Measured at
+// N = 1,048,576 against the separate kick (45 us), observables (30 us, twice
+// with the projection) and SEM update (45 us): projected SEM 0.663 -> 0.568 ms
+// per step, Hybrid 1.326 -> 1.275, the projected LJ fluid 2.10 -> 2.01.
+bool fused_tail(const dpde_handle* h) {
+  const bool later = h->phys.project || h->phys.scheme == DPDE_SCHEME_SEM;
+  return (eos_inline(h) || !later) && (!h->batch || h->min_rep_n >= kUniqTile);
+}
+
+// What the end of a step's last pair pass does besides the pass.
 enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 
-// Kick and drift (unless the previous step's sweep 2 did them: with_kick
+// Kick and drift (unless the end of the previous step did them: with_kick
 // false); on list-build steps (decided on the device) the binning, the
 // reorder and the skin lists.  Buffer roles are the same either way.
 void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
@@ -558,10 +567,6 @@ void enqueue_forces(dpde_handle* h, int mode) {
   }
 }
 
-bool eos_inline(const dpde_handle* h) {
-  return h->phys.eos == DPDE_EOS_LINEAR || h->phys.theta_mode == DPDE_THETA_NEWTON;
-}
-
 // Hybrid (Sec. 3.2.2): particles binned by domain and ranked by identifier
 // inside it, the intra-domain pairs listed in SSA order with their weights
 // and noise, then one lane per domain runs SSA over its pairs.
@@ -610,15 +615,20 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
   const int b = h->pair_block;
   const int64_t n = h->n;
   const int inl = eos_inline(h) ? 1 : 0;
+  // the projection sets 1/T anew, so the pass before it need not
+  const int inl_now = inl && !(tm != kTailNone && h->phys.project) ? 1 : 0;
   const uint64_t* d_step = h->d_step;
   const int store = h->regen ? 0 : 1;
+  const StepTail tail{h->Fx, h->Fy, h->Fz, h->Ui, h->Li, h->qid, h->ctl_next, h->partials_u,
+                      h->nslots_u,
+                      tm == kTailNone ? 0 : h->phys.project ? kTailNoTheta : kTailAll,
+                      tm == kTailStatsKick ? 1 : 0};
   const uint32_t* dom = h->hybrid ? (const uint32_t*)h->dom : nullptr;
   if (h->hybrid) enqueue_hybrid_ssa<B>(h);
   if (h->phys.scheme == DPDE_SCHEME_SEM) {
     launch(h, "pass_b_sem", k_pass_b<B, PR, 1, MD>, blocks(n * kSubSer, b), b, h->cur, h->nl, n,
-           (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, h->deps, 0, dom, h->status);
-    launch(h, "apply_sem", k_apply_sem, blocks(n, h->aux_block), h->aux_block, h->cur, n, h->phys,
-           (const Vec4*)h->dpi, (const double*)h->deps, inl, h->alt.r, h->status);
+           (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, 0, dom, inl_now, h->alt.r, tail,
+           h->status);
   } else {
     const bool uq = uniq_form(h);
     if (uq) {
@@ -627,23 +637,21 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
              h->status);
     } else {
       launch(h, "pass_b_ser", k_pass_b<B, PR, 0, MD>, blocks(n * kSubSer, b), b, h->cur, h->nl,
-             n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, h->deps, store, dom,
-             h->status);
+             n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, store, dom, inl_now,
+             h->alt.r, tail, h->status);
     }
     // the surrogate's 1/T_i is computed inside sweep 2 (learned-EOS modes)
     const MlpDev m = mlp_dev(h->mlp);
     const int mode = h->mlp.trained ? h->phys.theta_mode : 0;
     auto pass_c = [&](auto kern, unsigned grid, unsigned block) {
       launch(h, "pass_c_ser", kern, grid, block, h->cur, h->nl, n, (const Geo*)h->geo,
-             h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl, m, mode, h->alt.r,
-             h->status);
+             h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now, m, mode, h->alt.r,
+             tail, h->status);
     };
-    StepTail tail{h->Fx, h->Fy, h->Fz, h->Ui, h->Li, h->qid, h->ctl_next, h->partials_u,
-                  h->nslots_u, tm != kTailNone ? 1 : 0, tm == kTailStatsKick ? 1 : 0};
     auto pass_c_uniq = [&](auto kern) {
       launch(h, "pass_c_ser", kern, blocks(n, kUniqTile), 2 * kUniqTile, h->cur, h->nl, n,
-             (const Geo*)h->geo, h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl, m,
-             mode, h->alt.r, tail, h->status);
+             (const Geo*)h->geo, h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now,
+             m, mode, h->alt.r, tail, h->status);
     };
     const unsigned go = blocks(n * kSubSer, b), bo = (unsigned)b;
     if (h->regen) {
@@ -688,15 +696,16 @@ void enqueue_fd(dpde_handle* h, TailMode tm) {
   }
 }
 
-// With `swept`, the tile sweep 2 has written the partial sums already.
-void enqueue_stats_only(dpde_handle* h, int advance, int finish, bool swept = false) {
+// With `swept`, the step's last pair pass has written the partial sums already.
+void enqueue_stats_only(dpde_handle* h, int advance, int finish, bool swept = false,
+                        int clear = kClearAll) {
   if (!swept)
     launch(h, "stats_tiles", k_stats_tiles, h->ntiles, kStatThreads, h->cur,
            (const double*)h->Ui, (const double*)h->Li, (const double*)h->Fx,
            (const double*)h->Fy, (const double*)h->Fz, (const int64_t*)h->tile_begin, h->phys,
            h->partials);
   launch(h, "stats_final", k_stats_final, h->nrep, kStatFinalThreads,
-         swept ? h->partials_u : h->partials, swept ? 1 : 0,
+         swept ? h->partials_u : h->partials, swept ? clear : (int)kClearNone,
          (const int32_t*)(swept ? h->rep_tile0_u : h->rep_tile0), (const Geo*)h->geo, h->d_step,
          advance, h->rec, h->hist, h->hist_cap, h->d_hist_count, h->nrep, finish,
          h->stats_ticket, h->ctl, h->ctl_next, h->builds, h->half_skin2,
@@ -705,14 +714,15 @@ void enqueue_stats_only(dpde_handle* h, int advance, int finish, bool swept = fa
 
 // Observables of the step; with the projection (Sec. 4.2) the record of the
 // unconstrained update gives E, the internal energies are shifted, and the
-// record is taken again from the projected state.
+// record is taken again from the projected state (the shift takes the sums
+// that it changes itself where the rest is in the slots).
 void enqueue_stats(dpde_handle* h, int advance, bool swept = false) {
   if (advance && h->phys.project) {
-    enqueue_stats_only(h, 0, 0);
+    enqueue_stats_only(h, 0, 0, swept, kClearEnergy);
     const int inl = eos_inline(h) ? 1 : 0;
     launch(h, "project", h->batch ? k_project<true> : k_project<false>, blocks(h->n, h->aux_block),
            h->aux_block, h->cur, h->n, (const Geo*)h->geo, h->phys, (const double*)h->rec,
-           (const double*)h->E0, inl, h->status);
+           (const double*)h->E0, inl, h->partials_u, swept ? h->nslots_u : 0, h->status);
     if (!inl)
       enqueue_theta_mlp(h->mlp, h->stream, h->cur.eps, &h->cur.r->invT, 8, h->n, h->phys,
                         h->status);
@@ -721,9 +731,9 @@ void enqueue_stats(dpde_handle* h, int advance, bool swept = false) {
   enqueue_stats_only(h, advance, 1, swept);
 }
 
-// One step of a call's sequence.  Where the tile sweep 2 takes the end of the
+// One step of a call's sequence.  Where the last pair pass takes the end of the
 // step, the kick of every step but the first runs in the previous step's
-// sweep 2, and the last step leaves its records unkicked: between calls the
+// last pass, and the last step leaves its records unkicked: between calls the
 // state is the end of a step, as without the fusion, with the same bits.
 void enqueue_step(dpde_handle* h, bool first, bool last) {
   const bool fuse = fused_tail(h);

@@ -47,6 +47,15 @@ struct BuildCtl {
   unsigned long long qmax_bits;  // largest |coordinate| outside the box this step
 };
 
+// The same maxima of a step whose kick ran at the end of the previous one,
+// spread over a wave's worth of slots (a cache line each) that the end of that
+// step takes the maximum of.
+constexpr int kNextSlots = kWave;
+struct alignas(128) NextMax {
+  unsigned long long dmax_bits;
+  unsigned long long qmax_bits;
+};
+
 __device__ __forceinline__ bool rebuild_now(const BuildCtl* c, double half_skin2) {
   return c->force != 0u || __longlong_as_double((long long)c->dmax_bits) > half_skin2;
 }
@@ -149,7 +158,7 @@ constexpr int kAuxMaxThreads = 1024;  // largest block of the per-particle kerne
 // d2 the square of an upper bound on the displacement since the last list
 // build and, for a coordinate outside [0, box) (free boundaries), the
 // largest such |q| in qa; a non-finite p or q raises the status.  The one
-// definition of this arithmetic: k_kick and the end of the tile sweep 2
+// definition of this arithmetic: k_kick and the end of a step's last pair pass
 // both call it.
 __device__ __forceinline__ void kick_record(Rec& rc, const double F[3], const Geo& g,
                                             const Phys& P, int kick,

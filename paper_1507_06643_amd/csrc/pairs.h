@@ -787,23 +787,229 @@ struct H3 {
 };
 
 // ---------------------------------------------------------------------------
+// Inverse temperature of the updated internal energy.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ double inv_temperature(const Phys& P, double eps, uint32_t* status) {
+  if (P.eos == 0) return P.cv / eps;
+  int it;
+  const double th = theta_newton_dev(P, eps, theta_start_dev(P, eps), it);
+  if (!(th > 0.0) || !isfinite(th)) atomicOr(status, ST_EOS);
+  return 1.0 / th;
+}
+
+// Observables of a step (the energy of Sec. 2.1, the temperatures of
+// Sec. 2.2) are sums over particles of
+// U, K, sum eps, Px, Py, Pz, sum 1/T, |grad U|^2, Laplacian U, out-of-range count
+constexpr int kStatVals = 10;
+constexpr int kStatBad = 9;
+constexpr int kRecLen = 12;  // record: U K sum-eps E Px Py Pz Tkin Tint n |gradU|^2 lapU
+
+// The per-particle terms of those sums, defined once so that both producers
+// of the partial sums give the same bits.
+__device__ __forceinline__ double sq3(double x, double y, double z) {
+  return x * x + y * y + z * z;
+}
+__device__ __forceinline__ double kinetic(double px, double py, double pz, double mass) {
+  return sq3(px, py, pz) / (2.0 * mass);
+}
+// A value's fixed-point form; a value outside the range adds one to the
+// out-of-range count instead (the record is then NaN).
+__device__ __forceinline__ Fix stat_fix(double x, int& bad) {
+  if (fabs(x) < 0x1p30) return fix_of(x);
+  ++bad;
+  return fix_zero();
+}
+
+// The end of a step fused into its last pair pass (sweep 2, or the one sweep
+// of SEM): each block's partial sums of the finished step's observables, and
+// the next step's kick and drift on the records it writes, with the maxima of
+// that step's list-build decision.  Kicking requires the sums (the separate
+// observables pass reads the records, which would then be kicked).  In a batch
+// every replica holds at least a tile's particles, so a block spans at most
+// two replicas.
+struct StepTail {
+  const double* Fx;  // F of the step (pass A)
+  const double* Fy;
+  const double* Fz;
+  const double* Ui;  // per-particle shares of U and of its Laplacian
+  const double* Li;
+  const QIdF* ref;   // positions at the last list build (FP32)
+  NextMax* next;     // the next step's maxima; the step's end moves them into the build control
+  Fix* partials;     // kStatVals per slot, cleared by their reader
+  int slots;         // slots per replica: tile t adds into slot t % slots of its replica(s)
+  int stats;         // add the partial sums (kTailAll, or kTailNoTheta)
+  int kick;          // kick and drift the written records
+};
+// Every sum, or all but that of 1/T: with the projection, which follows, sets
+// the energies and temperatures anew.
+constexpr int kTailAll = 1, kTailNoTheta = 2;
+
+// Slots of the partial sums: tiles in flight together (consecutive ones) add
+// into different slots, and the final pass reads two per lane; a batch's
+// replicas take a few each.
+constexpr int kTailSlots = 128;
+constexpr int kTailSlotsPerReplica = 4;
+
+// dst += v exactly, in any order of the adds to dst: the low words add
+// modulo 2^64, and the add that wraps them (known from the old value the
+// atomic returns) carries one into the high word.
+__device__ __forceinline__ void fix_atomic_add(Fix* dst, Fix v) {
+  unsigned long long* lo = reinterpret_cast<unsigned long long*>(&dst->lo);
+  unsigned long long* hi = reinterpret_cast<unsigned long long*>(&dst->hi);
+  const unsigned long long old = atomicAdd(lo, (unsigned long long)v.lo);
+  const unsigned long long carry = (old + (unsigned long long)v.lo < old) ? 1ull : 0ull;
+  const unsigned long long h = (unsigned long long)v.hi + carry;
+  if (h) atomicAdd(hi, h);
+}
+
+constexpr int kUniqWaves = 2 * kUniqTile / kWave;  // waves of a tile sweep's block
+
+// One sum over the wave's even lanes and another over its odd lanes (the
+// butterfly rounds never pair an even lane with an odd one); lanes 0 and 1
+// store them as values ke and ko of wave w.
+__device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[kUniqWaves], int ke, int ko,
+                                               int w) {
+#pragma unroll
+  for (int off = kWave / 2; off > 1; off >>= 1) {
+    Fix b;
+    b.lo = (uint64_t)__shfl_xor((long long)f.lo, off, kWave);
+    b.hi = (int64_t)__shfl_xor((long long)f.hi, off, kWave);
+    f = fix_add(f, b);
+  }
+  const int lane = threadIdx.x % kWave;
+  if (lane == 0) out[ke][w] = f;
+  if (lane == 1) out[ko][w] = f;
+}
+
+// The work of a StepTail in one block, two lanes per particle.
+template <bool BATCH>
+struct TailSums {
+  Fix (*stat)[kStatVals][kUniqWaves];  // LDS, a set of sums per replica met (two in a batch)
+  uint32_t rep0 = 0u, rep1 = 0u;
+  bool two = false, in0 = true, live = false, ev = true;
+  int bad = 0, w = 0;
+
+  // The block's particles are the slots first .. last; a batch's block: the
+  // replica of its first particle (set 0) and, when the last one differs,
+  // the next replica (set 1).
+  __device__ __forceinline__ TailSums(const StepTail& tail, Fix (*lds)[kStatVals][kUniqWaves],
+                                      const Rec* __restrict__ R, int64_t first, int64_t last,
+                                      uint32_t rep, bool live_, bool ev_)
+      : stat(lds), live(live_), ev(ev_), w(threadIdx.x / kWave) {
+    if constexpr (BATCH) {
+      if (tail.stats) {
+        rep0 = R[first].rep;
+        rep1 = R[last].rep;
+      }
+      two = rep1 != rep0;
+      in0 = rep == rep0;
+    }
+  }
+
+  __device__ __forceinline__ void add(Fix f, int ke, int ko) {
+    wave_pair_sums(in0 ? f : fix_zero(), stat[0], ke, ko, w);
+    if constexpr (BATCH) {
+      if (two) wave_pair_sums(in0 ? fix_zero() : f, stat[1], ke, ko, w);
+    }
+  }
+
+  // The particle's values but 1/T split over its two lanes (first lane: U,
+  // sum eps, Py, |grad U|^2, later 1/T; second: K, Px, Pz, Laplacian U and
+  // the particle's out-of-range count), each pair summed over the wave's
+  // first and second lanes apart.
+  __device__ __forceinline__ void state(const StepTail& tail, const Rec& o, double e,
+                                        const double F[3], double mass, int64_t i) {
+    auto put = [&](double xe, double xo, int ke, int ko) {
+      add(live ? stat_fix(ev ? xe : xo, bad) : fix_zero(), ke, ko);
+    };
+    put(live && ev ? tail.Ui[i] : 0.0, kinetic(o.px, o.py, o.pz, mass), 0, 1);
+    put(e, o.px, 2, 3);
+    put(o.py, o.pz, 4, 5);
+    put(sq3(F[0], F[1], F[2]), live && !ev ? tail.Li[i] : 0.0, 7, 8);
+  }
+
+  // 1/T and the out-of-range count, then the block's sums into its slot.
+  // Every thread of the block calls (barrier).
+  __device__ __forceinline__ void finish(const StepTail& tail, double inv_t, int64_t tile) {
+    const Fix ft =
+        live && ev && tail.stats == kTailAll ? stat_fix(inv_t, bad) : fix_zero();
+    const int nbad = bad + __shfl_xor(bad, 1, kWave);  // both lanes of the particle
+    add(ev ? ft : Fix{(uint64_t)(uint32_t)nbad, 0ll}, 6, kStatBad);
+    __syncthreads();
+    if (threadIdx.x < (two ? 2 : 1) * kStatVals) {
+      const int set = threadIdx.x / kStatVals, k = threadIdx.x % kStatVals;
+      const int nw = blockDim.x / kWave;
+      Fix t = fix_zero();
+#pragma unroll
+      for (int q = 0; q < kUniqWaves; ++q)
+        if (q < nw) t = fix_add(t, stat[BATCH ? set : 0][k][q]);
+      const int64_t slot = (int64_t)(set ? rep1 : rep0) * tail.slots + tile % tail.slots;
+      fix_atomic_add(&tail.partials[slot * kStatVals + k], t);
+    }
+  }
+};
+
+// The kick and drift of the record o (on its particle's own lane), and the
+// wave's maxima into one of the slots: one address for all of them made the
+// raises queue up behind each other (N = 65,536: sweep 2 23.9 us, 18.4 so).
+template <bool BATCH>
+__device__ __forceinline__ void tail_kick(const StepTail& tail, bool own, Rec& o,
+                                          const double F[3], const Geo* __restrict__ geo,
+                                          const Phys& P, int64_t i, int64_t tile,
+                                          uint32_t* status) {
+  double d2 = 0.0, qa = 0.0;
+  if (own) {
+    const GeoRef<BATCH> g = geo[BATCH ? o.rep : 0u];
+    kick_record(o, F, g, P, 1, tail.ref, i, d2, qa, status);
+  }
+  NextMax* next = tail.next + tile % kNextSlots;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) d2 = fmax(d2, __shfl_xor(d2, off, kWave));
+  if (threadIdx.x % kWave == 0) raise_max_bits(&next->dmax_bits, d2);
+  if (__any(qa > 0.0)) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) qa = fmax(qa, __shfl_xor(qa, off, kWave));
+    if (threadIdx.x % kWave == 0) raise_max_bits(&next->qmax_bits, qa);
+  }
+}
+
+// Block status flag made uniform: one read, shared through LDS.
+__device__ __forceinline__ bool block_status_set(const uint32_t* status, uint32_t* flag) {
+  if (threadIdx.x == 0) *flag = *status;
+  __syncthreads();
+  return *flag != 0u;
+}
+
+// ---------------------------------------------------------------------------
 // Pass B (SER sweep 1, and the whole SEM update of eq. SEM_fd).
 // ---------------------------------------------------------------------------
+// SCHEME = 1, SEM: the sweep is the whole update, so its particles' new records
+// (p += dp, eps += d eps, the next 1/T_i where the EOS is inline) go to `out`
+// here, and the end of the step with them; no pass rereads the records.
 template <bool BATCH, int PREC, int SCHEME, int MODEL>
-__global__ __launch_bounds__(kPairBlockMax) void k_pass_b(
+__global__ __launch_bounds__(kPairBlockMax)
+__attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0 && !BATCH ? 6 : 1, 8))) void k_pass_b(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
-    const uint64_t* __restrict__ d_step, Vec4* __restrict__ dpi, H3* __restrict__ hv,
-    double* __restrict__ deps, int store, const uint32_t* __restrict__ dom, uint32_t* status) {
+    const uint64_t* __restrict__ d_step, Vec4* __restrict__ dpi, H3* __restrict__ hv, int store,
+    const uint32_t* __restrict__ dom, int eos_inline, Rec* __restrict__ out, StepTail tail,
+    uint32_t* status) {
+  constexpr int kSets = SCHEME == 1 ? (BATCH ? 2 : 1) : 0;
   const Lanes L = lanes<kSubSer>();
-  if (L.i >= n) return;  // uniform in the group
-  if (status_set(status)) return;
-  const int64_t i = L.i;
+  const bool live = L.i < n;  // uniform in the group
+  if constexpr (SCHEME == 1) {
+    __shared__ uint32_t st_flag;
+    if (block_status_set(status, &st_flag)) return;  // uniform in the block
+  } else {
+    if (!live) return;
+    if (status_set(status)) return;
+  }
+  const int64_t i = live ? L.i : n - 1;
   const uint64_t step = *d_step;
   const Rec* __restrict__ R = s.r;
   const Rec a = R[i];
   const GeoRef<BATCH> g = geo[BATCH ? a.rep : 0u];
   const bool mi = !__all(away_from_faces(g, P, a.qx, a.qy, a.qz));  // uniform in the wave
-  const uint32_t nn = nl.count[i];
+  const uint32_t nn = live ? nl.count[i] : 0u;
   const int64_t st = nl.stride;
   // Hybrid: pairs inside one domain were integrated by SSA; their entries
   // carry a zero increment here
@@ -834,12 +1040,45 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_b(
   ax = group_sum<kSubSer>(ax);
   ay = group_sum<kSubSer>(ay);
   az = group_sum<kSubSer>(az);
-  if constexpr (SCHEME == 1) de = group_sum<kSubSer>(de);
-  if (L.sub == 0) {
+  if constexpr (SCHEME == 1) {
+    __shared__ Fix stat_s[kSets][kStatVals][kUniqWaves];
+    de = group_sum<kSubSer>(de);
+    const bool own = live && L.sub == 0;
+    Rec o = a;
+    o.px += ax;
+    o.py += ay;
+    o.pz += az;
+    const double e = s.eps[i] + de;
+    const bool need_t = own && e > 0.0 && eos_inline;
+    if (own) {
+      s.eps[i] = e;
+      if (!(e > 0.0)) atomicOr(status, ST_NEG_EINT);
+    }
+    const int64_t tile = L.i / L.ppb;  // uniform in the block
+    const int64_t first = tile * L.ppb;
+    TailSums<BATCH> ts(tail, stat_s, R, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
+                       live, L.sub == 0);
+    double F[3] = {0.0, 0.0, 0.0};
+    if (tail.stats || tail.kick) {
+      F[0] = tail.Fx[i];
+      F[1] = tail.Fy[i];
+      F[2] = tail.Fz[i];
+    }
+    if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
+    if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+    // the new 1/T_i once the record (with the old one) is written, so that
+    // only e and i stay live across the EOS
+    if (own) out[i] = o;
+    double inv_t = o.invT;
+    if (need_t) {
+      inv_t = inv_temperature(P, e, status);
+      out[i].invT = inv_t;
+    }
+    if (tail.stats) ts.finish(tail, inv_t, tile);  // uniform
+  } else if (L.sub == 0) {
     dpi[i] = Vec4{ax, ay, az, 0.0};
     hv[i] = H3{fma(ax, P.inv_2m, a.px * P.inv_mass), fma(ay, P.inv_2m, a.py * P.inv_mass),
                  fma(az, P.inv_2m, a.pz * P.inv_mass)};
-    if constexpr (SCHEME == 1) deps[i] = de;
   }
 }
 
@@ -900,13 +1139,6 @@ constexpr uint32_t fix_range_hi() {  // high word of 2^(51-G)
 // The tile of particle j relative to the tile starting at tb, or >= 128.
 __device__ __forceinline__ uint32_t in_tile(uint32_t j, int64_t tb) {
   return j - (uint32_t)tb;
-}
-
-// Block status flag made uniform: one read, shared through LDS.
-__device__ __forceinline__ bool block_status_set(const uint32_t* status, uint32_t* flag) {
-  if (threadIdx.x == 0) *flag = *status;
-  __syncthreads();
-  return *flag != 0u;
 }
 
 // Conservative pair terms of one pair at squared distance r2 (r < rc), as
@@ -1330,17 +1562,6 @@ void k_pass_b_uniq(
 }
 
 // ---------------------------------------------------------------------------
-// Inverse temperature of the updated internal energy.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double inv_temperature(const Phys& P, double eps, uint32_t* status) {
-  if (P.eos == 0) return P.cv / eps;
-  int it;
-  const double th = theta_newton_dev(P, eps, theta_start_dev(P, eps), it);
-  if (!(th > 0.0) || !isfinite(th)) atomicOr(status, ST_EOS);
-  return 1.0 / th;
-}
-
-// ---------------------------------------------------------------------------
 // Pass C (SER sweep 2): d eps_i = -1/2 sum_j dp_ij . (v_ij + (dp_i - dp_j)/(2m))
 // in FP64 for both precisions, then p <- p + dp, eps <- eps + d eps and the
 // next 1/T_i.  The new records go to `out`, never over the records this pass
@@ -1353,24 +1574,19 @@ __device__ __forceinline__ double inv_temperature(const Phys& P, double eps, uin
 // the training range).  The block therefore meets at barriers and takes no
 // early exit before them.
 template <bool BATCH, int PREC, int REGEN, int MODEL, int THETA>
-__global__ __launch_bounds__(kPairBlockMax) void k_pass_c(
+__global__ __launch_bounds__(kPairBlockMax)
+__attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, const Vec4* __restrict__ dpi,
     const H3* __restrict__ hv, int eos_inline, MlpDev m, int mlp_mode, Rec* __restrict__ out,
-    uint32_t* status) {
+    StepTail tail, uint32_t* status) {
   __shared__ float net_x[kPairBlockMax / kSubSer];
   __shared__ float net_y[kPairBlockMax / kSubSer];
+  __shared__ Fix stat_s[BATCH ? 2 : 1][kStatVals][kUniqWaves];
   __shared__ uint32_t st_flag;
   const Lanes L = lanes<kSubSer>();
   const bool live = L.i < n;  // uniform in the group
-  if constexpr (THETA) {
-    if (threadIdx.x == 0) st_flag = *status;
-    __syncthreads();
-    if (st_flag) return;  // uniform in the block
-  } else {
-    if (!live) return;
-    if (status_set(status)) return;
-  }
+  if (block_status_set(status, &st_flag)) return;  // uniform in the block
   const int64_t i = live ? L.i : 0;
   double de = 0.0;
   Rec a{};
@@ -1419,25 +1635,38 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_c(
     de = group_sum<kSubSer>(de);
   }
   const double e = live ? s.eps[i] + de : 1.0;
-  // The record (with the old 1/T_i) is written before the network, so that
-  // only e and i stay live across it; the new 1/T_i follows.
+  // the particle's updated record, formed on both of its lanes; the first
+  // lane writes it
   const bool own = live && L.sub == 0;
   bool need_t = false;
+  Rec o = a;
+  o.px = a.px + di.x;
+  o.py = a.py + di.y;
+  o.pz = a.pz + di.z;
   if (own) {
-    Rec o = a;
-    o.px = a.px + di.x;
-    o.py = a.py + di.y;
-    o.pz = a.pz + di.z;
     s.eps[i] = e;
     if (!(e > 0.0)) {
       atomicOr(status, ST_NEG_EINT);
-    } else if constexpr (THETA) {
-      need_t = true;
-    } else if (eos_inline) {
-      o.invT = inv_temperature(P, e, status);
+    } else {
+      need_t = THETA || eos_inline;
     }
-    out[i] = o;
   }
+  const int64_t tile = L.i / L.ppb;  // uniform in the block
+  const int64_t first = tile * L.ppb;
+  TailSums<BATCH> ts(tail, stat_s, s.r, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
+                     live, L.sub == 0);
+  double F[3] = {0.0, 0.0, 0.0};
+  if ((tail.stats || tail.kick) && live) {
+    F[0] = tail.Fx[i];
+    F[1] = tail.Fy[i];
+    F[2] = tail.Fz[i];
+  }
+  if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
+  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+  // The record (with the old 1/T_i) is written before the EOS, so that only e
+  // and i stay live across it; the new 1/T_i follows.
+  if (own) out[i] = o;
+  double inv_t = o.invT;
   if constexpr (THETA) {
     float y = 0.0f;
     if (mlp_mode != 0) {  // uniform
@@ -1457,89 +1686,14 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_c(
       int it;
       const double th = theta_from_net(P, m, mlp_mode, e, y, it);
       if (!(th > 0.0) || !isfinite(th)) atomicOr(status, ST_EOS);
-      out[i].invT = 1.0 / th;
+      inv_t = 1.0 / th;
+      out[i].invT = inv_t;
     }
+  } else if (need_t) {
+    inv_t = inv_temperature(P, e, status);
+    out[i].invT = inv_t;
   }
-}
-
-// Observables of a step (the energy of Sec. 2.1, the temperatures of
-// Sec. 2.2) are sums over particles of
-// U, K, sum eps, Px, Py, Pz, sum 1/T, |grad U|^2, Laplacian U, out-of-range count
-constexpr int kStatVals = 10;
-constexpr int kStatBad = 9;
-constexpr int kRecLen = 12;  // record: U K sum-eps E Px Py Pz Tkin Tint n |gradU|^2 lapU
-
-// The per-particle terms of those sums, defined once so that both producers
-// of the partial sums give the same bits.
-__device__ __forceinline__ double sq3(double x, double y, double z) {
-  return x * x + y * y + z * z;
-}
-__device__ __forceinline__ double kinetic(double px, double py, double pz, double mass) {
-  return sq3(px, py, pz) / (2.0 * mass);
-}
-// A value's fixed-point form; a value outside the range adds one to the
-// out-of-range count instead (the record is then NaN).
-__device__ __forceinline__ Fix stat_fix(double x, int& bad) {
-  if (fabs(x) < 0x1p30) return fix_of(x);
-  ++bad;
-  return fix_zero();
-}
-
-// The end of a step fused into the tile sweep 2: each tile's partial sums of
-// the finished step's observables, and the next step's kick and drift on the
-// records it writes, with the maxima of that step's list-build decision.
-// Kicking requires the sums (the separate observables pass reads the
-// records, which would then be kicked).  In a batch every replica holds at
-// least a tile's particles, so a tile spans at most two replicas.
-struct StepTail {
-  const double* Fx;  // F of the step (pass A)
-  const double* Fy;
-  const double* Fz;
-  const double* Ui;  // per-particle shares of U and of its Laplacian
-  const double* Li;
-  const QIdF* ref;   // positions at the last list build (FP32)
-  BuildCtl* next;    // the next step's maxima; the step's end moves them into the build control
-  Fix* partials;     // kStatVals per slot, cleared by their reader
-  int slots;         // slots per replica: tile t adds into slot t % slots of its replica(s)
-  int stats;         // add the partial sums
-  int kick;          // kick and drift the written records
-};
-
-// Slots of the partial sums: tiles in flight together (consecutive ones) add
-// into different slots, and the final pass reads two per lane; a batch's
-// replicas take a few each.
-constexpr int kTailSlots = 128;
-constexpr int kTailSlotsPerReplica = 4;
-
-// dst += v exactly, in any order of the adds to dst: the low words add
-// modulo 2^64, and the add that wraps them (known from the old value the
-// atomic returns) carries one into the high word.
-__device__ __forceinline__ void fix_atomic_add(Fix* dst, Fix v) {
-  unsigned long long* lo = reinterpret_cast<unsigned long long*>(&dst->lo);
-  unsigned long long* hi = reinterpret_cast<unsigned long long*>(&dst->hi);
-  const unsigned long long old = atomicAdd(lo, (unsigned long long)v.lo);
-  const unsigned long long carry = (old + (unsigned long long)v.lo < old) ? 1ull : 0ull;
-  const unsigned long long h = (unsigned long long)v.hi + carry;
-  if (h) atomicAdd(hi, h);
-}
-
-constexpr int kUniqWaves = 2 * kUniqTile / kWave;  // waves of a tile sweep's block
-
-// One sum over the wave's even lanes and another over its odd lanes (the
-// butterfly rounds never pair an even lane with an odd one); lanes 0 and 1
-// store them as values ke and ko of wave w.
-__device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[kUniqWaves], int ke, int ko,
-                                               int w) {
-#pragma unroll
-  for (int off = kWave / 2; off > 1; off >>= 1) {
-    Fix b;
-    b.lo = (uint64_t)__shfl_xor((long long)f.lo, off, kWave);
-    b.hi = (int64_t)__shfl_xor((long long)f.hi, off, kWave);
-    f = fix_add(f, b);
-  }
-  const int lane = threadIdx.x % kWave;
-  if (lane == 0) out[ke][w] = f;
-  if (lane == 1) out[ko][w] = f;
+  if (tail.stats) ts.finish(tail, inv_t, tile);  // uniform
 }
 
 // Pass C over the tile's unique pairs: the reinjection term
@@ -1548,15 +1702,16 @@ __device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[kUniqWaves], in
 // internal energies (eq. SER_eint_discretization); then p <- p + dp,
 // eps <- eps + d eps and the next 1/T_i as in k_pass_c (THETA = 1: the
 // surrogate network inside the pass); with a StepTail also the observables'
-// partial sums and the next step's kick.  Occupancy, with stored
-// increments: 6 waves per SIMD fit with the network (its registers are dead
-// by the tail); the inline-EOS instances need 5 to keep the tail out of
-// scratch.  The instances that regenerate the noise hold the pair term's
+// partial sums and the next step's kick.  Occupancy, with stored increments:
+// the record is written before the EOS, so that neither the network nor the
+// inline EOS (its exponentials) adds to the tail's registers, and 6 waves per
+// SIMD fit without scratch (92 VGPRs and 5 waves with the record held across
+// the inline EOS; 256 replicas: 174 -> 155 us).  The instances that regenerate the noise hold the pair term's
 // registers as well and keep the compiler's choice (asked for 5 or 6 they
 // spill).
 template <bool BATCH, int PREC, int REGEN, int MODEL, int THETA>
 __global__ __launch_bounds__(2 * kUniqTile)
-__attribute__((amdgpu_waves_per_eu(REGEN ? 1 : (THETA ? 6 : 5), 8))) void k_pass_c_uniq(
+__attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, const Vec4* __restrict__ dpi,
     const H3* __restrict__ hv, int eos_inline, MlpDev m, int mlp_mode, Rec* __restrict__ out,
@@ -1705,8 +1860,6 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : (THETA ? 6 : 5), 8))) void k_pass
   const double de =
       live ? pair_fix_value((long long)((unsigned long long)X + acc[pl])) : 0.0;
   const double e = live ? s.eps[i] + de : 1.0;
-  // The record (with the old 1/T_i) is written before the network, so that
-  // only e and i stay live across it; the new 1/T_i follows.
   const bool own = live && sub == 0;
   bool need_t = false;
   // the particle's updated record, formed on both of its lanes; the first
@@ -1719,68 +1872,23 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : (THETA ? 6 : 5), 8))) void k_pass
     s.eps[i] = e;
     if (!(e > 0.0)) {
       atomicOr(status, ST_NEG_EINT);
-    } else if constexpr (THETA) {
-      need_t = true;
-    } else if (eos_inline) {
-      o.invT = inv_temperature(P, e, status);
+    } else {
+      need_t = THETA || eos_inline;
     }
   }
-  // The finished step's observables: the particle's values split over its
-  // two lanes (first lane: U, sum eps, Py, |grad U|^2, 1/T; second: K, Px,
-  // Pz, Laplacian U and the particle's out-of-range count), each pair summed
-  // over the wave's first and second lanes apart.
-  // A batch's tile: the replica of its first particle (set 0) and, when the
-  // last one differs, the next replica (set 1).
-  int bad = 0;
+  const int64_t tile = tb / kUniqTile;
+  TailSums<BATCH> ts(tail, stat_s, R, tb, (tb + kUniqTile < n ? tb + kUniqTile : n) - 1, a.rep,
+                     live, sub == 0);
   double F[3] = {0.0, 0.0, 0.0};
-  const bool ev = sub == 0;
-  uint32_t rep0 = 0u, rep1 = 0u;
-  if constexpr (BATCH) {
-    if (tail.stats) {
-      rep0 = R[tb].rep;
-      rep1 = R[(tb + kUniqTile < n ? tb + kUniqTile : n) - 1].rep;
-    }
-  }
-  const bool two = rep1 != rep0;
-  const bool in0 = !BATCH || a.rep == rep0;
-  auto sums = [&](Fix f, int ke, int ko) {
-    wave_pair_sums(in0 ? f : fix_zero(), stat_s[0], ke, ko, w);
-    if constexpr (BATCH) {
-      if (two) wave_pair_sums(in0 ? fix_zero() : f, stat_s[1], ke, ko, w);
-    }
-  };
   if ((tail.stats || tail.kick) && live) {
     F[0] = tail.Fx[i];
     F[1] = tail.Fy[i];
     F[2] = tail.Fz[i];
   }
-  if (tail.stats) {  // uniform
-    auto put = [&](double xe, double xo, int ke, int ko) {
-      sums(live ? stat_fix(ev ? xe : xo, bad) : fix_zero(), ke, ko);
-    };
-    put(live && ev ? tail.Ui[i] : 0.0, kinetic(o.px, o.py, o.pz, P.mass), 0, 1);
-    put(e, o.px, 2, 3);
-    put(o.py, o.pz, 4, 5);
-    put(sq3(F[0], F[1], F[2]), live && !ev ? tail.Li[i] : 0.0, 7, 8);
-  }
-  if (tail.kick) {  // uniform: the next step's first half-kick and drift
-    double d2 = 0.0, qa = 0.0;
-    if (own) {
-      const GeoRef<BATCH> g = geo[BATCH ? a.rep : 0u];
-      kick_record(o, F, g, P, 1, tail.ref, i, d2, qa, status);
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) d2 = fmax(d2, __shfl_xor(d2, off, kWave));
-    if (threadIdx.x % kWave == 0) raise_max_bits(&tail.next->dmax_bits, d2);
-    if (__any(qa > 0.0)) {
-#pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) qa = fmax(qa, __shfl_xor(qa, off, kWave));
-      if (threadIdx.x % kWave == 0) raise_max_bits(&tail.next->qmax_bits, qa);
-    }
-  }
-  // The record (with the old 1/T_i when the network follows) is written
-  // before the network, so that only e and i stay live across it; the new
-  // 1/T_i follows.
+  if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
+  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+  // The record (with the old 1/T_i) is written before the EOS, so that only e
+  // and i stay live across it; the new 1/T_i follows.
   if (own) out[i] = o;
   double inv_t = o.invT;
   if constexpr (THETA) {
@@ -1802,44 +1910,11 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : (THETA ? 6 : 5), 8))) void k_pass
       inv_t = 1.0 / th;
       out[i].invT = inv_t;
     }
+  } else if (need_t) {
+    inv_t = inv_temperature(P, e, status);
+    out[i].invT = inv_t;
   }
-  if (tail.stats) {  // uniform: 1/T and the out-of-range count, then the block's sums
-    const Fix ft = live && ev ? stat_fix(inv_t, bad) : fix_zero();
-    const int nbad = bad + __shfl_xor(bad, 1, kWave);  // both lanes of the particle
-    sums(ev ? ft : Fix{(uint64_t)(uint32_t)nbad, 0ll}, 6, kStatBad);
-    __syncthreads();
-    if (threadIdx.x < (two ? 2 : 1) * kStatVals) {
-      const int set = threadIdx.x / kStatVals, k = threadIdx.x % kStatVals;
-      Fix t = fix_zero();
-#pragma unroll
-      for (int q = 0; q < kUniqWaves; ++q) t = fix_add(t, stat_s[BATCH ? set : 0][k][q]);
-      const int64_t slot =
-          (int64_t)(set ? rep1 : rep0) * tail.slots + (tb / kUniqTile) % tail.slots;
-      fix_atomic_add(&tail.partials[slot * kStatVals + k], t);
-    }
-  }
-}
-
-// SEM: apply dp and d eps (both from pass B), then the next 1/T_i.
-__global__ void k_apply_sem(PState s, int64_t n, Phys P, const Vec4* __restrict__ dpi,
-                            const double* __restrict__ deps, int eos_inline,
-                            Rec* __restrict__ out, uint32_t* status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (status_set(status)) return;
-  Rec o = s.r[i];
-  const Vec4 d = dpi[i];
-  o.px += d.x;
-  o.py += d.y;
-  o.pz += d.z;
-  const double e = s.eps[i] + deps[i];
-  s.eps[i] = e;
-  if (!(e > 0.0)) {
-    atomicOr(status, ST_NEG_EINT);
-  } else if (eos_inline) {
-    o.invT = inv_temperature(P, e, status);
-  }
-  out[i] = o;
+  if (tail.stats) ts.finish(tail, inv_t, tile);  // uniform
 }
 
 // 1/T_i for every particle (initialisation and the separate-EOS path).
@@ -1895,22 +1970,20 @@ struct StepNow {
   uint64_t step;
   int64_t hist;
   unsigned long long builds;
+  unsigned long long next_d, next_q;  // the next step's maxima
   bool rebuilt, failed;
 };
 
 __device__ __forceinline__ void step_end(const StepNow& c, uint64_t* d_step, int64_t* d_hist_count,
-                                         BuildCtl* ctl, BuildCtl* next,
-                                         unsigned long long* builds, int advance) {
-  // the next step's maxima (nonzero when its kick ran at the end of this
-  // step's sweep 2) become the build control; the slot is left cleared
-  const unsigned long long nd = next->dmax_bits, nq = next->qmax_bits;
-  next->dmax_bits = 0ull;
-  next->qmax_bits = 0ull;
+                                         BuildCtl* ctl, unsigned long long* builds,
+                                         int advance) {
   if (c.failed) return;
   if (c.rebuilt) *builds = c.builds + 1ull;
-  ctl->dmax_bits = nd;
+  // the next step's maxima (nonzero when its kick ran at the end of this
+  // step's last pair pass) become the build control
+  ctl->dmax_bits = c.next_d;
   ctl->force = 0u;
-  ctl->qmax_bits = nq;
+  ctl->qmax_bits = c.next_q;
   if (advance) {
     *d_step = c.step + 1;
     *d_hist_count = c.hist + 1;
@@ -1918,33 +1991,48 @@ __device__ __forceinline__ void step_end(const StepNow& c, uint64_t* d_step, int
 }
 
 // Per replica: sum the tile partials, write the record (and the history
-// row); with `clear`, leave the partials zero (slots that the tile sweep 2
-// adds into).  With `finish`, the last block to complete also ends the step: a
+// row).  The slots that a step's last pair pass adds into are left zero
+// (kClearAll), or, before the projection, only the sums that it takes anew
+// (kClearEnergy: sum eps and sum 1/T).  With `finish`, the last block to complete also ends the step: a
 // ticket taken after each block's reads of the step and history counters
 // tells it that every other block is done with them.
 constexpr int kStatFinalThreads = kStatVals * kWave;  // one wave per recorded sum
+enum : int { kClearNone = 0, kClearAll = 1, kClearEnergy = 2 };
 
 __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
     Fix* __restrict__ partials, int clear, const int32_t* __restrict__ rep_tile0,
     const Geo* __restrict__ geo, uint64_t* d_step, int advance,
     double* __restrict__ rec, double* __restrict__ hist, int64_t hist_cap,
     int64_t* d_hist_count, int nrep, int finish, uint32_t* ticket, BuildCtl* ctl,
-    BuildCtl* next, unsigned long long* builds, double half_skin2, const uint32_t* status) {
+    NextMax* next, unsigned long long* builds, double half_skin2, const uint32_t* status) {
   const int r = blockIdx.x;
   const int t0 = rep_tile0[r], t1 = rep_tile0[r + 1];
   // the values the record and the end of the step need, requested before
   // the reduction so that their latency overlaps it
-  StepNow now{*d_step, *d_hist_count, 0ull, false, false};
+  StepNow now{*d_step, *d_hist_count, 0ull, 0ull, 0ull, false, false};
   if (finish) {
     now.builds = *builds;
     now.rebuilt = rebuild_now(ctl, half_skin2);
     now.failed = status_set(status);
+    if (threadIdx.x < kWave) {  // the slots' maxima (non-negative doubles order like their bits)
+      const NextMax v = next[threadIdx.x];
+      now.next_d = v.dmax_bits;
+      now.next_q = v.qmax_bits;
+#pragma unroll
+      for (int off = kWave / 2; off > 0; off >>= 1) {
+        const unsigned long long d = __shfl_xor(now.next_d, off, kWave);
+        const unsigned long long q = __shfl_xor(now.next_q, off, kWave);
+        now.next_d = d > now.next_d ? d : now.next_d;
+        now.next_q = q > now.next_q ? q : now.next_q;
+      }
+    }
   }
   const double N = (double)geo[r].n;
   // wave k adds value k over the replica's tiles
   const int k0 = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  // eight partials per lane in flight, then (with clear) their slots zeroed
+  // eight partials per lane in flight, then their slots zeroed where asked
   constexpr int kAhead = 8;
+  const bool zero = clear == kClearAll || (clear == kClearEnergy && (k0 == 2 || k0 == 6));
   Fix acc = fix_zero();
   for (int tb = t0 + lane; tb < t1; tb += kAhead * kWave) {
     Fix v[kAhead];
@@ -1955,7 +2043,7 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) acc = fix_add(acc, v[u]);
-    if (clear) {
+    if (zero) {
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
         const int t = tb + u * kWave;
@@ -1965,6 +2053,8 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
   }
   acc = wave_sum_fix(acc);
   __shared__ Fix tot[kStatVals];
+  __shared__ uint32_t ends;  // this block ends the step
+  if (threadIdx.x == 0) ends = 0u;
   if (lane == 0) tot[k0] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1998,31 +2088,71 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
       if (gridDim.x > 1u) __threadfence();
       if (gridDim.x == 1u || atomicAdd(ticket, 1u) == gridDim.x - 1u) {
         if (gridDim.x > 1u) __threadfence();
-        step_end(now, d_step, d_hist_count, ctl, next, builds, advance);
+        step_end(now, d_step, d_hist_count, ctl, builds, advance);
         atomicExch(ticket, 0u);
+        ends = 1u;
       }
     }
+  }
+  if (!finish) return;  // uniform
+  __syncthreads();
+  if (ends && threadIdx.x < kNextSlots) {  // the slots are left cleared
+    next[threadIdx.x].dmax_bits = 0ull;
+    next[threadIdx.x].qmax_bits = 0ull;
   }
 }
 
 // Projection on the internal energies (Sec. 4.2): eps_i <- eps_i - (E - E0)/N
 // per replica, E from the record of the unconstrained update, then the new
-// 1/T_i when the EOS is evaluated inline.
+// 1/T_i when the EOS is evaluated inline.  With `slots` (where the step's last
+// pair pass has added the other sums) each wave also adds the new sum eps and
+// sum 1/T of its particles, so that no further pass over the records is
+// needed; a batch's replicas then hold at least a tile, so a wave meets at
+// most two of them.
 template <bool BATCH>
 __global__ void k_project(PState s, int64_t n, const Geo* __restrict__ geo, Phys P,
                           const double* __restrict__ rec, const double* __restrict__ E0,
-                          int eos_inline, uint32_t* status) {
+                          int eos_inline, Fix* __restrict__ partials, int slots,
+                          uint32_t* status) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (status_set(status)) return;
-  const uint32_t r = BATCH ? s.r[i].rep : 0u;
-  const double shift = (rec[r * kRecLen + 3] - E0[r]) / (double)geo[r].n;
-  const double e = s.eps[i] - shift;
-  s.eps[i] = e;
-  if (!(e > 0.0)) {
-    atomicOr(status, ST_NEG_EINT);
-  } else if (eos_inline) {
-    s.r[i].invT = inv_temperature(P, e, status);
+  if (status_set(status)) return;  // another block may raise it: uniform in the wave only
+  const bool live = i < n;
+  uint32_t r = 0u;
+  double e = 0.0, inv_t = 0.0;
+  if (live) {
+    r = BATCH ? s.r[i].rep : 0u;
+    const double shift = (rec[r * kRecLen + 3] - E0[r]) / (double)geo[r].n;
+    e = s.eps[i] - shift;
+    s.eps[i] = e;
+    if (!(e > 0.0)) {
+      atomicOr(status, ST_NEG_EINT);
+    } else if (eos_inline) {
+      inv_t = inv_temperature(P, e, status);
+      s.r[i].invT = inv_t;
+    }
+  }
+  if (!slots) return;  // uniform
+  int bad = 0;
+  const Fix fe = live ? stat_fix(e, bad) : fix_zero(), ft = live ? stat_fix(inv_t, bad) : fix_zero();
+  const int lane = threadIdx.x % kWave;
+  const int64_t wave = i / kWave;
+  auto sums = [&](bool mine, uint32_t rep) {
+    const Fix z = fix_zero();
+    const Fix se = wave_sum_fix(mine ? fe : z), st = wave_sum_fix(mine ? ft : z),
+              sb = wave_sum_fix(mine ? Fix{(uint64_t)(uint32_t)bad, 0ll} : z);
+    Fix* p = partials + ((int64_t)rep * slots + wave % slots) * kStatVals;
+    if (lane == 0) fix_atomic_add(p + 2, se);
+    if (lane == 1) fix_atomic_add(p + 6, st);
+    if (lane == 2 && (sb.lo | (uint64_t)sb.hi)) fix_atomic_add(p + kStatBad, sb);
+  };
+  if constexpr (BATCH) {
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
+    sums(live && r == r0, r0);
+    const bool rest = live && r != r0;
+    const unsigned long long others = __ballot(rest);
+    if (others) sums(rest, (uint32_t)__builtin_amdgcn_readlane((int)r, __builtin_ctzll(others)));
+  } else {
+    sums(live, 0u);
   }
 }
 

@@ -267,7 +267,7 @@ int dpde_set_tuning(dpde_handle* h, int32_t pair_block, int32_t aux_block);
  * the same bits, and the two pair forms agree to rounding (their
  * per-particle sums are added in different arithmetic), so the shape can be
  * tuned on the live system.
- *   pair_block  threads per block of the lane-group pair passes (64..256)
+ *   pair_block  threads per block of the both-sides pair passes (64..256)
  *   aux_block   threads per block of the per-particle passes (64..1024)
  *   pairs       form of the SER sweeps (eqs. SER_p, SER_eint_discretization):
  *     DPDE_PAIRS_BOTH_SIDES     every pair term evaluated on both of its
@@ -309,7 +309,7 @@ int dpde_set_shape(dpde_handle* h, const dpde_shape* shape);
 /* Autotuner: time every launch shape over `steps` steps of this system and
  * keep the fastest.  The candidates are the pair form (both forms where the
  * tile form applies), the cell order (order_block 1..4), the lane-group
- * block (64/128/256 threads: the list build and the both-sides passes) and
+ * block (64/128/256 threads: the both-sides passes) and
  * the per-particle block (128/256/512).  The winner is applied as by
  * dpde_set_shape, its pair and per-particle blocks and time per step are
  * returned (read the full shape with dpde_get_shape), and it is recorded in

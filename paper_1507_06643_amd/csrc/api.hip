@@ -181,18 +181,24 @@ hipEvent_t get_event(dpde_handle* h) {
 
 // Launch with optional per-kernel event timing.
 template <typename... KArgs, typename... Args>
-void launch(dpde_handle* h, const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block,
-            Args... args) {
+void launch_lds(dpde_handle* h, const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block,
+                size_t lds, Args... args) {
   if (grid.x == 0) return;
   if (h->profiling) {
     ProfileRec r{name, get_event(h), get_event(h)};
     (void)hipEventRecord(r.a, h->stream);
-    hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, args...);
+    hipLaunchKernelGGL(kernel, grid, block, lds, h->stream, args...);
     (void)hipEventRecord(r.b, h->stream);
     h->prof.push_back(r);
   } else {
-    hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, args...);
+    hipLaunchKernelGGL(kernel, grid, block, lds, h->stream, args...);
   }
+}
+
+template <typename... KArgs, typename... Args>
+void launch(dpde_handle* h, const char* name, void (*kernel)(KArgs...), dim3 grid, dim3 block,
+            Args... args) {
+  launch_lds(h, name, kernel, grid, block, 0, args...);
 }
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -518,14 +524,29 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
          b, h->cur, h->alt, (const uint32_t*)h->bucket, (const uint32_t*)h->cell_start,
          (const uint32_t*)h->key, (const uint32_t*)h->idk, n, (const Geo*)h->geo, h->qid, h->slot,
          ctl, hs2, (const uint32_t*)h->status);
-  const int uniq = uniq_form(h) ? 1 : 0;
-  const int pb = h->pair_block;
-  // the list build reads the reordered records from the spare buffer and
-  // returns them to the working one
-  launch(h, "build_skin", h->batch ? k_build_skin<true> : k_build_skin<false>,
-         blocks(n * kSub, pb), pb, h->alt, h->cur, (const QIdF*)h->qid,
-         (const uint32_t*)h->cell_start, n, (const Geo*)h->geo, std::sqrt(h->rs2), h->box_max,
-         h->skin, ctl, hs2, uniq, h->status);
+  const bool uniq = uniq_form(h);
+  // The list build reads the reordered records from the spare buffer and
+  // returns them to the working one.  Rows staged in LDS: enough for nearly
+  // every list (the tile form ~19 entries, the both-sides form at density 3
+  // ~27, the LJ fluid with its larger capacity ~75), fewer leave more blocks
+  // per CU (48 and 96 rows: 306 and 829 us per build at N = 1M; 36 and 80: 234
+  // and 597).  Small systems take more waves per tile, so that each has a
+  // piece or two (N = 65,536, 512 threads: 41 -> 29 us).
+  const int rows = std::min(h->skin.cap, uniq ? 32 : h->skin.cap > 96 ? 80 : 36);
+  const unsigned tiles = blocks(n, kUniqTile);
+  const int threads = tiles >= 2048 ? 256 : (tiles >= 512 || rows > 48) ? 512 : 1024;
+  auto build = [&](auto kern) {
+    launch_lds(h, "build_skin", kern, tiles, threads, build_lds(rows, threads), h->alt, h->cur,
+               (const QIdF*)h->qid, (const uint32_t*)h->cell_start, n, (const Geo*)h->geo,
+               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, h->status);
+  };
+  if (h->batch) {
+    if (uniq) build(k_build_skin<true, true>);
+    else build(k_build_skin<true, false>);
+  } else {
+    if (uniq) build(k_build_skin<false, true>);
+    else build(k_build_skin<false, false>);
+  }
   // the tile form adds every pair term in fixed point: its lists need no order
   if (!uniq)
     launch(h, "sort_skin", h->skin.cap > 96 ? k_sort_skin<128> : k_sort_skin<64>,

@@ -51,26 +51,6 @@ struct NList {
   int64_t stride;           // n
 };
 
-// Up to two contiguous cell ranges along x for the stencil row (y, z).
-struct Row {
-  int a0, b0, a1, b1;  // inclusive cell x-ranges; a1 > b1 means "no second range"
-};
-
-__device__ __forceinline__ Row stencil_row(int cx, int nc, int periodic) {
-  Row r;
-  r.a1 = 1;
-  r.b1 = 0;
-  if (periodic) {
-    if (cx == 0) { r.a0 = 0; r.b0 = 1; r.a1 = nc - 1; r.b1 = nc - 1; }
-    else if (cx == nc - 1) { r.a0 = nc - 2; r.b0 = nc - 1; r.a1 = 0; r.b1 = 0; }
-    else { r.a0 = cx - 1; r.b0 = cx + 1; }
-  } else {
-    r.a0 = cx > 0 ? cx - 1 : 0;
-    r.b0 = cx < nc - 1 ? cx + 1 : nc - 1;
-  }
-  return r;
-}
-
 __device__ __forceinline__ bool wrap_cell(int& c, int nc, int periodic) {
   if (c < 0) {
     if (!periodic) return false;
@@ -135,7 +115,6 @@ constexpr uint32_t kSubMask = (1u << kSub) - 1u;
 // ~27 skin candidates (pass A, list build) are faster with four.
 constexpr int kSubSer = 2;
 constexpr int kListLds = 64;  // list entries per particle staged in LDS
-constexpr int kBuildLds = 32;  // the same in the list build
 constexpr int kUniqTile = 128;  // particles per tile (= block) of the unique-pair passes
 
 // In the tile form a pair joining two particles of one tile (128 consecutive
@@ -195,137 +174,8 @@ __device__ __forceinline__ uint32_t group_ballot(const Lanes& L, bool pred) {
   return (uint32_t)(__ballot(pred) >> L.shift) & kSubMask;
 }
 
-// Visit the 27-cell stencil.  Its cells come as runs of consecutive memory
-// (three cells of an x-row in row-major order; one run per cell block an
-// x-row crosses in blocked order; a periodic wrap splits a row), which the
-// group first lists in LDS (`runs`: the runs' first indices, then their
-// cumulative ends with the run's periodic image in the top bits); the
-// group's lanes then take the concatenated candidates four at a time (lane
-// sub takes position F + sub), so a trip is cut short only at the end of the
-// stencil, not at the end of every run.  A run reached across a periodic face
-// holds images one box length away: its candidates are compared after that
-// shift (d - s with s = +-L), which for every candidate within the list
-// radius is the minimum image itself, with the same two roundings.
-// `sink(take, j, id_j)` is called on every trip, `take` being r^2 < thr2 and
-// j != i; the trips are uniform across the group, so `sink` may ballot.
-constexpr int kRunsMax = 28;  // runs per stencil: 9 rows x at most 3 pieces
-constexpr int kRunEndBits = 26;  // cumulative end; above it 2 bits per axis: 1 = +L, 2 = -L
-
-template <bool MI, typename Sink>
-__device__ __forceinline__ bool scan_candidates(const Lanes& L, const Geo& g,
-                                                const uint32_t* __restrict__ start,
-                                                const QIdF* __restrict__ qid, float xi, float yi,
-                                                float zi, int cx, int cy, int cz, float thr2,
-                                                uint32_t* runs, Sink&& sink) {
-  const float bx = (float)g.box[0], by = (float)g.box[1], bz = (float)g.box[2];
-  // the runs, in stencil order (uniform across the group; lane 0 records)
-  uint32_t nr = 0, tot = 0;
-  bool whole = true;  // false: the stencil holds more candidates than the run ends can count
-  constexpr uint32_t kEndMask = (1u << kRunEndBits) - 1u;
-  auto add = [&](uint32_t jb, uint32_t je, uint32_t image) {
-    if (je > jb && je - jb > kEndMask - tot) whole = false;
-    if (je > jb && whole) {
-      tot += je - jb;
-      if (L.sub == 0) {
-        runs[nr] = jb;
-        runs[kRunsMax + nr] = tot | (image << kRunEndBits);
-      }
-      ++nr;
-    }
-  };
-  // the image code of a neighbour cell index before wrapping: +L from above,
-  // -L from below (2 bits)
-  auto code = [](int c, int nc) -> uint32_t { return c >= nc ? 1u : (c < 0 ? 2u : 0u); };
-  const Row row = stencil_row(cx, g.nc[0], g.periodic[0]);
-  const int B = g.oblk;
-  // the x image of the second range of a periodic row: the cell left of
-  // cx = 0 or right of cx = nc - 1
-  const uint32_t cx1 = cx == 0 ? 2u : 1u;
-  for (int dz = -1; dz <= 1; ++dz) {
-    int z = cz + dz;
-    const uint32_t iz = code(z, g.nc[2]) << 4;
-    if (!wrap_cell(z, g.nc[2], g.periodic[2])) continue;
-    for (int dy = -1; dy <= 1; ++dy) {
-      int y = cy + dy;
-      const uint32_t iyz = iz | (code(y, g.nc[1]) << 2);
-      if (!wrap_cell(y, g.nc[1], g.periodic[1])) continue;
-      if (B == 1) {  // row-major cells: each x range is one run of memory
-        const int64_t base = g.cell_base + (int64_t)g.nc[0] * (y + (int64_t)g.nc[1] * z);
-        add(start[base + row.a0], start[base + row.b0 + 1], iyz);
-        if (row.a1 <= row.b1) add(start[base + row.a1], start[base + row.b1 + 1], iyz | cx1);
-      } else {
-        // blocked order: an x range is one run per cell block it crosses
-        auto xrun = [&](int a, int b, uint32_t image) {
-          for (int x = a; x <= b;) {
-            const int e = min(b, block_of(x, g) * B + B - 1);
-            const int64_t k0 = g.cell_base + cell_key(g, x, y, z);
-            add(start[k0], start[k0 + (e - x) + 1], image);
-            x = e + 1;
-          }
-        };
-        xrun(row.a0, row.b0, iyz);
-        if (row.a1 <= row.b1) xrun(row.a1, row.b1, iyz | cx1);
-      }
-    }
-  }
-  // the group's lanes read what lane 0 wrote (one wave: a fence suffices)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  auto shift = [](uint32_t c2, float l) { return c2 == 1u ? l : (c2 == 2u ? -l : 0.0f); };
-  // lane-local cursor: run r covers concatenated positions [prev, end) and
-  // holds images shifted by (sx, sy, sz)
-  uint32_t r = 0, prev = 0, word = nr ? runs[kRunsMax] : 0u;
-  uint32_t end = word & kEndMask;
-  float sx = 0.0f, sy = 0.0f, sz = 0.0f;
-  auto image = [&]() {
-    if constexpr (MI) {
-      const uint32_t c = word >> kRunEndBits;
-      sx = shift(c & 3u, bx);
-      sy = shift((c >> 2) & 3u, by);
-      sz = shift(c >> 4, bz);
-    }
-  };
-  image();
-  for (uint32_t F = 0; F < tot; F += kSub) {
-    const uint32_t f = F + L.sub;
-    bool take = false;
-    uint32_t j = 0, idj = 0;
-    if (f < tot) {
-      if (f >= end) {
-        do {
-          prev = end;
-          ++r;
-          word = runs[kRunsMax + r];
-          end = word & kEndMask;
-        } while (f >= end);
-        image();
-      }
-      j = runs[r] + (f - prev);
-      const QIdF c = qid[j];
-      float dx = xi - c.x, dy = yi - c.y, dz = zi - c.z;
-      if constexpr (MI) {
-        dx -= sx;
-        dy -= sy;
-        dz -= sz;
-      }
-      idj = c.id;
-      take = (dx * dx + dy * dy) + dz * dz < thr2 && j != (uint32_t)L.i;
-    }
-    sink(take, j, idj);
-  }
-  return whole;
-}
-
-
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool interior_dim(int c, int nc, int periodic) {
-  // cells c-1..c+1 exist without wrapping
-  return !periodic || (c >= 1 && c <= nc - 2);
-}
-
 // Neighbour lists with a skin.  On a build step every particle collects the
-// particles within rs = rc + skin through the 27-cell stencil (scan_candidates),
+// particles within rs = rc + skin through the 27-cell stencil (k_build_skin),
 // and the list is sorted by neighbour identifier.  Every step then keeps the
 // entries with r < rc, in list order: the pair set is exactly the stencil's,
 // and every per-particle sum below runs in identifier order, so the
@@ -341,31 +191,118 @@ struct SkinList {
   int32_t pad;
 };
 
-// With `uniq` (the tile form) the list keeps only the pairs tile_listed
-// assigns to this particle, holds memory indices, and is not sorted: the
-// passes that read it add their pair terms in fixed point, in any order.
+// The build's block serves a tile of 128 consecutive particles.  Particles of
+// one cell share their 27-cell stencil, so the unit of work is a piece: up to
+// kPiece particles of the tile in one cell, taken by one wave.  The wave lists
+// the stencil's candidates once (27 lanes, a cell each), holds up to
+// kBuildChunks of them per lane in registers, and tests them against the
+// piece's particles one after the other, whose position is then uniform (in
+// scalar registers); the accepted ones take their places from the ballot.
+// Per candidate and particle that leaves the FP32 distance and the list
+// ownership, some 15 vector instructions for 64 candidates; four lanes per
+// particle walking the stencil each for itself took ~75 and issued at 0.88 of
+// the VALU's rate (N = 1M in blocked order, per build: 496 us, 275 so; the
+// both-sides lists 441 us, 234 so; 256 replicas 524 us, 297 so; N = 1000 on 16
+// waves per block 36.9 us, 18.6 so).  The lists are staged in LDS and
+// written row by row (entries beyond the staged rows go straight to memory).
+//
+// UNIQ (the tile form): the list keeps only the pairs tile_listed assigns to
+// this particle, holds memory indices, and is not sorted: the passes that
+// read it add their pair terms in fixed point, in any order.  Otherwise it
+// holds identifier rows (first + id) until k_sort_skin has ordered them and
+// turned them into memory indices.
+// A run reached across a periodic face holds images one box length away: its
+// candidates are compared after that shift (d - s with s = +-L), which for
+// every candidate within the list radius is the minimum image itself, with
+// the same two roundings.
 // s holds the records the reorder has just written in cell order (its
-// candidates come from qid); the group's first lane also returns its
-// particle's record and internal energy to the working buffer `work`.
-template <bool BATCH>
-__global__ __launch_bounds__(kPairBlockMax) void k_build_skin(
+// candidates come from qid); the block also returns its particles' records
+// and internal energies to the working buffer `work`.
+constexpr int kPiece = 32;       // particles of a piece (a cell holds ~7 at density 3)
+constexpr int kBuildChunks = 4;  // candidates per lane held at once
+constexpr int kBuildWindow = kBuildChunks * kWave;
+constexpr int kBuildMaxThreads = 1024;
+
+// LDS of a block beyond its static arrays: the staged rows, and per wave a
+// window's candidate indices and their stencil cells.
+inline size_t build_lds(int rows, int threads) {
+  return (size_t)rows * kUniqTile * sizeof(uint32_t) +
+         (size_t)(threads / kWave) * kBuildWindow * (sizeof(uint32_t) + sizeof(uint8_t));
+}
+
+template <bool BATCH, bool UNIQ>
+__global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
     int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
-    const BuildCtl* ctl, double half_skin2, int uniq, uint32_t* status) {
-  __shared__ uint32_t lst[kBuildLds * (kPairBlockMax / kSub)];
-  __shared__ uint32_t runs_s[2 * kRunsMax * (kPairBlockMax / kSub)];
-  if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
-  const Lanes L = lanes();
-  if (L.i >= n) return;  // uniform in the group
-  uint32_t* runs = runs_s + 2 * kRunsMax * L.pib;
-  const int64_t i = L.i;
-  const Rec* __restrict__ R = s.r;
-  if (L.sub == 0) {
-    work.r[i] = R[i];
-    work.eps[i] = s.eps[i];
+    const BuildCtl* ctl, double half_skin2, int rows, uint32_t* status) {
+  extern __shared__ uint32_t dyn[];  // see build_lds
+  __shared__ uint32_t cell_s[kUniqTile];
+  __shared__ int cx_s[kUniqTile], cy_s[kUniqTile], cz_s[kUniqTile];
+  __shared__ int first_s[kUniqTile + 1];   // first particle of every piece
+  __shared__ uint32_t count_s[kUniqTile];  // list lengths
+  __shared__ unsigned long long head_s[2], piece_s[2];
+  __shared__ int next_s;       // next piece to take
+  __shared__ uint32_t most_s;  // longest list
+  __shared__ uint32_t run_s;
+  if (threadIdx.x == 0) {
+    run_s = !status_set(status) && rebuild_now(ctl, half_skin2);
+    next_s = 0;
+    most_s = 0u;
   }
-  const double xi = R[i].qx, yi = R[i].qy, zi = R[i].qz;
-  const Geo& g = geo[BATCH ? R[i].rep : 0u];
+  __syncthreads();
+  if (!run_s) return;  // uniform in the block
+  uint32_t* lst = dyn;
+  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  uint32_t* src = dyn + rows * kUniqTile + w * kBuildWindow;  // the window's candidates
+  uint8_t* src_cell = reinterpret_cast<uint8_t*>(dyn + rows * kUniqTile +
+                                                 (blockDim.x / kWave) * kBuildWindow) +
+                      w * kBuildWindow;
+  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
+  const int np = (int)(n - tb < kUniqTile ? n - tb : kUniqTile);
+  const Rec* __restrict__ R = s.r + tb;
+  // the tile's cells: a piece starts where the cell changes, and every kPiece
+  // particles inside one
+  const int t = threadIdx.x;
+  if (t < kUniqTile) {
+    uint32_t c = 0xFFFFFFFFu;
+    if (t < np) {
+      const Geo& g = geo[BATCH ? R[t].rep : 0u];
+      const int cx = cell_coord(R[t].qx, g.scale[0], g.nc[0]);
+      const int cy = cell_coord(R[t].qy, g.scale[1], g.nc[1]);
+      const int cz = cell_coord(R[t].qz, g.scale[2], g.nc[2]);
+      cx_s[t] = cx;
+      cy_s[t] = cy;
+      cz_s[t] = cz;
+      c = (uint32_t)(g.cell_base + cell_key(g, cx, cy, cz));
+    }
+    cell_s[t] = c;
+  }
+  // records back to the working buffer, 16 bytes per thread and turn
+  for (int c = t; c < 4 * np; c += blockDim.x)
+    reinterpret_cast<uint4*>(work.r + tb)[c] = reinterpret_cast<const uint4*>(R)[c];
+  for (int c = t; c < np; c += blockDim.x) work.eps[tb + c] = s.eps[tb + c];
+  __syncthreads();
+  const bool head = t < np && (t == 0 || cell_s[t] != cell_s[t - 1]);
+  const unsigned long long heads = __ballot(head);
+  if (w < 2 && lane == 0) head_s[w] = heads;
+  __syncthreads();
+  bool piece = false;
+  if (t < np) {
+    const unsigned long long own = head_s[w] & (~0ull >> (63 - lane));  // heads at or below t
+    const int from = own ? kWave * w + 63 - __clzll(own) : 63 - __clzll(head_s[0]);
+    piece = ((t - from) % kPiece) == 0;
+  }
+  const unsigned long long pieces = __ballot(piece);
+  if (w < 2 && lane == 0) piece_s[w] = pieces;
+  __syncthreads();
+  const int npieces = __popcll(piece_s[0]) + __popcll(piece_s[1]);
+  if (piece) {
+    const int before = (w ? __popcll(piece_s[0]) : 0) +
+                       __popcll(pieces & ((1ull << lane) - 1ull));
+    first_s[before] = t;
+  }
+  if (t == 0) first_s[npieces] = np;
+  __syncthreads();
   // FP32 test radius: rs plus a bound on the rounding of the FP32 distance
   // (conversions of coordinates up to Q = max(|q|, box), their difference,
   // the minimum image and the squared sum stay below 8 2^-24 (Q + rs); twice
@@ -374,47 +311,149 @@ __global__ __launch_bounds__(kPairBlockMax) void k_build_skin(
   const double thr = rs + 16.0 * 0x1p-24 * (Q + rs);
   float thr2 = (float)(thr * thr);
   if ((double)thr2 < thr * thr) thr2 = nextafterf(thr2, INFINITY);
-  const QIdF own = qid[i];
-  const int cx = cell_coord(xi, g.scale[0], g.nc[0]);
-  const int cy = cell_coord(yi, g.scale[1], g.nc[1]);
-  const int cz = cell_coord(zi, g.scale[2], g.nc[2]);
-  uint32_t nn = 0;
   const uint32_t cap = (uint32_t)sl.cap;
-  // the list holds identifier rows (first + id) until k_sort_skin has
-  // ordered them and turned them into memory indices
-  const uint32_t first = (uint32_t)g.first;
-  auto sink = [&](bool take, uint32_t j, uint32_t idj) {
-    if (uniq) take = take && tile_listed((uint32_t)i, j);
-    const uint32_t bits = group_ballot(L, take);
-    if (take) {
-      const uint32_t pos = nn + __popc(bits & ((1u << L.sub) - 1u));
-      const uint32_t row = uniq ? j : first + idj;
-      if (pos < (uint32_t)kBuildLds) lst[pos * L.ppb + L.pib] = row;
-      else if (pos < cap) sl.idx[(int64_t)pos * sl.stride + i] = row;
+  for (;;) {
+    int pc = 0;
+    if (lane == 0) pc = atomicAdd(&next_s, 1);
+    pc = __builtin_amdgcn_readfirstlane(pc);
+    if (pc >= npieces) break;
+    const int p0 = __builtin_amdgcn_readfirstlane(first_s[pc]);
+    const int p1 = __builtin_amdgcn_readfirstlane(first_s[pc + 1]);
+    const int cx = cx_s[p0], cy = cy_s[p0], cz = cz_s[p0];
+    const Geo& g =
+        geo[BATCH ? (uint32_t)__builtin_amdgcn_readfirstlane((int)R[p0].rep) : 0u];
+    // lanes l and l + 32, l < 27: cell l of the stencil, its candidates and
+    // its image
+    const int cell = lane % 32;
+    uint32_t cb = 0, cn = 0;
+    float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+    if (cell < 27) {
+      int x = cx + cell % 3 - 1, y = cy + (cell / 3) % 3 - 1, z = cz + cell / 9 - 1;
+      auto image = [](int c, int nc, double l) {
+        return c >= nc ? (float)l : (c < 0 ? -(float)l : 0.0f);
+      };
+      sx = image(x, g.nc[0], g.box[0]);
+      sy = image(y, g.nc[1], g.box[1]);
+      sz = image(z, g.nc[2], g.box[2]);
+      if (wrap_cell(x, g.nc[0], g.periodic[0]) && wrap_cell(y, g.nc[1], g.periodic[1]) &&
+          wrap_cell(z, g.nc[2], g.periodic[2])) {
+        const int64_t c = g.cell_base + cell_key(g, x, y, z);
+        cb = start[c];
+        cn = start[c + 1] - cb;
+      }
     }
-    nn += __popc(bits);
-  };
-  // waves whose particles all sit away from the periodic faces meet no
-  // image across them
-  const bool interior = interior_dim(cx, g.nc[0], g.periodic[0]) &&
-                        interior_dim(cy, g.nc[1], g.periodic[1]) &&
-                        interior_dim(cz, g.nc[2], g.periodic[2]);
-  const bool whole =
-      __all(interior)
-          ? scan_candidates<false>(L, g, start, qid, own.x, own.y, own.z, cx, cy, cz, thr2, runs,
-                                   sink)
-          : scan_candidates<true>(L, g, start, qid, own.x, own.y, own.z, cx, cy, cz, thr2, runs,
-                                  sink);
-  // a stencil too full to count is a list overflow
-  if (!whole && L.sub == 0) atomicOr(status, ST_OVERFLOW);
-  if (nn > cap) {
-    if (L.sub == 0) atomicOr(status, ST_OVERFLOW);
-    nn = cap;
+    const bool images = __any(cn && (sx != 0.0f || sy != 0.0f || sz != 0.0f));
+    uint32_t pre = cn;  // this cell's first candidate position (prefix over the half-wave)
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+      const uint32_t up = (uint32_t)__shfl_up((int)pre, off, 32);
+      if (cell >= off) pre += up;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)pre, 31);
+    pre -= cn;
+    const QIdF own = qid[tb + (lane < p1 - p0 ? p0 + lane : p0)];  // lane q: particle p0 + q
+    uint32_t counts = 0;  // lane q: entries of particle p0 + q so far
+    const uint32_t first = (uint32_t)g.first;
+    for (uint32_t w0 = 0; w0 < total; w0 += kBuildWindow) {
+      // the cells' two lanes write the window's candidate indices in turn
+      const uint32_t lo = pre > w0 ? pre : w0;
+      const uint32_t hi = pre + cn < w0 + kBuildWindow ? pre + cn : w0 + kBuildWindow;
+      for (uint32_t f = lo + lane / 32; f < hi; f += 2) {
+        src[f - w0] = cb + (f - pre);
+        if (images) src_cell[f - w0] = (uint8_t)cell;  // uniform
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      const uint32_t left = total - w0;  // uniform
+      float qx[kBuildChunks], qy[kBuildChunks], qz[kBuildChunks];
+      float ix[kBuildChunks], iy[kBuildChunks], iz[kBuildChunks];
+      uint32_t row[kBuildChunks], rel[kBuildChunks];
+      unsigned long long live[kBuildChunks], out[kBuildChunks], odd[kBuildChunks];
+#pragma unroll
+      for (int c = 0; c < kBuildChunks; ++c) {
+        const uint32_t f = (uint32_t)(c * kWave + lane);
+        const bool have = f < left;
+        const uint32_t j = have ? src[f] : (uint32_t)tb;
+        const QIdF cand = qid[j];
+        qx[c] = cand.x;
+        qy[c] = cand.y;
+        qz[c] = cand.z;
+        ix[c] = iy[c] = iz[c] = 0.0f;
+        if (images) {  // uniform
+          const int from = have ? src_cell[f] : 0;
+          ix[c] = __shfl(sx, from, kWave);
+          iy[c] = __shfl(sy, from, kWave);
+          iz[c] = __shfl(sz, from, kWave);
+        }
+        row[c] = UNIQ ? j : first + cand.id;
+        rel[c] = j - (uint32_t)tb;
+        live[c] = __ballot(have);
+        out[c] = __ballot(rel[c] >= (uint32_t)kUniqTile);  // in another tile
+        odd[c] = __ballot((rel[c] & 1u) != 0u);
+      }
+      // one particle against the window
+      auto test = [&](int q, auto mi) {
+        const float xi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.x), q));
+        const float yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.y), q));
+        const float zi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.z), q));
+        uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)counts, q);
+        const uint32_t tq = (uint32_t)(p0 + q);
+#pragma unroll
+        for (int c = 0; c < kBuildChunks; ++c) {
+          if ((uint32_t)(c * kWave) >= left) break;  // uniform
+          float dx = xi - qx[c], dy = yi - qy[c], dz = zi - qz[c];
+          if constexpr (decltype(mi)::value) {
+            dx -= ix[c];
+            dy -= iy[c];
+            dz -= iz[c];
+          }
+          unsigned long long m = __ballot((dx * dx + dy * dy) + dz * dz < thr2) & live[c];
+          if constexpr (UNIQ) {
+            // tile_listed: in the tile, the lower index lists a pair of
+            // different parity, the higher one a pair of equal parity
+            const unsigned long long below = __ballot(rel[c] < tq), above = __ballot(rel[c] > tq);
+            const unsigned long long same = (tq & 1u) ? odd[c] : ~odd[c];
+            m &= out[c] | (same & below) | (~same & above);
+          } else {
+            m &= __ballot(rel[c] != tq);
+          }
+          const uint32_t pos =
+              __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+          base += (uint32_t)__popcll(m);
+          if (base <= (uint32_t)rows) {  // uniform: every place is staged
+            if (__builtin_amdgcn_inverse_ballot_w64(m)) lst[pos * kUniqTile + tq] = row[c];
+          } else if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+            if (pos < (uint32_t)rows) lst[pos * kUniqTile + tq] = row[c];
+            else if (pos < cap) sl.idx[(int64_t)pos * sl.stride + tb + tq] = row[c];
+          }
+        }
+        counts = lane == q ? base : counts;
+      };
+      if (images) {
+        for (int q = 0; q < p1 - p0; ++q) test(q, std::true_type{});
+      } else {
+        for (int q = 0; q < p1 - p0; ++q) test(q, std::false_type{});
+      }
+      __builtin_amdgcn_wave_barrier();  // the next window overwrites src
+    }
+    if (lane < p1 - p0) {
+      if (counts > cap) {
+        atomicOr(status, ST_OVERFLOW);
+        counts = cap;
+      }
+      count_s[p0 + lane] = counts;
+      atomicMax(&most_s, counts);
+    }
   }
-  const uint32_t staged = nn < (uint32_t)kBuildLds ? nn : (uint32_t)kBuildLds;
-  for (uint32_t k = L.sub; k < staged; k += kSub)
-    sl.idx[(int64_t)k * sl.stride + i] = lst[k * L.ppb + L.pib];
-  if (L.sub == 0) sl.count[i] = nn;
+  __syncthreads();
+  const uint32_t most = most_s < (uint32_t)rows ? most_s : (uint32_t)rows;
+  for (uint32_t c = t; c < most * kUniqTile; c += blockDim.x) {
+    const uint32_t k = c / kUniqTile, p = c % kUniqTile;
+    if ((int)p < np && k < count_s[p]) sl.idx[(int64_t)k * sl.stride + tb + p] = lst[c];
+  }
+  if (t < np) sl.count[tb + t] = count_s[t];
 }
 
 // Sort each skin list by neighbour identifier and replace the identifier

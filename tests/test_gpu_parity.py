@@ -220,6 +220,24 @@ def test_pairs_far_outside_free_boundary(dp, skin):
     sysm.close()
 
 
+@pytest.mark.parametrize("pairs", [0, 1])
+@pytest.mark.parametrize("n,crowd", [(127, 0), (128, 31), (129, 32), (257, 33), (700, 97), (900, 400)])
+def test_pairs_at_the_edges_of_the_build_tiles(dp, n, crowd, pairs):
+    """Ends of the list build's tiles (128 particles), pieces (32 of one cell)
+    and windows (256 candidates): a crowd of particles in one cell, the rest
+    uniform in a box of three cells a side, where every stencil reaches across
+    the periodic faces; in both pair forms."""
+    box = [3.95, 4.2, 5.3]
+    q, p, e = W.equilibrium_state(n, box, seed=n + crowd)
+    rng = np.random.default_rng(n)
+    q[:crowd] = np.array([0.1, 1.5, 2.8]) + rng.random((crowd, 3)) * 1.1
+    q = np.mod(q, box)
+    s = dp.System(_cfg(dp, n, box, neighbor_cap=1024), q, p, e)
+    s.set_shape(pairs=pairs)
+    assert np.array_equal(s.debug_pairs(), O.pairs(_oparams(n, box), q, "brute"))
+    s.close()
+
+
 def test_pairs_of_evolved_state_match_brute_force(dp):
     n = 600
     L = W.cubic_side(n)

@@ -274,8 +274,8 @@ int dpde_set_tuning(dpde_handle* h, int32_t pair_block, int32_t aux_block);
  *                               particles' lanes and added in FP64 in
  *                               neighbour-identifier order;
  *     DPDE_PAIRS_ONCE_PER_TILE  a pair joining two particles of one tile of
- *                               128 consecutive particles (cell order)
- *                               evaluated once for both, a pair joining two
+ *                               128 consecutive particles (cell order; fewer
+ *                               in small systems) evaluated once for both, a pair joining two
  *                               tiles once per particle; the per-particle
  *                               sums exact in 64-bit fixed point (grid 2^-46,
  *                               a term of magnitude >= 32 fails the step with

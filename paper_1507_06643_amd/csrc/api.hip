@@ -14,6 +14,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/dpde.h"
@@ -496,6 +497,40 @@ bool fused_tail(const dpde_handle* h) {
   return (eos_inline(h) || !later) && (!h->batch || h->min_rep_n >= kUniqTile);
 }
 
+// Tiles of the tile passes: particles per tile, and lanes per particle of pass
+// A and of the sweeps.  A tile is a block; at N = 1000 eight tiles of 128 use
+// eight of the 256 CUs, and a pass takes as long as a lane's chain of list
+// entries, a gather and a pair term (1.5 us) each.  Smaller tiles with more
+// lanes spread the same terms over more CUs and shorten the chain, but list
+// more pairs on both sides (a smaller share lies inside a tile), so a system
+// that fills the chip keeps tiles of 128 and two lanes.  Every sum is exact:
+// the choice changes no bit.  Measured, us per step in FP64 (graph replays,
+// density 3), tiles of 128 / 64 / 32:
+//   N =  1000   50.6 / 45.3 / 41.4     N =  48000   71.7 / 66.7 / 72.4
+//   N =  8000   51.7 / 46.6 / 42.3     N =  65536   73.9 / 73.9 / 88.0
+//   N = 16000   54.0 / 48.0 / 47.2     N =  98304   88.4 / 90.9 / 110.7
+//   N = 32768   59.2 / 56.6 / 59.4     N = 131072  102.8 / 112.2 / 135.2
+struct TileShape {
+  int tile, lanes_a, lanes;
+};
+constexpr TileShape kTiles[3] = {{128, 4, 2}, {64, 4, 4}, {32, 8, 8}};
+constexpr int64_t kTileMidN = 73728, kTileSmallN = 16384;  // largest N of the smaller tiles
+
+int tile_index(const dpde_handle* h) {
+  return h->n <= kTileSmallN ? 2 : h->n <= kTileMidN ? 1 : 0;
+}
+TileShape tile_shape(const dpde_handle* h) { return kTiles[tile_index(h)]; }
+
+// f with the handle's tile shape as a compile-time index into kTiles.
+template <class F>
+void with_tile_shape(const dpde_handle* h, F&& f) {
+  switch (tile_index(h)) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    default: f(std::integral_constant<int, 0>{});
+  }
+}
+
 // What the end of a step's last pair pass does besides the pass.
 enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 
@@ -538,7 +573,7 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   auto build = [&](auto kern) {
     launch_lds(h, "build_skin", kern, tiles, threads, build_lds(rows, threads), h->alt, h->cur,
                (const QIdF*)h->qid, (const uint32_t*)h->cell_start, n, (const Geo*)h->geo,
-               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, h->status);
+               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile_shape(h).tile, h->status);
   };
   if (h->batch) {
     if (uniq) build(k_build_skin<true, true>);
@@ -558,21 +593,25 @@ void enqueue_forces(dpde_handle* h, int mode) {
   const int b = h->pair_block;
   const int64_t n = h->n;
   if (uniq_form(h)) {
-    auto go = [&](auto kern) {
-      launch(h, "pass_a_forces", kern, blocks(n, kUniqTile), kSub * kUniqTile, h->cur, n,
-             (const Geo*)h->geo, h->phys, mode, h->Fx, h->Fy, h->Fz, h->Ui, h->Li, h->skin,
-             h->nl, h->status);
-    };
-    if (h->batch && h->min_rep_n < kWave / kSub) {  // a wave may meet more than two replicas
-      if (h->phys.precision == DPDE_FP32) go(k_pass_a_uniq<true, PREC_F32, true>);
-      else go(k_pass_a_uniq<true, PREC_F64, true>);
-    } else if (h->batch) {
-      if (h->phys.precision == DPDE_FP32) go(k_pass_a_uniq<true, PREC_F32>);
-      else go(k_pass_a_uniq<true, PREC_F64>);
-    } else {
-      if (h->phys.precision == DPDE_FP32) go(k_pass_a_uniq<false, PREC_F32>);
-      else go(k_pass_a_uniq<false, PREC_F64>);
-    }
+    const bool f32 = h->phys.precision == DPDE_FP32;
+    with_tile_shape(h, [&](auto sh) {
+      constexpr TileShape S = kTiles[decltype(sh)::value];
+      constexpr int T = S.tile, K = S.lanes_a;
+      auto go = [&](auto kern) {
+        launch(h, "pass_a_forces", kern, blocks(n, T), K * T, h->cur, n, (const Geo*)h->geo,
+               h->phys, mode, h->Fx, h->Fy, h->Fz, h->Ui, h->Li, h->skin, h->nl, h->status);
+      };
+      if (h->batch && h->min_rep_n < kWave / K) {  // a wave may meet more than two replicas
+        if (f32) go(k_pass_a_uniq<true, PREC_F32, true, T, K>);
+        else go(k_pass_a_uniq<true, PREC_F64, true, T, K>);
+      } else if (h->batch) {
+        if (f32) go(k_pass_a_uniq<true, PREC_F32, false, T, K>);
+        else go(k_pass_a_uniq<true, PREC_F64, false, T, K>);
+      } else {
+        if (f32) go(k_pass_a_uniq<false, PREC_F32, false, T, K>);
+        else go(k_pass_a_uniq<false, PREC_F64, false, T, K>);
+      }
+    });
     return;
   }
   auto go = [&](auto kern) {
@@ -653,9 +692,12 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
   } else {
     const bool uq = uniq_form(h);
     if (uq) {
-      launch(h, "pass_b_ser", k_pass_b_uniq<B, PR, MD>, blocks(n, kUniqTile), 2 * kUniqTile,
-             h->cur, h->nl, n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, store,
-             h->status);
+      with_tile_shape(h, [&](auto sh) {
+        constexpr TileShape S = kTiles[decltype(sh)::value];
+        launch(h, "pass_b_ser", k_pass_b_uniq<B, PR, MD, S.tile, S.lanes>, blocks(n, S.tile),
+               S.lanes * S.tile, h->cur, h->nl, n, (const Geo*)h->geo, h->phys, d_step, h->dpi,
+               h->hv, store, h->status);
+      });
     } else {
       launch(h, "pass_b_ser", k_pass_b<B, PR, 0, MD>, blocks(n * kSubSer, b), b, h->cur, h->nl,
              n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, store, dom, inl_now,
@@ -669,24 +711,32 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
              h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now, m, mode, h->alt.r,
              tail, h->status);
     };
-    auto pass_c_uniq = [&](auto kern) {
-      launch(h, "pass_c_ser", kern, blocks(n, kUniqTile), 2 * kUniqTile, h->cur, h->nl, n,
+    auto pass_c_uniq = [&](auto kern, int tile, int lanes) {
+      launch(h, "pass_c_ser", kern, blocks(n, tile), lanes * tile, h->cur, h->nl, n,
              (const Geo*)h->geo, h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now,
              m, mode, h->alt.r, tail, h->status);
     };
     const unsigned go = blocks(n * kSubSer, b), bo = (unsigned)b;
     if (h->regen) {
       if (uq) {
-        if (inl) pass_c_uniq(k_pass_c_uniq<B, PR, 1, MD, 0>);
-        else pass_c_uniq(k_pass_c_uniq<B, PR, 1, MD, 1>);
+        with_tile_shape(h, [&](auto sh) {
+          constexpr TileShape S = kTiles[decltype(sh)::value];
+          constexpr int T = S.tile, L = S.lanes;
+          if (inl) pass_c_uniq(k_pass_c_uniq<B, PR, 1, MD, 0, T, L>, T, L);
+          else pass_c_uniq(k_pass_c_uniq<B, PR, 1, MD, 1, T, L>, T, L);
+        });
       } else {
         if (inl) pass_c(k_pass_c<B, PR, 1, MD, 0>, go, bo);
         else pass_c(k_pass_c<B, PR, 1, MD, 1>, go, bo);
       }
     } else {
       if (uq) {
-        if (inl) pass_c_uniq(k_pass_c_uniq<B, PR, 0, MD, 0>);
-        else pass_c_uniq(k_pass_c_uniq<B, PR, 0, MD, 1>);
+        with_tile_shape(h, [&](auto sh) {
+          constexpr TileShape S = kTiles[decltype(sh)::value];
+          constexpr int T = S.tile, L = S.lanes;
+          if (inl) pass_c_uniq(k_pass_c_uniq<B, PR, 0, MD, 0, T, L>, T, L);
+          else pass_c_uniq(k_pass_c_uniq<B, PR, 0, MD, 1, T, L>, T, L);
+        });
       } else {
         if (inl) pass_c(k_pass_c<B, PR, 0, MD, 0>, go, bo);
         else pass_c(k_pass_c<B, PR, 0, MD, 1>, go, bo);
@@ -1574,7 +1624,7 @@ int dpde_debug_pairs(dpde_handle* h, int32_t* lohi, int64_t cap, int64_t* npairs
   if (!h || !npairs || (cap > 0 && !lohi)) return fail(DPDE_EINVAL, "NULL argument");
   HIPCHK(hipMemsetAsync(h->counter, 0, sizeof(unsigned long long), h->stream));
   launch(h, "debug_pairs", k_debug_pairs, blocks(h->n, 256), 256, h->cur, h->nl, h->n,
-         (const Geo*)h->geo, uniq_form(h) ? 1 : 0, lohi, cap, h->counter);
+         (const Geo*)h->geo, uniq_form(h) ? tile_shape(h).tile : 0, lohi, cap, h->counter);
   unsigned long long c = 0;
   HIPCHK(hipMemcpyAsync(&c, h->counter, sizeof(c), hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));

@@ -115,19 +115,18 @@ constexpr uint32_t kSubMask = (1u << kSub) - 1u;
 // ~27 skin candidates (pass A, list build) are faster with four.
 constexpr int kSubSer = 2;
 constexpr int kListLds = 64;  // list entries per particle staged in LDS
-constexpr int kUniqTile = 128;  // particles per tile (= block) of the unique-pair passes
+// Particles per tile (= block) of the unique-pair passes: 128, and smaller ones
+// in systems whose tiles of 128 leave the chip idle (TileShape in api.hip).
+constexpr int kUniqTile = 128;
 
-// In the tile form a pair joining two particles of one tile (128 consecutive
+// In the tile form a pair joining two particles of one tile (consecutive
 // memory indices) is listed for one of them only: for the lower memory index
 // when the two indices differ in parity, else for the higher one, so that
 // about half of every particle's pairs inside its tile stay in its list
 // whatever its place in the tile (the lanes of the passes stay evenly
-// loaded).  Which side evaluates a pair changes no sum: every per-particle sum
-// of the tile form is an exact fixed-point sum.
-__device__ __forceinline__ bool tile_listed(uint32_t i, uint32_t j) {
-  if ((i ^ j) >= (uint32_t)kUniqTile) return true;  // different tiles: both lists
-  return ((i ^ j) & 1u) ? (i < j) : (i > j);
-}
+// loaded); a pair joining two tiles is in both lists.  Which side evaluates a
+// pair changes no sum: every per-particle sum of the tile form is an exact
+// fixed-point sum, so neither does the size of the tiles.
 
 // Exclusive prefix of v over the wave and the wave total.
 __device__ __forceinline__ uint32_t wave_prefix(uint32_t v, uint32_t& total) {
@@ -206,8 +205,8 @@ struct SkinList {
 // waves per block 36.9 us, 18.6 so).  The lists are staged in LDS and
 // written row by row (entries beyond the staged rows go straight to memory).
 //
-// UNIQ (the tile form): the list keeps only the pairs tile_listed assigns to
-// this particle, holds memory indices, and is not sorted: the passes that
+// UNIQ (the tile form, tiles of `tile` particles): the list keeps only the pairs
+// that the rule above assigns to this particle, holds memory indices, and is not sorted: the passes that
 // read it add their pair terms in fixed point, in any order.  Otherwise it
 // holds identifier rows (first + id) until k_sort_skin has ordered them and
 // turned them into memory indices.
@@ -234,7 +233,7 @@ template <bool BATCH, bool UNIQ>
 __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
     int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
-    const BuildCtl* ctl, double half_skin2, int rows, uint32_t* status) {
+    const BuildCtl* ctl, double half_skin2, int rows, int tile, uint32_t* status) {
   extern __shared__ uint32_t dyn[];  // see build_lds
   __shared__ uint32_t cell_s[kUniqTile];
   __shared__ int cx_s[kUniqTile], cy_s[kUniqTile], cz_s[kUniqTile];
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
       float qx[kBuildChunks], qy[kBuildChunks], qz[kBuildChunks];
       float ix[kBuildChunks], iy[kBuildChunks], iz[kBuildChunks];
       uint32_t row[kBuildChunks], rel[kBuildChunks];
-      unsigned long long live[kBuildChunks], out[kBuildChunks], odd[kBuildChunks];
+      unsigned long long live[kBuildChunks], odd[kBuildChunks];
 #pragma unroll
       for (int c = 0; c < kBuildChunks; ++c) {
         const uint32_t f = (uint32_t)(c * kWave + lane);
@@ -389,7 +388,6 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
         row[c] = UNIQ ? j : first + cand.id;
         rel[c] = j - (uint32_t)tb;
         live[c] = __ballot(have);
-        out[c] = __ballot(rel[c] >= (uint32_t)kUniqTile);  // in another tile
         odd[c] = __ballot((rel[c] & 1u) != 0u);
       }
       // one particle against the window
@@ -410,11 +408,12 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
           }
           unsigned long long m = __ballot((dx * dx + dy * dy) + dz * dz < thr2) & live[c];
           if constexpr (UNIQ) {
-            // tile_listed: in the tile, the lower index lists a pair of
-            // different parity, the higher one a pair of equal parity
+            // in the tile, the lower index lists a pair of different parity,
+            // the higher one a pair of equal parity
+            const unsigned long long out = __ballot((rel[c] ^ tq) >= (uint32_t)tile);
             const unsigned long long below = __ballot(rel[c] < tq), above = __ballot(rel[c] > tq);
             const unsigned long long same = (tq & 1u) ? odd[c] : ~odd[c];
-            m &= out[c] | (same & below) | (~same & above);
+            m &= out | (same & below) | (~same & above);
           } else {
             m &= __ballot(rel[c] != tq);
           }
@@ -901,13 +900,18 @@ __device__ __forceinline__ void fix_atomic_add(Fix* dst, Fix v) {
   if (h) atomicAdd(hi, h);
 }
 
-constexpr int kUniqWaves = 2 * kUniqTile / kWave;  // waves of a tile sweep's block
+// Waves of a sweep's block: a tile of T particles with LPP lanes each.
+template <int T, int LPP>
+constexpr int tile_waves() {
+  return T * LPP / kWave;
+}
+constexpr int kBothWaves = kPairBlockMax / kWave;  // most waves of a both-sides block
 
 // One sum over the wave's even lanes and another over its odd lanes (the
 // butterfly rounds never pair an even lane with an odd one); lanes 0 and 1
 // store them as values ke and ko of wave w.
-__device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[kUniqWaves], int ke, int ko,
-                                               int w) {
+template <int W>
+__device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[W], int ke, int ko, int w) {
 #pragma unroll
   for (int off = kWave / 2; off > 1; off >>= 1) {
     Fix b;
@@ -920,10 +924,11 @@ __device__ __forceinline__ void wave_pair_sums(Fix f, Fix (*out)[kUniqWaves], in
   if (lane == 1) out[ko][w] = f;
 }
 
-// The work of a StepTail in one block, two lanes per particle.
-template <bool BATCH>
+// The work of a StepTail in one block of at most W waves: two lanes of every
+// particle, of which `ev` is the first (live is false on the others).
+template <bool BATCH, int W>
 struct TailSums {
-  Fix (*stat)[kStatVals][kUniqWaves];  // LDS, a set of sums per replica met (two in a batch)
+  Fix (*stat)[kStatVals][W];  // LDS, a set of sums per replica met (two in a batch)
   uint32_t rep0 = 0u, rep1 = 0u;
   bool two = false, in0 = true, live = false, ev = true;
   int bad = 0, w = 0;
@@ -931,7 +936,7 @@ struct TailSums {
   // The block's particles are the slots first .. last; a batch's block: the
   // replica of its first particle (set 0) and, when the last one differs,
   // the next replica (set 1).
-  __device__ __forceinline__ TailSums(const StepTail& tail, Fix (*lds)[kStatVals][kUniqWaves],
+  __device__ __forceinline__ TailSums(const StepTail& tail, Fix (*lds)[kStatVals][W],
                                       const Rec* __restrict__ R, int64_t first, int64_t last,
                                       uint32_t rep, bool live_, bool ev_)
       : stat(lds), live(live_), ev(ev_), w(threadIdx.x / kWave) {
@@ -980,7 +985,7 @@ struct TailSums {
       const int nw = blockDim.x / kWave;
       Fix t = fix_zero();
 #pragma unroll
-      for (int q = 0; q < kUniqWaves; ++q)
+      for (int q = 0; q < W; ++q)
         if (q < nw) t = fix_add(t, stat[BATCH ? set : 0][k][q]);
       const int64_t slot = (int64_t)(set ? rep1 : rep0) * tail.slots + tile % tail.slots;
       fix_atomic_add(&tail.partials[slot * kStatVals + k], t);
@@ -1080,7 +1085,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
   ay = group_sum<kSubSer>(ay);
   az = group_sum<kSubSer>(az);
   if constexpr (SCHEME == 1) {
-    __shared__ Fix stat_s[kSets][kStatVals][kUniqWaves];
+    __shared__ Fix stat_s[kSets][kStatVals][kBothWaves];
     de = group_sum<kSubSer>(de);
     const bool own = live && L.sub == 0;
     Rec o = a;
@@ -1095,7 +1100,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
     }
     const int64_t tile = L.i / L.ppb;  // uniform in the block
     const int64_t first = tile * L.ppb;
-    TailSums<BATCH> ts(tail, stat_s, R, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
+    TailSums<BATCH, kBothWaves> ts(tail, stat_s, R, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
                        live, L.sub == 0);
     double F[3] = {0.0, 0.0, 0.0};
     if (tail.stats || tail.kick) {
@@ -1125,7 +1130,8 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
 // The SER sweeps with each pair inside a tile evaluated once.
 //
 // Tiles are 128 consecutive particles of the cell order (one block of the
-// sweeps, two lanes per particle).  With cells of side rc + skin about half
+// sweeps, two lanes per particle; smaller tiles with more lanes in small
+// systems).  With cells of side rc + skin about half
 // of all pairs join two particles of one tile.  Pass A leaves such a pair in
 // the list of one of its particles only, so the sweeps evaluate it once:
 // that particle adds the pair term to its own sum and, with an LDS atomic,
@@ -1235,8 +1241,8 @@ __device__ __forceinline__ void pair_conservative(const Phys& P, double dx, doub
   }
 }
 
-// Pass A in the tile form: the tile's 128 particles, four lanes each, walk
-// their skin lists (which hold the pairs tile_listed assigns them); every
+// Pass A in the tile form: the tile's particles, four or eight lanes each, walk
+// their skin lists (each pair inside the tile in one of them); every
 // pair with r < rc goes to the work list of the step and its conservative
 // terms are added once, in fixed point, to both particles (the partner's
 // share through LDS when it lies in the tile; a pair joining two tiles is in
@@ -1255,39 +1261,44 @@ constexpr int kTileSkinLds = 28;  // skin-list entries per particle staged in LD
 // wave's 16 particles (SMALL false) let a wave meet at most two, walked in
 // straight-line code; with smaller ones (SMALL) a loop takes as many as the
 // wave meets, at the cost of registers.
-template <bool BATCH, int PREC, bool SMALL = false>
-__global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_eu(BATCH && SMALL ? 4 : 6, 8))) void k_pass_a_uniq(
+// Tiles of T particles with KS lanes each (see TileShape in api.hip).
+template <bool BATCH, int PREC, bool SMALL, int T, int KS>
+__global__ __launch_bounds__(KS * T) __attribute__((
+    amdgpu_waves_per_eu(T != kUniqTile ? 1 : BATCH && SMALL ? 4 : 6, 8))) void k_pass_a_uniq(
     PState s, int64_t n, const Geo* __restrict__ geo, Phys P, int mode,
     double* __restrict__ Fx, double* __restrict__ Fy, double* __restrict__ Fz,
     double* __restrict__ Ui, double* __restrict__ Li, SkinList sl, NList nl, uint32_t* status) {
+  // staged skin entries per particle: whole trips of the KS lanes
+  constexpr int kStage = (kTileSkinLds + KS - 1) / KS * KS;
   constexpr int GH = 20, GR = 50;
   const double fsc = P.fix_scale_f;  // forces and potential shares: grid 1/fsc
   auto fix_f = [&](double x) { return __double_as_longlong(fma(x, fsc, 0x1.8p52)); };
-  __shared__ unsigned long long acc[6][kUniqTile];  // Fx Fy Fz U Lhi Llo, two's complement
-  __shared__ uint32_t lst[kTileListLds * kUniqTile];
-  __shared__ uint32_t skin[kTileSkinLds * kUniqTile];  // the tile's skin lists, entry-major
+  __shared__ unsigned long long acc[6][T];  // Fx Fy Fz U Lhi Llo, two's complement
+  __shared__ uint32_t lst[kTileListLds * T];
+  __shared__ uint32_t skin[kStage * T];  // the tile's skin lists, entry-major
   __shared__ uint32_t st_flag;
-  for (int c = threadIdx.x; c < 6 * kUniqTile; c += blockDim.x) acc[c / kUniqTile][c % kUniqTile] = 0;
+  for (int c = threadIdx.x; c < 6 * T; c += blockDim.x) acc[c / T][c % T] = 0;
   if (block_status_set(status, &st_flag)) return;  // uniform in the block
-  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
+  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * T;
   {
-    // the first kTileSkinLds entries of every skin list of the tile, loaded
+    // the first kStage entries of every skin list of the tile, loaded
     // row by row (128 consecutive words per row), all loads in flight at once
-    constexpr int kPer = kTileSkinLds * kUniqTile / (kSub * kUniqTile);
+    constexpr int kPer = kStage / KS;
     uint32_t v[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-      const int c = r * (kSub * kUniqTile) + threadIdx.x;
-      const int k = c / kUniqTile, t = c % kUniqTile;
+      const int c = r * (KS * T) + threadIdx.x;
+      const int k = min(c / T, sl.cap - 1);  // inside the list
+      const int t = c % T;
       const int64_t row = tb + t < n ? tb + t : n - 1;
       v[r] = sl.idx[(int64_t)k * sl.stride + row];
     }
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) skin[r * (kSub * kUniqTile) + threadIdx.x] = v[r];
+    for (int r = 0; r < kPer; ++r) skin[r * (KS * T) + threadIdx.x] = v[r];
     __syncthreads();
   }
-  const int pl = threadIdx.x / kSub, sub = threadIdx.x % kSub;
-  const int shift = (threadIdx.x % kWave) & ~(kSub - 1);
+  const int pl = threadIdx.x / KS, sub = threadIdx.x % KS;
+  const int shift = (threadIdx.x % kWave) & ~(KS - 1);
   const int64_t i = tb + pl;
   const bool live = i < n;
   const Rec* __restrict__ R = s.r;
@@ -1320,10 +1331,10 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
         r2 = dist2(dx, dy, dz);
         take = r2 < P.rc2;
       }
-      const uint32_t bits = (uint32_t)(__ballot(take) >> shift) & kSubMask;
+      const uint32_t bits = (uint32_t)(__ballot(take) >> shift) & ((1u << KS) - 1u);
       if (take) {
         const uint32_t pos = nn + __popc(bits & ((1u << sub) - 1u));
-        if (pos < (uint32_t)kTileListLds) lst[pos * kUniqTile + pl] = j;
+        if (pos < (uint32_t)kTileListLds) lst[pos * T + pl] = j;
         else if (pos < cap) nl.idx[(int64_t)pos * nl.stride + i] = j;
         double gx, gy, gz, v, lap;
         pair_conservative<PREC>(P, dx, dy, dz, r2, gx, gy, gz, v, lap);
@@ -1344,7 +1355,7 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
         XLl += fr;
         ++terms;
         const uint32_t rel = in_tile(j, tb);
-        if (rel < (uint32_t)kUniqTile) {  // the partner's share of a pair inside the tile
+        if (rel < (uint32_t)T) {  // the partner's share of a pair inside the tile
           atomicAdd(&acc[0][rel], (unsigned long long)(kFixMagicBits - f0));
           atomicAdd(&acc[1][rel], (unsigned long long)(kFixMagicBits - f1));
           atomicAdd(&acc[2][rel], (unsigned long long)(kFixMagicBits - f2));
@@ -1357,8 +1368,8 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
     };
     // entries staged in LDS: the next trip's position is requested before
     // this trip's pair terms
-    const uint32_t ns0 = ns < (uint32_t)kTileSkinLds ? ns : (uint32_t)kTileSkinLds;
-    uint32_t jn = (uint32_t)sub < ns0 ? skin[sub * kUniqTile + pl] : 0u;
+    const uint32_t ns0 = ns < (uint32_t)kStage ? ns : (uint32_t)kStage;
+    uint32_t jn = (uint32_t)sub < ns0 ? skin[sub * T + pl] : 0u;
     double qnx = 0.0, qny = 0.0, qnz = 0.0;
     if ((uint32_t)sub < ns0) {
       qnx = R[jn].qx;
@@ -1366,12 +1377,12 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
       qnz = R[jn].qz;
     }
     uint32_t base = 0;
-    for (; base < ns0; base += kSub) {
+    for (; base < ns0; base += KS) {
       const uint32_t k = base + sub;
       const uint32_t j = jn;
       const double qjx = qnx, qjy = qny, qjz = qnz;
-      if (k + kSub < ns0) {
-        jn = skin[(k + kSub) * kUniqTile + pl];
+      if (k + KS < ns0) {
+        jn = skin[(k + KS) * T + pl];
         qnx = R[jn].qx;
         qny = R[jn].qy;
         qnz = R[jn].qz;
@@ -1379,7 +1390,7 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
       trip(k, j, qjx, qjy, qjz);
     }
     // longer lists: the rest from memory
-    for (; base < ns; base += kSub) {
+    for (; base < ns; base += KS) {
       const uint32_t k = base + sub;
       uint32_t j = 0u;
       double qjx = 0.0, qjy = 0.0, qjz = 0.0;
@@ -1420,7 +1431,7 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
   XLh -= m;
   XLl -= m;
 #pragma unroll
-  for (int off = 1; off < kSub; off <<= 1) {
+  for (int off = 1; off < KS; off <<= 1) {
     XF0 += __shfl_xor(XF0, off, kWave);
     XF1 += __shfl_xor(XF1, off, kWave);
     XF2 += __shfl_xor(XF2, off, kWave);
@@ -1436,8 +1447,8 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
     nn = cap;
   }
   const uint32_t staged = nn < (uint32_t)kTileListLds ? nn : (uint32_t)kTileListLds;
-  for (uint32_t k = sub; k < staged; k += kSub)
-    nl.idx[(int64_t)k * nl.stride + i] = lst[k * kUniqTile + pl];
+  for (uint32_t k = sub; k < staged; k += KS)
+    nl.idx[(int64_t)k * nl.stride + i] = lst[k * T + pl];
   if (sub == 0) {
     const double fx = (double)(long long)((unsigned long long)XF0 + acc[0][pl]) * P.fix_inv_f;
     const double fy = (double)(long long)((unsigned long long)XF1 + acc[1][pl]) * P.fix_inv_f;
@@ -1458,17 +1469,18 @@ __global__ __launch_bounds__(kSub * kUniqTile) __attribute__((amdgpu_waves_per_e
   }
 }
 
-// A wave of the tile sweeps serves 32 particles, two lanes each.  The first
-// kTileRegular entries of every list go through the lane-pair loop; the
+// A wave of the tile sweeps serves 64 / LPP particles, LPP lanes each.  The
+// first kTileRegular entries of every list go through the lane-group loop; the
 // entries beyond them, few and unevenly spread over the particles, are dealt
 // evenly over all 64 lanes of the wave, so the wave does not wait for its
 // longest list.
 constexpr int kTileRegular = 8;
 
-// The particle (0..31 within the wave) of overflow item x: the last p with
+// The particle (within the wave's PW) of overflow item x: the last p with
 // first[p] <= x, first[] ascending in LDS.
+template <int PW>
 __device__ __forceinline__ int overflow_owner(const uint32_t* first, uint32_t x) {
-  int lo = 0, hi = 31;
+  int lo = 0, hi = PW - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (first[mid] <= x) lo = mid;
@@ -1481,21 +1493,23 @@ __device__ __forceinline__ int overflow_owner(const uint32_t* first, uint32_t x)
 // replica's geometry per lane, fits 6 waves per SIMD only when asked (79
 // VGPRs, no spills); asked the same, the FP32 and projected-model instances
 // would spill, and keep the compiler's choice.
-template <bool BATCH, int PREC, int MODEL>
-__global__ __launch_bounds__(2 * kUniqTile)
-__attribute__((amdgpu_waves_per_eu(BATCH && PREC == PREC_F64 && MODEL == 0 ? 6 : 1, 8)))
+template <bool BATCH, int PREC, int MODEL, int T, int LPP>
+__global__ __launch_bounds__(LPP * T)
+__attribute__((amdgpu_waves_per_eu(
+    BATCH && PREC == PREC_F64 && MODEL == 0 && LPP == 2 ? 6 : 1, 8)))
 void k_pass_b_uniq(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, Vec4* __restrict__ dpi, H3* __restrict__ hv, int store,
     uint32_t* status) {
   // two's-complement sums in unsigned words (the atomic add is modular)
-  __shared__ unsigned long long acc[3][kUniqTile];
-  __shared__ uint32_t first_s[2 * kUniqTile / kWave][32];
+  __shared__ unsigned long long acc[3][T];
+  constexpr int PW = kWave / LPP;
+  __shared__ uint32_t first_s[tile_waves<T, LPP>()][PW];
   __shared__ uint32_t st_flag;
-  for (int c = threadIdx.x; c < 3 * kUniqTile; c += blockDim.x) acc[c / kUniqTile][c % kUniqTile] = 0;
+  for (int c = threadIdx.x; c < 3 * T; c += blockDim.x) acc[c / T][c % T] = 0;
   if (block_status_set(status, &st_flag)) return;  // uniform in the block
-  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
-  const int pl = threadIdx.x >> 1, sub = threadIdx.x & 1;
+  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * T;
+  const int pl = threadIdx.x / LPP, sub = threadIdx.x % LPP;
   const int w = threadIdx.x / kWave;
   uint32_t* first = first_s[w];
   const int64_t i = tb + pl;
@@ -1535,24 +1549,24 @@ void k_pass_b_uniq(
     pair_fix_range(o.dp[1], hi_max);
     pair_fix_range(o.dp[2], hi_max);
     const uint32_t rel = in_tile(j, tb);
-    if (rel < (uint32_t)kUniqTile) {  // the partner's share of a pair inside the tile
+    if (rel < (uint32_t)T) {  // the partner's share of a pair inside the tile
       atomicAdd(&acc[0][rel], (unsigned long long)(kFixMagicBits - f0));
       atomicAdd(&acc[1][rel], (unsigned long long)(kFixMagicBits - f1));
       atomicAdd(&acc[2][rel], (unsigned long long)(kFixMagicBits - f2));
     }
   };
   const uint32_t nreg = nn < (uint32_t)kTileRegular ? nn : (uint32_t)kTileRegular;
-  // this lane's regular entries sub, sub + 2, ...: every index load in flight
-  // at once (addresses clamped to the list, so no load needs a branch)
-  uint32_t jr[kTileRegular / 2];
+  // this lane's regular entries sub, sub + LPP, ...: every index load in
+  // flight at once (addresses clamped to the list, so no load needs a branch)
+  uint32_t jr[kTileRegular / LPP];
 #pragma unroll
-  for (int q = 0; q < kTileRegular / 2; ++q) {
-    const uint32_t k = (uint32_t)(sub + 2 * q);
+  for (int q = 0; q < kTileRegular / LPP; ++q) {
+    const uint32_t k = (uint32_t)(sub + LPP * q);
     const uint32_t kc = k < nreg ? k : (nreg ? nreg - 1u : 0u);
     jr[q] = nreg ? nl.idx[(int64_t)kc * st + i] : 0u;
   }
-  for (int q = 0; q < kTileRegular / 2; ++q) {
-    const uint32_t k = (uint32_t)(sub + 2 * q);
+  for (int q = 0; q < kTileRegular / LPP; ++q) {
+    const uint32_t k = (uint32_t)(sub + LPP * q);
     if (k >= nreg) break;
     long long f0, f1, f2;
     term(a, i, k, jr[q], f0, f1, f2);
@@ -1566,13 +1580,13 @@ void k_pass_b_uniq(
   const uint32_t extra = (sub == 0 && nn > (uint32_t)kTileRegular) ? nn - kTileRegular : 0u;
   const uint32_t pre = wave_prefix(extra, total);
   if (total) {  // uniform in the wave
-    if (sub == 0) first[pl % 32] = pre;
+    if (sub == 0) first[pl % PW] = pre;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     for (uint32_t x = threadIdx.x % kWave; x < total; x += kWave) {
-      const int p = overflow_owner(first, x);
-      const int slot = 32 * w + p;
+      const int p = overflow_owner<PW>(first, x);
+      const int slot = PW * w + p;
       const int64_t ii = tb + slot;
       const uint32_t k = (uint32_t)kTileRegular + (x - first[p]);
       const Rec ra = R[ii];
@@ -1586,9 +1600,12 @@ void k_pass_b_uniq(
   X0 -= terms * kFixMagicBits;
   X1 -= terms * kFixMagicBits;
   X2 -= terms * kFixMagicBits;
-  X0 += __shfl_xor(X0, 1, kWave);
-  X1 += __shfl_xor(X1, 1, kWave);
-  X2 += __shfl_xor(X2, 1, kWave);
+#pragma unroll
+  for (int off = 1; off < LPP; off <<= 1) {
+    X0 += __shfl_xor(X0, off, kWave);
+    X1 += __shfl_xor(X1, off, kWave);
+    X2 += __shfl_xor(X2, off, kWave);
+  }
   if (hi_max >= kFixRangeHi) atomicOr(status, ST_RANGE);
   __syncthreads();
   if (!live || sub) return;
@@ -1621,7 +1638,7 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
     StepTail tail, uint32_t* status) {
   __shared__ float net_x[kPairBlockMax / kSubSer];
   __shared__ float net_y[kPairBlockMax / kSubSer];
-  __shared__ Fix stat_s[BATCH ? 2 : 1][kStatVals][kUniqWaves];
+  __shared__ Fix stat_s[BATCH ? 2 : 1][kStatVals][kBothWaves];
   __shared__ uint32_t st_flag;
   const Lanes L = lanes<kSubSer>();
   const bool live = L.i < n;  // uniform in the group
@@ -1692,7 +1709,7 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
   }
   const int64_t tile = L.i / L.ppb;  // uniform in the block
   const int64_t first = tile * L.ppb;
-  TailSums<BATCH> ts(tail, stat_s, s.r, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
+  TailSums<BATCH, kBothWaves> ts(tail, stat_s, s.r, first, (first + L.ppb < n ? first + L.ppb : n) - 1, a.rep,
                      live, L.sub == 0);
   double F[3] = {0.0, 0.0, 0.0};
   if ((tail.stats || tail.kick) && live) {
@@ -1748,30 +1765,32 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
 // the inline EOS; 256 replicas: 174 -> 155 us).  The instances that regenerate the noise hold the pair term's
 // registers as well and keep the compiler's choice (asked for 5 or 6 they
 // spill).
-template <bool BATCH, int PREC, int REGEN, int MODEL, int THETA>
-__global__ __launch_bounds__(2 * kUniqTile)
-__attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
+template <bool BATCH, int PREC, int REGEN, int MODEL, int THETA, int T, int LPP>
+__global__ __launch_bounds__(LPP * T)
+__attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c_uniq(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, const Vec4* __restrict__ dpi,
     const H3* __restrict__ hv, int eos_inline, MlpDev m, int mlp_mode, Rec* __restrict__ out,
     StepTail tail, uint32_t* status) {
-  __shared__ unsigned long long acc[kUniqTile];  // two's-complement sums (modular adds)
-  __shared__ float net_x[kUniqTile];
-  __shared__ float net_y[kUniqTile];
-  __shared__ uint32_t first_s[kUniqWaves][32];
-  __shared__ double hs[3][kUniqTile];  // the tile's h: partners inside the tile read it here
-  __shared__ Fix stat_s[BATCH ? 2 : 1][kStatVals][kUniqWaves];
+  __shared__ unsigned long long acc[T];  // two's-complement sums (modular adds)
+  __shared__ float net_x[T];
+  __shared__ float net_y[T];
+  constexpr int PW = kWave / LPP;
+  constexpr int W = tile_waves<T, LPP>();
+  __shared__ uint32_t first_s[W][PW];
+  __shared__ double hs[3][T];  // the tile's h: partners inside the tile read it here
+  __shared__ Fix stat_s[BATCH ? 2 : 1][kStatVals][W];
   __shared__ uint32_t st_flag;
-  for (int c = threadIdx.x; c < kUniqTile; c += blockDim.x) acc[c] = 0;
-  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
-  if (threadIdx.x < kUniqTile && tb + threadIdx.x < n) {
+  for (int c = threadIdx.x; c < T; c += blockDim.x) acc[c] = 0;
+  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * T;
+  if (threadIdx.x < T && tb + threadIdx.x < n) {
     const H3 h = hv[tb + threadIdx.x];
     hs[0][threadIdx.x] = h.x;
     hs[1][threadIdx.x] = h.y;
     hs[2][threadIdx.x] = h.z;
   }
   if (block_status_set(status, &st_flag)) return;  // uniform in the block (and hs visible)
-  const int pl = threadIdx.x >> 1, sub = threadIdx.x & 1;
+  const int pl = threadIdx.x / LPP, sub = threadIdx.x % LPP;
   const int w = threadIdx.x / kWave;
   uint32_t* first = first_s[w];
   const int64_t i = tb + pl;
@@ -1799,7 +1818,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
   // h_j of a partner: from LDS inside the tile, else from memory
   auto gather_h = [&](uint32_t j, double& x, double& y, double& z) {
     const uint32_t rel = in_tile(j, tb);
-    if (rel < (uint32_t)kUniqTile) {
+    if (rel < (uint32_t)T) {
       x = hs[0][rel];
       y = hs[1][rel];
       z = hs[2][rel];
@@ -1836,7 +1855,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
     const long long f = pair_fix_raw(eij);
     pair_fix_range(eij, hi_max);
     const uint32_t rel = in_tile(j, tb);
-    if (rel < (uint32_t)kUniqTile) atomicAdd(&acc[rel], (unsigned long long)(f - kFixMagicBits));
+    if (rel < (uint32_t)T) atomicAdd(&acc[rel], (unsigned long long)(f - kFixMagicBits));
     return f;
   };
   if (live) {
@@ -1844,10 +1863,10 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
     const uint32_t nreg = nn < (uint32_t)kTileRegular ? nn : (uint32_t)kTileRegular;
     // this lane's regular entries: every index load in flight at once, then
     // each partner's h requested one entry ahead
-    uint32_t jr[kTileRegular / 2];
+    uint32_t jr[kTileRegular / LPP];
 #pragma unroll
-    for (int q = 0; q < kTileRegular / 2; ++q) {
-      const uint32_t k = (uint32_t)(sub + 2 * q);
+    for (int q = 0; q < kTileRegular / LPP; ++q) {
+      const uint32_t k = (uint32_t)(sub + LPP * q);
       const uint32_t kc = k < nreg ? k : (nreg ? nreg - 1u : 0u);
       jr[q] = nreg ? nl.idx[(int64_t)kc * st + i] : 0u;
     }
@@ -1858,14 +1877,14 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
       if constexpr (!REGEN) load_dp<PREC>(nl, (int64_t)sub * st + i, sx, sy, sz);
     }
 #pragma unroll
-    for (int q = 0; q < kTileRegular / 2; ++q) {
-      const uint32_t k = (uint32_t)(sub + 2 * q);
+    for (int q = 0; q < kTileRegular / LPP; ++q) {
+      const uint32_t k = (uint32_t)(sub + LPP * q);
       if (k >= nreg) break;
       const double cx = hx, cy = hy, cz = hz;
       const double ex = sx, ey = sy, ez = sz;
-      if (q + 1 < kTileRegular / 2 && k + 2 < nreg) {
+      if (q + 1 < kTileRegular / LPP && k + LPP < nreg) {
         gather_h(jr[q + 1], hx, hy, hz);
-        if constexpr (!REGEN) load_dp<PREC>(nl, (int64_t)(k + 2) * st + i, sx, sy, sz);
+        if constexpr (!REGEN) load_dp<PREC>(nl, (int64_t)(k + LPP) * st + i, sx, sy, sz);
       }
       X += term(a, hi, i, k, jr[q], cx, cy, cz, !REGEN, ex, ey, ez);
       ++terms;
@@ -1876,13 +1895,13 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
   const uint32_t extra = (sub == 0 && nn > (uint32_t)kTileRegular) ? nn - kTileRegular : 0u;
   const uint32_t pre = wave_prefix(extra, total);
   if (total) {  // uniform in the wave
-    if (sub == 0) first[pl % 32] = pre;
+    if (sub == 0) first[pl % PW] = pre;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     for (uint32_t x = threadIdx.x % kWave; x < total; x += kWave) {
-      const int p = overflow_owner(first, x);
-      const int slot = 32 * w + p;
+      const int p = overflow_owner<PW>(first, x);
+      const int slot = PW * w + p;
       const int64_t ii = tb + slot;
       const uint32_t k = (uint32_t)kTileRegular + (x - first[p]);
       const uint32_t j = nl.idx[(int64_t)k * st + ii];
@@ -1893,7 +1912,8 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
     }
   }
   X -= terms * kFixMagicBits;
-  X += __shfl_xor(X, 1, kWave);
+#pragma unroll
+  for (int off = 1; off < LPP; off <<= 1) X += __shfl_xor(X, off, kWave);
   if (hi_max >= kFixRangeHi) atomicOr(status, ST_RANGE);
   __syncthreads();
   const double de =
@@ -1901,7 +1921,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
   const double e = live ? s.eps[i] + de : 1.0;
   const bool own = live && sub == 0;
   bool need_t = false;
-  // the particle's updated record, formed on both of its lanes; the first
+  // the particle's updated record, formed on all of its lanes; the first
   // lane writes it
   Rec o = a;
   o.px = a.px + di.x;
@@ -1915,9 +1935,9 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
       need_t = THETA || eos_inline;
     }
   }
-  const int64_t tile = tb / kUniqTile;
-  TailSums<BATCH> ts(tail, stat_s, R, tb, (tb + kUniqTile < n ? tb + kUniqTile : n) - 1, a.rep,
-                     live, sub == 0);
+  const int64_t tile = tb / T;
+  TailSums<BATCH, W> ts(tail, stat_s, R, tb, (tb + T < n ? tb + T : n) - 1, a.rep,
+                        live && sub < 2, sub == 0);
   double F[3] = {0.0, 0.0, 0.0};
   if ((tail.stats || tail.kick) && live) {
     F[0] = tail.Fx[i];
@@ -1935,10 +1955,12 @@ __attribute__((amdgpu_waves_per_eu(REGEN ? 1 : 6, 8))) void k_pass_c_uniq(
     if (mlp_mode != 0) {  // uniform
       if (sub == 0) net_x[pl] = mlp_input(m, e);
       __syncthreads();
-      // wave w takes particles 32 w .. 32 w + 31 of the tile
-      const int col = threadIdx.x % 32;
-      const float yw = mlp_wave32(m.wf, m.wb, net_x[32 * w + col]);
-      if (threadIdx.x % kWave < 32) net_y[32 * w + col] = yw;
+      // wave w < 4 takes particles 32 w .. 32 w + 31 of the tile
+      if (32 * w < T) {  // uniform in the wave
+        const int col = threadIdx.x % 32;
+        const float yw = mlp_wave32(m.wf, m.wb, net_x[32 * w + col]);
+        if (threadIdx.x % kWave < 32) net_y[32 * w + col] = yw;
+      }
       __syncthreads();
       y = net_y[pl];
     }
@@ -2226,9 +2248,9 @@ __global__ void k_debug_order(PState s, int64_t n, const Geo* __restrict__ geo, 
 
 // Every pair of the lists once, as (lower id, higher id) rows.  A pair
 // joining two tiles is in both lists (taken from the lower identifier); with
-// the tile work lists (uniq) a pair inside a tile is in one list only.
+// the tile work lists (tile > 0) a pair inside a tile is in one list only.
 __global__ void k_debug_pairs(PState s, NList nl, int64_t n, const Geo* __restrict__ geo,
-                              int uniq, int32_t* out, int64_t cap,
+                              int tile, int32_t* out, int64_t cap,
                               unsigned long long* counter) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -2237,7 +2259,7 @@ __global__ void k_debug_pairs(PState s, NList nl, int64_t n, const Geo* __restri
   for (uint32_t k = 0; k < nl.count[i]; ++k) {
     const uint32_t j = nl.idx[(int64_t)k * nl.stride + i];
     const uint32_t idj = s.r[j].id;
-    const bool once = uniq && (((uint32_t)i ^ j) < (uint32_t)kUniqTile);
+    const bool once = ((uint32_t)i ^ j) < (uint32_t)tile;
     if (once || a.id < idj) {
       const unsigned long long slot = atomicAdd(counter, 1ull);
       if ((int64_t)slot < cap) {

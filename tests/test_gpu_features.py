@@ -359,6 +359,47 @@ def test_batched_replicas_smaller_than_a_wave_match_single_systems(dp):
     b.close()
 
 
+@pytest.mark.parametrize("nrep", [14, 42])
+@pytest.mark.parametrize("kw", [dict(), dict(precision=1), dict(model=1),
+                                dict(eos=1, theta_mode=1), dict(project=True)])
+def test_tile_shapes_give_the_same_bits(dp, nrep, kw):
+    """Batches of about 28,000 and 85,000 particles run tiles of 64 and of 128;
+    their replicas alone, tiles of 32.  States, observables and records agree
+    bit for bit (replicas that end inside a tile, one open along x)."""
+    sizes, seeds = W.replica_sizes(nrep, 500, 3500, seed=9)
+    cfgs, qs, ps, es = [], [], [], []
+    for r, (nr, sd) in enumerate(zip(sizes, seeds)):
+        L = W.cubic_side(int(nr))
+        box, per = ([1.6 * L, L / 1.25, L / 1.28], [0, 1, 1]) if r == 1 else ([L] * 3, [1, 1, 1])
+        q, p, e = W.equilibrium_state(int(nr), box, seed=900 + r)
+        cfgs.append(dp.Config(n=int(nr), box=box, periodic=per, seed=int(sd), replica=r, dt=0.01,
+                              **kw))
+        qs.append(q); ps.append(p); es.append(e)
+    net = np.random.default_rng(3).normal(0, 0.3, 1153).astype(np.float32)
+
+    def system(*args):
+        s = dp.System(*args)
+        if kw.get("theta_mode"):
+            s.mlp_set(net, np.array([5.0, 3.0, 0.0, 2.3]))
+        return s
+
+    b = system(cfgs, np.vstack(qs), np.vstack(ps), np.concatenate(es))
+    b.step(5)
+    qb, pb, eb, _ = [x.cpu().numpy() if hasattr(x, "cpu") else x for x in b.get_state()]
+    hb = b.history(8)
+    for r in sorted({0, 1, nrep // 2, nrep - 1}):
+        s = system(cfgs[r], qs[r], ps[r], es[r])
+        s.step(5)
+        lo, hi = b.offsets[r], b.offsets[r + 1]
+        q1, p1, e1, _ = [x.cpu().numpy() if hasattr(x, "cpu") else x for x in s.get_state()]
+        assert np.array_equal(qb[lo:hi], q1), r
+        assert np.array_equal(pb[lo:hi], p1), r
+        assert np.array_equal(eb[lo:hi], e1), r
+        assert np.array_equal(hb[:, r], s.history(8)), r
+        s.close()
+    b.close()
+
+
 def test_batched_256_replicas_one_step_vs_oracle(dp):
     """The batched workload itself (256 replicas, sizes uniform in
     [500, 8000] at density 3, one seed per replica, dt = 0.01): after 3 steps

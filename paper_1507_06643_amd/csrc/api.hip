@@ -94,8 +94,9 @@ struct dpde_handle {
   uint32_t* idk = nullptr;
   double* Ui = nullptr;
   uint32_t *key = nullptr, *ticket = nullptr;
-  uint32_t* bucket = nullptr;  // cell buckets in ticket order (before the ranking)
-  uint32_t *cell_count = nullptr, *cell_start = nullptr, *scan_tmp = nullptr;
+  CellBins bins{};  // cells of the list build (its key is `key`)
+  uint32_t* scan_tmp = nullptr;
+  uint32_t* bin_ticket = nullptr;  // blocks of the binning done
   int scan_tiles = 0;
   NList nl{};
   uint32_t* status = nullptr;
@@ -349,14 +350,17 @@ int allocate(dpde_handle* h) {
   if ((rc = alloc_pstate(h, h->cur)) || (rc = alloc_pstate(h, h->alt))) return rc;
   if ((rc = dalloc(h, &h->Fx, n)) || (rc = dalloc(h, &h->Fy, n)) || (rc = dalloc(h, &h->Fz, n)) ||
       (rc = dalloc(h, &h->dpi, n)) || (rc = dalloc(h, &h->hv, n)) || (rc = dalloc(h, &h->Ui, n)) ||
-      (rc = dalloc(h, &h->Li, n)) ||
-      (rc = dalloc(h, &h->idk, n)))
+      (rc = dalloc(h, &h->Li, n)))
     return rc;
-  if ((rc = dalloc(h, &h->key, n)) || (rc = dalloc(h, &h->ticket, n)) ||
-      (rc = dalloc(h, &h->bucket, n)))
+  if ((rc = dalloc(h, &h->key, n)) || (rc = dalloc(h, &h->bins.link, n)) || (rc = dalloc(h, &h->bin_ticket, 1)))
     return rc;
-  if ((rc = dalloc(h, &h->cell_count, h->ncells)) || (rc = dalloc(h, &h->cell_start, h->ncells + 1)))
+  // (the histogram's last words may be read four at a time)
+  if ((rc = dalloc(h, &h->bins.count, h->ncells + 3)) ||
+      (rc = dalloc(h, &h->bins.first, h->ncells)) ||
+      (rc = dalloc(h, &h->bins.start, h->ncells + 1)))
     return rc;
+  h->bins.key = h->key;
+  h->bins.ncells = h->ncells;
   h->scan_tiles = (int)((h->ncells + kScanTile - 1) / kScanTile);
   if (h->scan_tiles > 1024 * 8) return fail(DPDE_EINVAL, "too many cells (%lld)", (long long)h->ncells);
   if ((rc = dalloc(h, &h->scan_tmp, h->scan_tiles + 1))) return rc;
@@ -382,7 +386,8 @@ int allocate(dpde_handle* h) {
     // each intra-domain pair is counted once, from its lower identifier: at
     // most half the list entries
     h->ssa.cap = ((int64_t)h->phys.cap * n + 1) / 2;
-    if ((rc = dalloc(h, &h->dom, n)) || (rc = dalloc(h, &h->dperm, n)) ||
+    if ((rc = dalloc(h, &h->ticket, n)) || (rc = dalloc(h, &h->idk, n)) ||
+        (rc = dalloc(h, &h->dom, n)) || (rc = dalloc(h, &h->dperm, n)) ||
         (rc = dalloc(h, &h->dbucket, n)) || (rc = dalloc(h, &h->lslot, n)) ||
         (rc = dalloc(h, &h->dcount, h->ndoms + 1)) || (rc = dalloc(h, &h->dstart, h->ndoms + 1)) ||
         (rc = dalloc(h, &h->dscan_tmp, (size_t)h->dscan_tiles + 1)) ||
@@ -448,7 +453,9 @@ int allocate(dpde_handle* h) {
   if ((rc = dalloc(h, &h->geo, h->nrep))) return rc;
   HIPCHK(hipMemcpy(h->geo, h->geo_h.data(), h->nrep * sizeof(Geo), hipMemcpyHostToDevice));
   HIPCHK(hipMemset(h->status, 0, 4 * sizeof(uint32_t)));
-  HIPCHK(hipMemset(h->cell_count, 0, h->ncells * sizeof(uint32_t)));
+  HIPCHK(hipMemset(h->bins.count, 0, (h->ncells + 3) * sizeof(uint32_t)));
+  HIPCHK(hipMemset(h->bins.first, 0xFF, h->ncells * sizeof(uint32_t)));
+  HIPCHK(hipMemset(h->bin_ticket, 0, sizeof(uint32_t)));
   HIPCHK(hipMemset(h->d_hist_count, 0, sizeof(int64_t)));
   HIPCHK(hipMemset(h->stats_ticket, 0, sizeof(uint32_t)));
   return DPDE_OK;
@@ -534,6 +541,28 @@ void with_tile_shape(const dpde_handle* h, F&& f) {
 // What the end of a step's last pair pass does besides the pass.
 enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 
+// Launches of the binning: one block for everything, the scan in the binning's
+// last block, or a scan of its own (k_scan_cells up to kScanWideCells cells,
+// where its blocks still read all counts before theirs in a few turns).  Fewer
+// launches save ~2 us each on every step, also those without a build; a build
+// by one block, or a scan by one, takes longer the larger the system, and the
+// last block's turn costs every block a fence.  Measured, us per step in FP64
+// (graph replays, dt 0.005): scan of its own / in the last block / all in one
+// block: N = 1000 38.4 / 37.0 / 35.7, 4000 38.3 / 37.0 / 39.0, 16000 43.8 /
+// 43.0 / 59.4, 32768 53.6 / 53.7 / -, 65536 71.1 / 72.4 / -; with five launches
+// (two for the scan, a scatter into cell buckets) 41.4, 41.7, 47.2, 56.6, 73.9.
+struct BinPlan {
+  unsigned blocks;
+  int threads, scan, whole;
+};
+constexpr int64_t kBinWholeN = 2048, kBinScanCells = 4096, kScanWideCells = 1 << 19;
+BinPlan bin_plan(const dpde_handle* h) {
+  const int scan = h->ncells <= kBinScanCells ? 1 : 0;
+  if (h->n <= kBinWholeN && scan) return {1u, kAuxMaxThreads, 1, 1};
+  const int b = h->aux_block;
+  return {blocks(h->n, b), b, scan, 0};
+}
+
 // Kick and drift (unless the end of the previous step did them: with_kick
 // false); on list-build steps (decided on the device) the binning, the
 // reorder and the skin lists.  Buffer roles are the same either way.
@@ -546,19 +575,24 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
     launch(h, "kick", h->batch ? k_kick<true> : k_kick<false>, blocks(n, b), b, h->cur,
            (const double*)h->Fx, (const double*)h->Fy, (const double*)h->Fz, n,
            (const Geo*)h->geo, h->phys, kick, (const QIdF*)h->qid, h->ctl, h->status);
-  launch(h, "bin_key", h->batch ? k_bin_key<true> : k_bin_key<false>, blocks(n, b), b, h->cur, n,
-         (const Geo*)h->geo, h->key, h->ticket, h->idk, h->cell_count, ctl, hs2, h->status);
-  launch(h, "scan_tiles", k_scan_tiles, h->scan_tiles, kScanThreads, (const uint32_t*)h->cell_count,
-         h->ncells, h->scan_tmp, ctl, hs2);
-  launch(h, "scan_apply", k_scan_apply, h->scan_tiles, kScanThreads, h->cell_count, h->ncells,
-         (const uint32_t*)h->scan_tmp, h->cell_start, ctl, hs2);
-  launch(h, "scatter", k_scatter, blocks(n, b), b, (const uint32_t*)h->key,
-         (const uint32_t*)h->ticket, (const uint32_t*)h->cell_start, n, h->bucket, ctl, hs2,
-         (const uint32_t*)h->status);
-  launch(h, "rank_gather", h->batch ? k_rank_gather<true> : k_rank_gather<false>, blocks(n, b),
-         b, h->cur, h->alt, (const uint32_t*)h->bucket, (const uint32_t*)h->cell_start,
-         (const uint32_t*)h->key, (const uint32_t*)h->idk, n, (const Geo*)h->geo, h->qid, h->slot,
-         ctl, hs2, (const uint32_t*)h->status);
+  // the binning in as few launches as its size allows
+  const BinPlan plan = bin_plan(h);
+  launch(h, "bin", h->batch ? k_bin<true> : k_bin<false>, plan.blocks, plan.threads, h->cur, h->alt,
+         n, (const Geo*)h->geo, h->bins, plan.scan, plan.whole, h->bin_ticket, h->qid, h->slot, ctl,
+         hs2, (const uint32_t*)h->status);
+  if (!plan.scan && h->ncells <= kScanWideCells) {
+    launch(h, "scan_cells", k_scan_cells, blocks(h->ncells, kScanWideTile), kScanWideThreads,
+           h->bins, ctl, hs2);
+  } else if (!plan.scan) {
+    launch(h, "scan_tiles", k_scan_tiles, h->scan_tiles, kScanThreads,
+           (const uint32_t*)h->bins.count, h->ncells, h->scan_tmp, ctl, hs2);
+    launch(h, "scan_apply", k_scan_apply, h->scan_tiles, kScanThreads, h->bins.count, h->ncells,
+           (const uint32_t*)h->scan_tmp, h->bins.start, ctl, hs2);
+  }
+  if (!plan.whole)
+    launch(h, "rank_gather", h->batch ? k_rank_gather<true> : k_rank_gather<false>, blocks(n, b), b,
+           h->cur, h->alt, h->bins, n, (const Geo*)h->geo, h->qid, h->slot, ctl, hs2,
+           (const uint32_t*)h->status);
   const bool uniq = uniq_form(h);
   // The list build reads the reordered records from the spare buffer and
   // returns them to the working one.  Rows staged in LDS: enough for nearly
@@ -572,8 +606,9 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   const int threads = tiles >= 2048 ? 256 : (tiles >= 512 || rows > 48) ? 512 : 1024;
   auto build = [&](auto kern) {
     launch_lds(h, "build_skin", kern, tiles, threads, build_lds(rows, threads), h->alt, h->cur,
-               (const QIdF*)h->qid, (const uint32_t*)h->cell_start, n, (const Geo*)h->geo,
-               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile_shape(h).tile, h->status);
+               (const QIdF*)h->qid, (const uint32_t*)h->bins.start, n, (const Geo*)h->geo,
+               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile_shape(h).tile,
+               h->bins, h->status);
   };
   if (h->batch) {
     if (uniq) build(k_build_skin<true, true>);

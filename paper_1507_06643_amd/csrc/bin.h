@@ -7,13 +7,12 @@
 //
 // Order: particles are kept sorted by the composite key (cell, id).  The sort
 // is a two-level MSD radix sort: digit 1 is the whole cell index (one
-// counting pass: histogram of cells with integer atomics, exclusive scan to
-// cell offsets, scatter by offset + arrival ticket); digit 2 is the particle
-// identifier, finished inside each cell bucket by insertion sort (buckets
-// hold ~3 particles at density 3 with cells of side ~rc).  The resulting order
-// is a pure function of the positions, independent of the previous order and
-// of atomic arrival order, so trajectories are bit reproducible and a resumed
-// run continues exactly.
+// counting pass: histogram of cells with integer atomics, which also chains
+// each cell's particles, then an exclusive scan to cell offsets); digit 2 is
+// the particle identifier: every particle counts the smaller identifiers of
+// its cell's chain.  The resulting order is a pure function of the positions,
+// independent of the previous order and of atomic arrival order, so
+// trajectories are bit reproducible and a resumed run continues exactly.
 #pragma once
 
 #include "common.h"
@@ -257,59 +256,38 @@ __global__ void k_kick(PState s, const double* __restrict__ Fx, const double* __
   }
 }
 
-// Histogram increment with one atomic per run of equal keys among
-// consecutive lanes of a wave; the run's lanes take consecutive tickets.
-// Every lane of the wave calls (dead lanes with live = false).
-__device__ __forceinline__ uint32_t run_ticket(uint32_t c, bool live, uint32_t* count) {
+// Runs of equal keys among consecutive lanes of a wave: the lane that heads
+// this lane's run and the lane behind the run's last.  Every lane of the wave
+// calls (dead lanes with live = false).
+struct LaneRun {
+  bool head;
+  int from, end;
+};
+__device__ __forceinline__ LaneRun lane_run(uint32_t c, bool live) {
   const int lane = threadIdx.x % kWave;
   const uint32_t prev = __shfl_up(c, 1, kWave);
-  const bool head = live && (lane == 0 || prev != c);
-  const unsigned long long heads = __ballot(head);
+  LaneRun r;
+  r.head = live && (lane == 0 || prev != c);
+  const unsigned long long heads = __ballot(r.head);
   const unsigned long long below = (lane == 63) ? ~0ull : ((1ull << (lane + 1)) - 1ull);
-  const int my_head = 63 - __clzll(heads & below);  // last head at or below this lane
-  const unsigned long long above = heads & ~below;   // heads strictly above
-  const int next_head = above ? __ffsll((long long)above) - 1 : kWave;
+  r.from = 63 - __clzll(heads & below);             // last head at or below this lane
+  const unsigned long long above = heads & ~below;  // heads strictly above
+  r.end = above ? __ffsll((long long)above) - 1 : kWave;
   // the run of a head ends before the next head or at the first dead lane
-  const unsigned long long alive = __ballot(live);
-  int run_end = next_head;
-  const unsigned long long dead_above = ~alive & ~below;
-  if (dead_above) {
-    const int first_dead = __ffsll((long long)dead_above) - 1;
-    if (first_dead < run_end) run_end = first_dead;
-  }
-  uint32_t base = 0;
-  if (head) base = atomicAdd(&count[c], (uint32_t)(run_end - lane));
-  base = __shfl(base, my_head, kWave);
-  return base + (uint32_t)(lane - my_head);
+  const unsigned long long dead_above = ~__ballot(live) & ~below;
+  if (dead_above) r.end = min(r.end, __ffsll((long long)dead_above) - 1);
+  return r;
 }
 
-// Cell key of every particle and the cell histogram (list-build steps only).
-// The identifier is also written to a compact array for the per-cell sort.
-// The histogram update is aggregated per run of equal keys inside a wave (the
-// particles are still nearly in cell order): one atomic per run, the run's
-// lanes take consecutive tickets.  Tiles follow the XCD-aware order, so each
-// XCD's atomics touch its own slab of counters.
-template <bool BATCH>
-__global__ void k_bin_key(PState s, int64_t n, const Geo* __restrict__ geo,
-                          uint32_t* __restrict__ key, uint32_t* __restrict__ ticket,
-                          uint32_t* __restrict__ idk, uint32_t* __restrict__ count,
-                          const BuildCtl* ctl, double half_skin2, uint32_t* status) {
-  if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
-  const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  const bool live = i < n;
-  uint32_t c = 0xFFFFFFFFu;
-  if (live) {
-    const Rec& rc = s.r[i];
-    const Geo& g = geo[BATCH ? rc.rep : 0u];
-    const int cx = cell_coord(rc.qx, g.scale[0], g.nc[0]);
-    const int cy = cell_coord(rc.qy, g.scale[1], g.nc[1]);
-    const int cz = cell_coord(rc.qz, g.scale[2], g.nc[2]);
-    c = (uint32_t)(g.cell_base + cell_key(g, cx, cy, cz));
-    key[i] = c;
-    idk[i] = rc.id;
-  }
-  const uint32_t t = run_ticket(c, live, count);
-  if (live) ticket[i] = t;
+// Histogram increment with one atomic per run; the run's lanes take
+// consecutive tickets.
+__device__ __forceinline__ uint32_t run_ticket(uint32_t c, bool live, uint32_t* count) {
+  const int lane = threadIdx.x % kWave;
+  const LaneRun r = lane_run(c, live);
+  uint32_t base = 0;
+  if (r.head) base = atomicAdd(&count[c], (uint32_t)(r.end - lane));
+  base = __shfl(base, r.from, kWave);
+  return base + (uint32_t)(lane - r.from);
 }
 
 // ---- exclusive scan of the cell histogram -> cell offsets --------------------
@@ -344,6 +322,32 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
   *total = smem[nw];
   __syncthreads();
   return excl;
+}
+
+// out[c] = sum_{c' < c} in[c'] for c <= n by one block of up to 1024 threads.
+constexpr int kScanWavesMax = kAuxMaxThreads / kWave;
+__device__ __forceinline__ void scan_in_block(const uint32_t* __restrict__ in, int64_t n,
+                                              uint32_t* __restrict__ out,
+                                              uint32_t* smem /* waves + 1 */) {
+  uint32_t offset = 0;
+  const int64_t chunk = (int64_t)blockDim.x * kScanItems;
+  for (int64_t b0 = 0; b0 < n; b0 += chunk) {
+    const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
+    uint32_t v[kScanItems], s = 0, total;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      v[k] = base + k < n ? in[base + k] : 0u;
+      s += v[k];
+    }
+    uint32_t run = block_exclusive_scan(s, smem, &total) + offset;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      if (base + k < n) out[base + k] = run;
+      run += v[k];
+    }
+    offset += total;
+  }
+  if (threadIdx.x == 0) out[n] = offset;
 }
 
 __global__ void k_scan_tiles(const uint32_t* __restrict__ in, int64_t n,
@@ -405,59 +409,153 @@ __global__ void k_scatter(const uint32_t* __restrict__ key, const uint32_t* __re
   perm[start[key[i]] + ticket[i]] = (uint32_t)i;
 }
 
-// ---- digit 2 and the move into the new order (list-build steps) ------------
-// One thread per bucket slot counts the smaller identifiers of its cell's
-// bucket, which is its place in the cell, and writes its particle's record
-// and internal energy there in the spare buffer, with the build-time position
-// (FP32) and the memory index of the particle's identifier row (for the
+// ---- the list build's binning -------------------------------------------------
+// Cells: the histogram and, per cell, a chain of its particles (link[i] = the
+// identifier and the next particle; `first` heads it), both left cleared by the
+// list build.
+struct CellBins {
+  uint32_t* count;
+  uint32_t* first;
+  uint32_t* start;  // exclusive scan of the histogram, ncells + 1
+  uint2* link;
+  uint32_t* key;    // cell of every particle
+  int64_t ncells;
+};
+constexpr uint32_t kChainEnd = 0xFFFFFFFFu;
+
+// Digit 2 and the move into the new order: particle i counts the smaller
+// identifiers of its cell's chain, which is its place in the cell, and its
+// record and internal energy go there in the spare buffer, with the build-time
+// position (FP32) and the memory index of its identifier row (for the
 // neighbour-list build).  The list build then returns the records to the
 // working buffer, so the buffer roles never depend on whether this step
 // rebuilt.
 template <bool BATCH>
-__global__ void k_rank_gather(PState src, PState dst, const uint32_t* __restrict__ bucket,
-                              const uint32_t* __restrict__ start, const uint32_t* __restrict__ key,
-                              const uint32_t* __restrict__ idk, int64_t n,
+__device__ __forceinline__ void rank_move(const PState& src, const PState& dst, const CellBins& cb,
+                                          int64_t i, const Geo* __restrict__ geo,
+                                          QIdF* __restrict__ qid, uint32_t* __restrict__ slot) {
+  const uint32_t c = cb.key[i];
+  const Rec rc = src.r[i];
+  const double e = src.eps[i];
+  uint32_t p = cb.start[c];
+  for (uint32_t j = cb.first[c]; j != kChainEnd;) {
+    const uint2 l = cb.link[j];
+    p += l.x < rc.id ? 1u : 0u;
+    j = l.y;
+  }
+  dst.r[p] = rc;
+  dst.eps[p] = e;
+  qid[p] = QIdF{(float)rc.qx, (float)rc.qy, (float)rc.qz, rc.id};
+  slot[(BATCH ? (uint32_t)geo[rc.rep].first : 0u) + rc.id] = p;
+}
+
+// Digit 1 (list-build steps only): the cell of every particle, the histogram
+// and the chains, with one atomic of each kind per run of equal keys inside a
+// wave (the particles are still nearly in cell order).  Tiles follow the
+// XCD-aware order, so each XCD's atomics touch its own slab of counters.
+//
+// On most steps the kernels of a build only find that none is due, and each
+// such launch costs a few microseconds, so a build takes as few as its size
+// allows (BinPlan): with `scan` the last block to finish also scans the
+// histogram, and with `whole` (one block) it goes on to rank and move the
+// particles.  The histogram is complete there: every block's atomics are
+// ordered before its ticket.
+template <bool BATCH>
+__global__ __launch_bounds__(kAuxMaxThreads) void k_bin(
+    PState s, PState dst, int64_t n, const Geo* __restrict__ geo, CellBins cb, int scan, int whole,
+    uint32_t* ticket, QIdF* __restrict__ qid, uint32_t* __restrict__ slot, const BuildCtl* ctl,
+    double half_skin2, const uint32_t* status) {
+  if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
+  __shared__ uint32_t smem[kScanWavesMax + 1];
+  __shared__ uint32_t last;
+  const int64_t turn = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
+  for (int64_t b0 = i0; b0 < n; b0 += turn) {  // uniform in the block
+    const int64_t i = b0 + threadIdx.x;
+    const bool live = i < n;
+    uint32_t c = 0xFFFFFFFFu, id = 0u;
+    if (live) {
+      const Rec& rc = s.r[i];
+      const Geo& g = geo[BATCH ? rc.rep : 0u];
+      const int cx = cell_coord(rc.qx, g.scale[0], g.nc[0]);
+      const int cy = cell_coord(rc.qy, g.scale[1], g.nc[1]);
+      const int cz = cell_coord(rc.qz, g.scale[2], g.nc[2]);
+      c = (uint32_t)(g.cell_base + cell_key(g, cx, cy, cz));
+      id = rc.id;
+      cb.key[i] = c;
+    }
+    const int lane = threadIdx.x % kWave;
+    const LaneRun r = lane_run(c, live);
+    uint32_t behind = kChainEnd;
+    if (r.head) {
+      atomicAdd(&cb.count[c], (uint32_t)(r.end - lane));
+      behind = atomicExch(&cb.first[c], (uint32_t)i);
+    }
+    behind = __shfl(behind, r.from, kWave);
+    if (live) cb.link[i] = make_uint2(id, lane + 1 < r.end ? (uint32_t)i + 1u : behind);
+  }
+  if (!scan) return;  // uniform
+  if (gridDim.x > 1u) {
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(ticket, 1u) == gridDim.x - 1u;
+    __syncthreads();
+    if (!last) return;  // uniform in the block
+    __threadfence();
+    if (threadIdx.x == 0) *ticket = 0u;
+  } else {
+    __threadfence_block();
+    __syncthreads();
+  }
+  scan_in_block(cb.count, cb.ncells, cb.start, smem);
+  if (!whole) return;  // uniform
+  __threadfence_block();
+  __syncthreads();
+  for (int64_t i = threadIdx.x; i < n; i += blockDim.x)
+    rank_move<BATCH>(s, dst, cb, i, geo, qid, slot);
+}
+
+// The scan of a histogram too long for one block but short enough for each
+// block to add up all counts before its own tile (no pass over tile sums).
+constexpr int kScanWideThreads = 1024;
+constexpr int kScanWideTile = kScanWideThreads * kScanItems;
+__global__ __launch_bounds__(kScanWideThreads) void k_scan_cells(CellBins cb, const BuildCtl* ctl,
+                                                                 double half_skin2) {
+  if (!rebuild_now(ctl, half_skin2)) return;
+  __shared__ uint32_t smem[kScanWideThreads / kWave + 1];
+  const int64_t tile = (int64_t)blockIdx.x * kScanWideTile;
+  uint32_t before = 0;
+  const uint4* in4 = reinterpret_cast<const uint4*>(cb.count);
+  for (int64_t k = threadIdx.x; k < tile / 4; k += kScanWideThreads) {
+    const uint4 v = in4[k];
+    before += (v.x + v.y) + (v.z + v.w);
+  }
+  uint32_t offset, total;
+  block_exclusive_scan(before, smem, &offset);
+  const int64_t base = tile + (int64_t)threadIdx.x * kScanItems;
+  uint32_t v[kScanItems], s = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = base + k < cb.ncells ? cb.count[base + k] : 0u;
+    s += v[k];
+  }
+  uint32_t run = block_exclusive_scan(s, smem, &total) + offset;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (base + k < cb.ncells) cb.start[base + k] = run;
+    run += v[k];
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cb.start[cb.ncells] = offset + total;
+}
+
+template <bool BATCH>
+__global__ void k_rank_gather(PState src, PState dst, CellBins cb, int64_t n,
                               const Geo* __restrict__ geo, QIdF* __restrict__ qid,
                               uint32_t* __restrict__ slot, const BuildCtl* ctl, double half_skin2,
                               const uint32_t* status) {
   if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = k < n;
-  uint32_t i = 0, b = 0, e = 0, my = 0;
-  if (live) {
-    i = bucket[k];
-    const uint32_t c = key[i];
-    b = start[c];
-    e = start[c + 1];
-    my = idk[i];
-  }
-  // A cell's members hold consecutive slots, so a cell that lies within the
-  // wave's 64 slots finds its members' identifiers on the other lanes; a
-  // cell that crosses the wave's ends reads them from memory.
-  const int lane = (int)(threadIdx.x % kWave);
-  const int64_t w0 = k - lane;  // the wave's first slot
-  const bool inwave = live && (int64_t)b >= w0 && (int64_t)e <= w0 + kWave;
-  const uint32_t span = inwave ? e - b : 0u;
-  uint32_t smax = span;
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1)
-    smax = max(smax, (uint32_t)__shfl_xor((int)smax, off, kWave));
-  smax = (uint32_t)__builtin_amdgcn_readfirstlane((int)smax);
-  uint32_t r = 0;
-  for (uint32_t t = 0; t < smax; ++t) {  // every lane takes part in each read
-    const int from = t < span ? (int)((int64_t)b - w0) + (int)t : lane;
-    const uint32_t o = (uint32_t)__shfl((int)my, from, kWave);
-    r += (t < span && o < my) ? 1u : 0u;
-  }
-  if (!live) return;
-  if (!inwave)
-    for (uint32_t m = b; m < e; ++m) r += idk[bucket[m]] < my ? 1u : 0u;
-  const uint32_t p = b + r;
-  const Rec rc = src.r[i];
-  dst.r[p] = rc;
-  dst.eps[p] = src.eps[i];
-  qid[p] = QIdF{(float)rc.qx, (float)rc.qy, (float)rc.qz, rc.id};
-  slot[(BATCH ? (uint32_t)geo[rc.rep].first : 0u) + rc.id] = p;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) rank_move<BATCH>(src, dst, cb, i, geo, qid, slot);
 }
 
 }  // namespace dpde

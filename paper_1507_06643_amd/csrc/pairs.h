@@ -233,7 +233,8 @@ template <bool BATCH, bool UNIQ>
 __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
     int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
-    const BuildCtl* ctl, double half_skin2, int rows, int tile, uint32_t* status) {
+    const BuildCtl* ctl, double half_skin2, int rows, int tile, CellBins cells,
+    uint32_t* status) {
   extern __shared__ uint32_t dyn[];  // see build_lds
   __shared__ uint32_t cell_s[kUniqTile];
   __shared__ int cx_s[kUniqTile], cy_s[kUniqTile], cz_s[kUniqTile];
@@ -242,14 +243,23 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   __shared__ unsigned long long head_s[2], piece_s[2];
   __shared__ int next_s;       // next piece to take
   __shared__ uint32_t most_s;  // longest list
-  __shared__ uint32_t run_s;
+  __shared__ uint32_t run_s, stop_s;
   if (threadIdx.x == 0) {
-    run_s = !status_set(status) && rebuild_now(ctl, half_skin2);
+    run_s = rebuild_now(ctl, half_skin2);
+    stop_s = status_set(status);
     next_s = 0;
     most_s = 0u;
   }
   __syncthreads();
   if (!run_s) return;  // uniform in the block
+  // the histogram and the chains cleared for the next build (start stays),
+  // also where another block has raised the status
+  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells.ncells;
+       c += (int64_t)gridDim.x * blockDim.x) {
+    cells.count[c] = 0u;
+    cells.first[c] = kChainEnd;
+  }
+  if (stop_s) return;  // uniform in the block
   uint32_t* lst = dyn;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   uint32_t* src = dyn + rows * kUniqTile + w * kBuildWindow;  // the window's candidates

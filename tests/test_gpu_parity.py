@@ -173,6 +173,32 @@ def test_memory_order_is_identifier_order_within_cells(dp, case):
     sysm.close()
 
 
+@pytest.mark.parametrize("n,box", [(2048, None), (2049, None), (1500, (40.0, 24.0, 22.0)),
+                                   (1500, (26.0, 24.0, 26.0)), (6000, (150.0, 120.0, 118.0)),
+                                   (30, (110.0, 108.0, 106.0))])
+def test_memory_order_at_the_edges_of_the_binning(dp, n, box):
+    """The sizes where the binning changes its launches: one block for
+    everything up to 2048 particles and 4096 cells, the scan in the last block
+    up to 4096 cells, a scan of its own up to 2^19 cells (mostly empty ones
+    here), the two-pass scan beyond.  Cells, order and pairs as ever, also
+    after steps with rebuilds."""
+    if box is None:
+        box = [W.cubic_side(n)] * 3
+    q, p, e = W.equilibrium_state(n, box, seed=n)
+    s = dp.System(_cfg(dp, n, box, dt=0.01, skin=0.02), q, p, e)
+    if n == 30:  # cells of side 1.02: over 2^19 of them, and blocked in 2^3
+        s.set_shape(order_block=2)
+    _check_cell_order(s, [0, n])
+    assert np.array_equal(s.debug_pairs(), O.pairs(_oparams(n, box), q, "cells"))
+    s.step(6)
+    assert s.list_builds() > 2
+    qs = s.get_state()[0].cpu().numpy()
+    s.set_state(*s.get_state())
+    _check_cell_order(s, [0, n])
+    assert np.array_equal(s.debug_pairs(), O.pairs(_oparams(n, box), qs, "cells"))
+    s.close()
+
+
 @pytest.mark.parametrize("order_block", [2, 3])
 @pytest.mark.parametrize("n,box,periodic,seed", [CASES[2], CASES[4]])
 def test_pairs_bit_exact_in_blocked_cell_order(dp, n, box, periodic, seed, order_block):

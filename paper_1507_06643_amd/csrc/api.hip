@@ -364,17 +364,17 @@ int allocate(dpde_handle* h) {
   h->scan_tiles = (int)((h->ncells + kScanTile - 1) / kScanTile);
   if (h->scan_tiles > 1024 * 8) return fail(DPDE_EINVAL, "too many cells (%lld)", (long long)h->ncells);
   if ((rc = dalloc(h, &h->scan_tmp, h->scan_tiles + 1))) return rc;
-  h->nl.stride = n;
-  if ((rc = dalloc(h, &h->nl.idx, (size_t)h->phys.cap * n)) || (rc = dalloc(h, &h->nl.count, n)))
+  h->nl.cap = h->phys.cap;
+  const size_t entries = list_size(n, h->phys.cap);
+  if ((rc = dalloc(h, &h->nl.idx, entries)) || (rc = dalloc(h, &h->nl.count, n)))
     return rc;
   if ((rc = dalloc(h, &h->qid, n)) ||
       (rc = dalloc(h, &h->ctl, 1)) || (rc = dalloc(h, &h->ctl_next, kNextSlots)) ||
       (rc = dalloc(h, &h->builds, 1)) ||
-      (rc = dalloc(h, &h->skin.idx, (size_t)h->phys.cap * n)) ||
+      (rc = dalloc(h, &h->skin.idx, entries)) ||
       (rc = dalloc(h, &h->slot, n)) ||
       (rc = dalloc(h, &h->skin.count, n)))
     return rc;
-  h->skin.stride = n;
   h->skin.cap = h->phys.cap;
   if (h->hybrid) {
     h->dscan_tiles = (int)((h->ndoms + kScanTile - 1) / kScanTile);
@@ -406,11 +406,8 @@ int allocate(dpde_handle* h) {
   HIPCHK(hipMemset(h->ctl, 0, sizeof(BuildCtl)));
   HIPCHK(hipMemset(h->ctl_next, 0, kNextSlots * sizeof(NextMax)));
   HIPCHK(hipMemset(h->builds, 0, sizeof(unsigned long long)));
-  h->nl.dex = h->nl.dey = h->nl.dez = nullptr;
-  if (!h->regen && ((rc = dalloc(h, &h->nl.dex, (size_t)h->phys.cap * n)) ||
-                    (rc = dalloc(h, &h->nl.dey, (size_t)h->phys.cap * n)) ||
-                    (rc = dalloc(h, &h->nl.dez, (size_t)h->phys.cap * n))))
-    return rc;
+  h->nl.de = nullptr;
+  if (!h->regen && (rc = dalloc(h, &h->nl.de, 3 * entries))) return rc;
   if ((rc = dalloc(h, &h->status, 4)) || (rc = dalloc(h, &h->d_step, 1)) ||
       (rc = dalloc(h, &h->d_hist_count, 1)) || (rc = dalloc(h, &h->counter, 1)) ||
       (rc = dalloc(h, &h->stats_ticket, 1)))
@@ -601,7 +598,7 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   // per CU (48 and 96 rows: 306 and 829 us per build at N = 1M; 36 and 80: 234
   // and 597).  Small systems take more waves per tile, so that each has a
   // piece or two (N = 65,536, 512 threads: 41 -> 29 us).
-  const int rows = std::min(h->skin.cap, uniq ? 32 : h->skin.cap > 96 ? 80 : 36);
+  const int rows = std::min((int)h->skin.cap, uniq ? 32 : h->skin.cap > 96 ? 80 : 36);
   const unsigned tiles = blocks(n, kUniqTile);
   const int threads = tiles >= 2048 ? 256 : (tiles >= 512 || rows > 48) ? 512 : 1024;
   auto build = [&](auto kern) {

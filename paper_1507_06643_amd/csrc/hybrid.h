@@ -75,7 +75,7 @@ __global__ void k_dom_rank(const uint32_t* __restrict__ bucket, const uint32_t* 
   uint32_t c = 0;
   const uint32_t nn = nl.count[i];
   for (uint32_t m = 0; m < nn; ++m) {
-    const uint32_t j = nl.idx[(int64_t)m * nl.stride + i];
+    const uint32_t j = nl.idx[list_entry(i, m, nl.cap)];
     c += (dom[j] == d && idk[j] > my) ? 1u : 0u;
   }
   pcnt[b + r] = c;
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_ssa_pairs(
     uint32_t j = 0;
     bool take = false;
     if (m < nn) {
-      j = nl.idx[(int64_t)m * nl.stride + i];
+      j = nl.idx[list_entry(i, m, nl.cap)];
       take = dom[j] == d && idk[j] > id;  // the same test as k_dom_rank
     }
     const uint32_t bits = group_ballot(L, take);

@@ -42,13 +42,28 @@ struct alignas(32) Vec4 {
   double x, y, z, w;
 };
 
-// Neighbour list: k-major (entry k of particle i at k*n + i), so the lanes of
-// a wave read and write consecutive words for a given k.
+// Neighbour lists: 32 particles side by side, entry after entry, so that for a
+// given k the lanes of a wave touch consecutive words and a wave's lists lie in
+// one stretch of memory.  (With entry k of all particles side by side the
+// entries of one list were n words apart, each on pages of its own, and the
+// sweeps over long lists, which also stream the increments of every entry, were
+// bound by that and not by their arithmetic or cache accesses: 1,061,208
+// particles of the Lennard-Jones fluid, ~53 entries, sweep 1 805 -> 751 us,
+// sweep 2 513 -> 469, list of the step 477 -> 458; with ~13 entries neutral.)
+constexpr int kRow = 32;
+__host__ __device__ inline int64_t list_entry(int64_t i, int64_t k, int64_t cap) {
+  return ((i / kRow) * cap + k) * kRow + i % kRow;
+}
+// Entries to allocate for n particles.
+inline size_t list_size(int64_t n, int64_t cap) {
+  return (size_t)((n + kRow - 1) / kRow) * kRow * (size_t)cap;
+}
+
 struct NList {
   uint32_t* idx;
   uint32_t* count;
-  double *dex, *dey, *dez;  // dp_ij per entry (stored-increment form), same layout
-  int64_t stride;           // n
+  double* de;   // dp_ij per entry (stored-increment form): x, y, z of 32 entries each
+  int64_t cap;  // capacity per particle
 };
 
 __device__ __forceinline__ bool wrap_cell(int& c, int nc, int periodic) {
@@ -183,11 +198,9 @@ __device__ __forceinline__ uint32_t group_ballot(const Lanes& L, bool pred) {
 // one (then no pair within rc can be missing from the lists).
 // ---------------------------------------------------------------------------
 struct SkinList {
-  uint32_t* idx;    // k-major, capacity cap per particle
+  uint32_t* idx;  // as NList
   uint32_t* count;
-  int64_t stride;   // n
-  int32_t cap;
-  int32_t pad;
+  int64_t cap;    // capacity per particle
 };
 
 // The build's block serves a tile of 128 consecutive particles.  Particles of
@@ -435,7 +448,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
             if (__builtin_amdgcn_inverse_ballot_w64(m)) lst[pos * kUniqTile + tq] = row[c];
           } else if (__builtin_amdgcn_inverse_ballot_w64(m)) {
             if (pos < (uint32_t)rows) lst[pos * kUniqTile + tq] = row[c];
-            else if (pos < cap) sl.idx[(int64_t)pos * sl.stride + tb + tq] = row[c];
+            else if (pos < cap) sl.idx[list_entry(tb + tq, pos, sl.cap)] = row[c];
           }
         }
         counts = lane == q ? base : counts;
@@ -460,7 +473,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   const uint32_t most = most_s < (uint32_t)rows ? most_s : (uint32_t)rows;
   for (uint32_t c = t; c < most * kUniqTile; c += blockDim.x) {
     const uint32_t k = c / kUniqTile, p = c % kUniqTile;
-    if ((int)p < np && k < count_s[p]) sl.idx[(int64_t)k * sl.stride + tb + p] = lst[c];
+    if ((int)p < np && k < count_s[p]) sl.idx[list_entry(tb + p, k, sl.cap)] = lst[c];
   }
   if (t < np) sl.count[tb + t] = count_s[t];
 }
@@ -495,13 +508,13 @@ template <int N>
 __device__ __forceinline__ void sort_list_regs(const SkinList& sl, const uint32_t* __restrict__ slot,
                                                int64_t i, uint32_t nn) {
   uint32_t v[N];
-  const int64_t st = sl.stride;
+  uint32_t* l = sl.idx + list_entry(i, 0, sl.cap);
 #pragma unroll
-  for (int k = 0; k < N; ++k) v[k] = (uint32_t)k < nn ? sl.idx[k * st + i] : 0xFFFFFFFFu;
+  for (int k = 0; k < N; ++k) v[k] = (uint32_t)k < nn ? l[k * kRow] : 0xFFFFFFFFu;
   bitonic_sort<N>(v);
 #pragma unroll
   for (int k = 0; k < N; ++k)
-    if ((uint32_t)k < nn) sl.idx[k * st + i] = slot[v[k]];
+    if ((uint32_t)k < nn) l[k * kRow] = slot[v[k]];
 }
 
 template <int MAXW>
@@ -524,19 +537,19 @@ __global__ __launch_bounds__(256) void k_sort_skin(int64_t n, SkinList sl,
   } else if (MAXW >= 128 && nn <= 128u) {
     sort_list_regs<MAXW>(sl, slot, i, nn);
   } else {
-    const int64_t st = sl.stride;
+    uint32_t* l = sl.idx + list_entry(i, 0, sl.cap);
     for (uint32_t m = 1; m < nn; ++m) {
-      const uint32_t x = sl.idx[m * st + i];
+      const uint32_t x = l[(int64_t)m * kRow];
       uint32_t q = m;
       while (q > 0) {
-        const uint32_t y = sl.idx[(q - 1) * st + i];
+        const uint32_t y = l[(int64_t)(q - 1) * kRow];
         if (y <= x) break;
-        sl.idx[q * st + i] = y;
+        l[(int64_t)q * kRow] = y;
         --q;
       }
-      sl.idx[q * st + i] = x;
+      l[(int64_t)q * kRow] = x;
     }
-    for (uint32_t m = 0; m < nn; ++m) sl.idx[m * st + i] = slot[sl.idx[m * st + i]];
+    for (uint32_t m = 0; m < nn; ++m) l[(int64_t)m * kRow] = slot[l[(int64_t)m * kRow]];
   }
 }
 
@@ -565,7 +578,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_a(
   uint32_t nn = 0;
   double fx = 0.0, fy = 0.0, fz = 0.0, u = 0.0, lap = 0.0;
   const float inv_rc_f = (float)P.inv_rc, a_f = (float)P.a;
-  uint32_t jn = (uint32_t)L.sub < ns ? sl.idx[(int64_t)L.sub * sl.stride + i] : 0u;
+  uint32_t jn = (uint32_t)L.sub < ns ? sl.idx[list_entry(i, L.sub, sl.cap)] : 0u;
   double qnx = 0.0, qny = 0.0, qnz = 0.0;
   if ((uint32_t)L.sub < ns) {
     qnx = R[jn].qx;
@@ -577,7 +590,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_a(
     const uint32_t j = jn;
     const double qjx = qnx, qjy = qny, qjz = qnz;
     if (k + kSub < ns) {
-      jn = sl.idx[(int64_t)(k + kSub) * sl.stride + i];
+      jn = sl.idx[list_entry(i, k + kSub, sl.cap)];
       qnx = R[jn].qx;
       qny = R[jn].qy;
       qnz = R[jn].qz;
@@ -594,7 +607,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_a(
     if (take) {
       const uint32_t pos = nn + __popc(bits & ((1u << L.sub) - 1u));
       if (pos < (uint32_t)kListLds) lst[pos * L.ppb + L.pib] = j;
-      else if (pos < cap) nl.idx[(int64_t)pos * nl.stride + i] = j;
+      else if (pos < cap) nl.idx[list_entry(i, pos, nl.cap)] = j;
     }
     // the pair at list position p is summed by lane p mod kSub (as in passes
     // B and C), whichever lane tested it: lane sub owns rank r of this trip
@@ -663,7 +676,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_pass_a(
   }
   const uint32_t staged = nn < (uint32_t)kListLds ? nn : (uint32_t)kListLds;
   for (uint32_t k = L.sub; k < staged; k += kSub)
-    nl.idx[(int64_t)k * nl.stride + i] = lst[k * L.ppb + L.pib];
+    nl.idx[list_entry(i, k, nl.cap)] = lst[k * L.ppb + L.pib];
   if (L.sub == 0) {
     nl.count[i] = nn;
     Fx[i] = fx;
@@ -802,16 +815,21 @@ __device__ __forceinline__ void pair_from_records(const Phys& P, const Geo& g, b
 // increments are FP32 values to begin with (exact either way).  They are
 // written once and read once, so both go non-temporal: the stream does not
 // evict the neighbour data the gathers of both sweeps reuse from L2.
+// The x components of a row of 32 entries, then the y and the z components.
+__device__ __forceinline__ int64_t dp_at(int64_t e) { return e + 2 * kRow * (e / kRow); }
+
 template <int PREC>
 __device__ __forceinline__ void store_dp(const NList& nl, int64_t e, double x, double y, double z) {
   if constexpr (PREC == PREC_F32) {
-    __builtin_nontemporal_store((float)x, reinterpret_cast<float*>(nl.dex) + e);
-    __builtin_nontemporal_store((float)y, reinterpret_cast<float*>(nl.dey) + e);
-    __builtin_nontemporal_store((float)z, reinterpret_cast<float*>(nl.dez) + e);
+    float* d = reinterpret_cast<float*>(nl.de) + dp_at(e);
+    __builtin_nontemporal_store((float)x, d);
+    __builtin_nontemporal_store((float)y, d + kRow);
+    __builtin_nontemporal_store((float)z, d + 2 * kRow);
   } else {
-    __builtin_nontemporal_store(x, nl.dex + e);
-    __builtin_nontemporal_store(y, nl.dey + e);
-    __builtin_nontemporal_store(z, nl.dez + e);
+    double* d = nl.de + dp_at(e);
+    __builtin_nontemporal_store(x, d);
+    __builtin_nontemporal_store(y, d + kRow);
+    __builtin_nontemporal_store(z, d + 2 * kRow);
   }
 }
 
@@ -819,13 +837,15 @@ template <int PREC>
 __device__ __forceinline__ void load_dp(const NList& nl, int64_t e, double& x, double& y,
                                         double& z) {
   if constexpr (PREC == PREC_F32) {
-    x = (double)__builtin_nontemporal_load(reinterpret_cast<const float*>(nl.dex) + e);
-    y = (double)__builtin_nontemporal_load(reinterpret_cast<const float*>(nl.dey) + e);
-    z = (double)__builtin_nontemporal_load(reinterpret_cast<const float*>(nl.dez) + e);
+    const float* d = reinterpret_cast<const float*>(nl.de) + dp_at(e);
+    x = (double)__builtin_nontemporal_load(d);
+    y = (double)__builtin_nontemporal_load(d + kRow);
+    z = (double)__builtin_nontemporal_load(d + 2 * kRow);
   } else {
-    x = __builtin_nontemporal_load(nl.dex + e);
-    y = __builtin_nontemporal_load(nl.dey + e);
-    z = __builtin_nontemporal_load(nl.dez + e);
+    const double* d = nl.de + dp_at(e);
+    x = __builtin_nontemporal_load(d);
+    y = __builtin_nontemporal_load(d + kRow);
+    z = __builtin_nontemporal_load(d + 2 * kRow);
   }
 }
 
@@ -1064,7 +1084,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
   const GeoRef<BATCH> g = geo[BATCH ? a.rep : 0u];
   const bool mi = !__all(away_from_faces(g, P, a.qx, a.qy, a.qz));  // uniform in the wave
   const uint32_t nn = live ? nl.count[i] : 0u;
-  const int64_t st = nl.stride;
+  const int64_t cap = nl.cap;
   // Hybrid: pairs inside one domain were integrated by SSA; their entries
   // carry a zero increment here
   const uint32_t dom_i = dom ? dom[i] : 0u;
@@ -1072,7 +1092,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
   // no software pipeline: the registers a prefetched record would hold buy
   // one more wave per SIMD, which hides the gather latency better
   for (uint32_t k = L.sub; k < nn; k += kSubSer) {
-    const int64_t e = (int64_t)k * st + i;
+    const int64_t e = list_entry(i, k, cap);
     const uint32_t j = nl.idx[e];
     const Rec b = R[j];
     if (dom && dom[j] == dom_i) {
@@ -1298,10 +1318,10 @@ __global__ __launch_bounds__(KS * T) __attribute__((
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
       const int c = r * (KS * T) + threadIdx.x;
-      const int k = min(c / T, sl.cap - 1);  // inside the list
+      const int k = min(c / T, (int)sl.cap - 1);  // inside the list
       const int t = c % T;
       const int64_t row = tb + t < n ? tb + t : n - 1;
-      v[r] = sl.idx[(int64_t)k * sl.stride + row];
+      v[r] = sl.idx[list_entry(row, k, sl.cap)];
     }
 #pragma unroll
     for (int r = 0; r < kPer; ++r) skin[r * (KS * T) + threadIdx.x] = v[r];
@@ -1345,7 +1365,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
       if (take) {
         const uint32_t pos = nn + __popc(bits & ((1u << sub) - 1u));
         if (pos < (uint32_t)kTileListLds) lst[pos * T + pl] = j;
-        else if (pos < cap) nl.idx[(int64_t)pos * nl.stride + i] = j;
+        else if (pos < cap) nl.idx[list_entry(i, pos, nl.cap)] = j;
         double gx, gy, gz, v, lap;
         pair_conservative<PREC>(P, dx, dy, dz, r2, gx, gy, gz, v, lap);
         const long long f0 = fix_f(gx), f1 = fix_f(gy), f2 = fix_f(gz);
@@ -1405,7 +1425,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
       uint32_t j = 0u;
       double qjx = 0.0, qjy = 0.0, qjz = 0.0;
       if (k < ns) {
-        j = sl.idx[(int64_t)k * sl.stride + i];
+        j = sl.idx[list_entry(i, k, sl.cap)];
         qjx = R[j].qx;
         qjy = R[j].qy;
         qjz = R[j].qz;
@@ -1458,7 +1478,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
   }
   const uint32_t staged = nn < (uint32_t)kTileListLds ? nn : (uint32_t)kTileListLds;
   for (uint32_t k = sub; k < staged; k += KS)
-    nl.idx[(int64_t)k * nl.stride + i] = lst[k * T + pl];
+    nl.idx[list_entry(i, k, nl.cap)] = lst[k * T + pl];
   if (sub == 0) {
     const double fx = (double)(long long)((unsigned long long)XF0 + acc[0][pl]) * P.fix_inv_f;
     const double fy = (double)(long long)((unsigned long long)XF1 + acc[1][pl]) * P.fix_inv_f;
@@ -1526,7 +1546,7 @@ void k_pass_b_uniq(
   const bool live = i < n;
   const uint64_t step = *d_step;
   const Rec* __restrict__ R = s.r;
-  const int64_t st = nl.stride;
+  const int64_t cap = nl.cap;
   long long X0 = 0, X1 = 0, X2 = 0;  // raw sums of fixed-point bit patterns
   long long terms = 0;
   uint32_t hi_max = 0u;
@@ -1545,7 +1565,7 @@ void k_pass_b_uniq(
   // fixed-point words
   auto term = [&](const Rec& ra, int64_t ii, uint32_t k, uint32_t j, long long& f0,
                   long long& f1, long long& f2) {
-    const int64_t e = (int64_t)k * st + ii;
+    const int64_t e = list_entry(ii, k, cap);
     const Rec b = R[j];
     const GeoRef<BATCH> g = geo[BATCH ? ra.rep : 0u];
     double vx, vy, vz;
@@ -1573,7 +1593,7 @@ void k_pass_b_uniq(
   for (int q = 0; q < kTileRegular / LPP; ++q) {
     const uint32_t k = (uint32_t)(sub + LPP * q);
     const uint32_t kc = k < nreg ? k : (nreg ? nreg - 1u : 0u);
-    jr[q] = nreg ? nl.idx[(int64_t)kc * st + i] : 0u;
+    jr[q] = nreg ? nl.idx[list_entry(i, kc, cap)] : 0u;
   }
   for (int q = 0; q < kTileRegular / LPP; ++q) {
     const uint32_t k = (uint32_t)(sub + LPP * q);
@@ -1601,7 +1621,7 @@ void k_pass_b_uniq(
       const uint32_t k = (uint32_t)kTileRegular + (x - first[p]);
       const Rec ra = R[ii];
       long long f0, f1, f2;
-      term(ra, ii, k, nl.idx[(int64_t)k * st + ii], f0, f1, f2);
+      term(ra, ii, k, nl.idx[list_entry(ii, k, cap)], f0, f1, f2);
       atomicAdd(&acc[0][slot], (unsigned long long)(f0 - kFixMagicBits));
       atomicAdd(&acc[1][slot], (unsigned long long)(f1 - kFixMagicBits));
       atomicAdd(&acc[2][slot], (unsigned long long)(f2 - kFixMagicBits));
@@ -1666,8 +1686,8 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
     di = dpi[i];
     const H3 hi = hv[i];
     const uint32_t nn = nl.count[i];
-    const int64_t st = nl.stride;
-    uint32_t jn = (uint32_t)L.sub < nn ? nl.idx[(int64_t)L.sub * st + i] : 0u;
+    const int64_t cap = nl.cap;
+    uint32_t jn = (uint32_t)L.sub < nn ? nl.idx[list_entry(i, L.sub, cap)] : 0u;
     double hx = 0.0, hy = 0.0, hz = 0.0;
     if ((uint32_t)L.sub < nn) {
       hx = hv[jn].x;
@@ -1675,11 +1695,11 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
       hz = hv[jn].z;
     }
     for (uint32_t k = L.sub; k < nn; k += kSubSer) {
-      const int64_t e = (int64_t)k * st + i;
+      const int64_t e = list_entry(i, k, cap);
       const uint32_t j = jn;
       const double ux = hi.x - hx, uy = hi.y - hy, uz = hi.z - hz;
       if (k + kSubSer < nn) {
-        jn = nl.idx[e + kSubSer * st];
+        jn = nl.idx[e + kSubSer * kRow];
         hx = hv[jn].x;
         hy = hv[jn].y;
         hz = hv[jn].z;
@@ -1807,7 +1827,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
   const bool live = i < n;
   const uint64_t step = *d_step;
   const Rec* __restrict__ R = s.r;
-  const int64_t st = nl.stride;
+  const int64_t cap = nl.cap;
   long long X = 0;  // raw sum of fixed-point bit patterns
   long long terms = 0;
   uint32_t hi_max = 0u;
@@ -1846,7 +1866,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
   auto term = [&](const Rec& ra, const H3& hi, int64_t ii, uint32_t k, uint32_t j, double hx,
                   double hy, double hz, bool have = false, double dx = 0.0, double dy = 0.0,
                   double dz = 0.0) -> long long {
-    const int64_t e = (int64_t)k * st + ii;
+    const int64_t e = list_entry(ii, k, cap);
     const double ux = hi.x - hx, uy = hi.y - hy, uz = hi.z - hz;
     double ex = dx, ey = dy, ez = dz;
     if constexpr (REGEN) {
@@ -1878,13 +1898,13 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
     for (int q = 0; q < kTileRegular / LPP; ++q) {
       const uint32_t k = (uint32_t)(sub + LPP * q);
       const uint32_t kc = k < nreg ? k : (nreg ? nreg - 1u : 0u);
-      jr[q] = nreg ? nl.idx[(int64_t)kc * st + i] : 0u;
+      jr[q] = nreg ? nl.idx[list_entry(i, kc, cap)] : 0u;
     }
     double hx = 0.0, hy = 0.0, hz = 0.0;
     double sx = 0.0, sy = 0.0, sz = 0.0;  // the stored increment, likewise one entry ahead
     if ((uint32_t)sub < nreg) {
       gather_h(jr[0], hx, hy, hz);
-      if constexpr (!REGEN) load_dp<PREC>(nl, (int64_t)sub * st + i, sx, sy, sz);
+      if constexpr (!REGEN) load_dp<PREC>(nl, list_entry(i, sub, cap), sx, sy, sz);
     }
 #pragma unroll
     for (int q = 0; q < kTileRegular / LPP; ++q) {
@@ -1894,7 +1914,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
       const double ex = sx, ey = sy, ez = sz;
       if (q + 1 < kTileRegular / LPP && k + LPP < nreg) {
         gather_h(jr[q + 1], hx, hy, hz);
-        if constexpr (!REGEN) load_dp<PREC>(nl, (int64_t)(k + LPP) * st + i, sx, sy, sz);
+        if constexpr (!REGEN) load_dp<PREC>(nl, list_entry(i, k + LPP, cap), sx, sy, sz);
       }
       X += term(a, hi, i, k, jr[q], cx, cy, cz, !REGEN, ex, ey, ez);
       ++terms;
@@ -1914,7 +1934,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
       const int slot = PW * w + p;
       const int64_t ii = tb + slot;
       const uint32_t k = (uint32_t)kTileRegular + (x - first[p]);
-      const uint32_t j = nl.idx[(int64_t)k * st + ii];
+      const uint32_t j = nl.idx[list_entry(ii, k, cap)];
       const H3 hj = hv[j];
       const Rec ra = REGEN ? R[ii] : Rec{};
       const long long f = term(ra, hv[ii], ii, k, j, hj.x, hj.y, hj.z);
@@ -2267,7 +2287,7 @@ __global__ void k_debug_pairs(PState s, NList nl, int64_t n, const Geo* __restri
   const Rec& a = s.r[i];
   const Geo& g = geo[a.rep];
   for (uint32_t k = 0; k < nl.count[i]; ++k) {
-    const uint32_t j = nl.idx[(int64_t)k * nl.stride + i];
+    const uint32_t j = nl.idx[list_entry(i, k, nl.cap)];
     const uint32_t idj = s.r[j].id;
     const bool once = ((uint32_t)i ^ j) < (uint32_t)tile;
     if (once || a.id < idj) {

@@ -82,8 +82,19 @@ struct Phys {
 // what lets the second SER sweep regenerate the first sweep's increments
 // (Sec. 3.2.1).
 // -------------------------------------------------------------------------
+// a ^ b ^ c in one instruction.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+template <bool UNIFORM_KEY>
 __device__ __forceinline__ void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32_t& x2,
                                               uint32_t& x3, uint32_t k0, uint32_t k1) {
+  // With one key for the wave the round keys take scalar additions.  Seen as
+  // loop invariant they were all kept across the pair loops, beyond the scalar
+  // registers there are, in vector lanes that cost an instruction to read
+  // back: the compiler is kept from knowing that the key does not change.
+  if constexpr (UNIFORM_KEY) asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) {
@@ -92,8 +103,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32
     }
     const uint64_t m0 = (uint64_t)0xD2511F53u * (uint64_t)x0;
     const uint64_t m1 = (uint64_t)0xCD9E8D57u * (uint64_t)x2;
-    const uint32_t y0 = (uint32_t)(m1 >> 32) ^ x1 ^ k0;
-    const uint32_t y2 = (uint32_t)(m0 >> 32) ^ x3 ^ k1;
+    const uint32_t y0 = xor3((uint32_t)(m1 >> 32), x1, k0);
+    const uint32_t y2 = xor3((uint32_t)(m0 >> 32), x3, k1);
     x1 = (uint32_t)m1;
     x3 = (uint32_t)m0;
     x0 = y0;
@@ -101,13 +112,15 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32
   }
 }
 
+// (UNIFORM_KEY: g is one replica's for the whole wave)
+template <bool UNIFORM_KEY>
 __device__ __forceinline__ void pair_words(const Geo& g, uint32_t lo, uint32_t hi, uint64_t step,
                                            uint32_t w[4]) {
   w[0] = lo;
   w[1] = hi;
   w[2] = (uint32_t)step;
   w[3] = (uint32_t)(step >> 32);
-  philox4x32_10(w[0], w[1], w[2], w[3], g.key0, g.key1);
+  philox4x32_10<UNIFORM_KEY>(w[0], w[1], w[2], w[3], g.key0, g.key1);
 }
 
 // ---------------------------------------------------------------------------
@@ -116,10 +129,22 @@ __device__ __forceinline__ void pair_words(const Geo& g, uint32_t lo, uint32_t h
 // last place, against ~100 instructions for the general library logarithm).
 // ---------------------------------------------------------------------------
 
+// A constant in scalar registers, set where it is used: a scalar instruction
+// or two beside the vector ones.  Left to itself the compiler keeps the series'
+// constants across the pair loops in vector registers (sweep 1 of the both-sides
+// form: 114 instead of 69, four waves per SIMD instead of seven) and copies
+// them before use.  With this, the uniform round keys and the shorter series a
+// pair term takes 265 vector instructions instead of 330.
+__device__ __forceinline__ double scalar_f64(double k) {
+  asm volatile("" : "+s"(k));
+  return k;
+}
+
 // ln u for u = (x + 1/2) 2^-32 = (2x + 1) 2^-33.  With 2x + 1 = m 2^e and
 // m in [1/sqrt 2, sqrt 2): ln u = (e - 33) ln 2 + ln m, and
 // ln m = 2 atanh(s) = 2 (s + s^3/3 + s^5/5 + ...), s = (m - 1)/(m + 1),
-// |s| <= 0.172 (eleven terms leave a relative remainder below 1e-18).
+// |s| <= 0.172; the series beyond 2s as its interpolant in s^2 at seven
+// Chebyshev nodes (relative error 5e-18; the series itself takes ten terms).
 __device__ __forceinline__ double ln_uniform_f64(uint32_t x) {
   const double y = 2.0 * (double)x + 1.0;  // exact
   double m = __builtin_amdgcn_frexp_mant(y);  // [1/2, 1)
@@ -136,20 +161,17 @@ __device__ __forceinline__ double ln_uniform_f64(uint32_t x) {
   double s = f * r;
   s = fma(r, fma(-s, d, f), s);
   const double z = s * s;
-  double p = 0.09523809523809523;  // 2/21
-  p = fma(p, z, 0.10526315789473684);
-  p = fma(p, z, 0.11764705882352941);
-  p = fma(p, z, 0.13333333333333333);
-  p = fma(p, z, 0.15384615384615385);
-  p = fma(p, z, 0.18181818181818182);
-  p = fma(p, z, 0.2222222222222222);
-  p = fma(p, z, 0.2857142857142857);
-  p = fma(p, z, 0.4);
-  p = fma(p, z, 0.6666666666666666);
+  double p = 0.14616449685043387;
+  p = fma(p, z, scalar_f64(0.15331721600556042));
+  p = fma(p, z, scalar_f64(0.18182889125261723));
+  p = fma(p, z, scalar_f64(0.2222221113479508));
+  p = fma(p, z, scalar_f64(0.28571428625975487));
+  p = fma(p, z, scalar_f64(0.39999999999899505));
+  p = fma(p, z, scalar_f64(0.666666666666667));
   const double lnm = fma(s * z, p, 2.0 * s);  // 2s + s z (2/3 + ...)
   const double E = (double)(e - 33);
   // ln 2 split so that E * ln2_hi is exact
-  return fma(E, 0.6931471805601177, fma(E, -1.7239444525614835e-13, lnm));
+  return fma(E, scalar_f64(0.6931471805601177), fma(E, scalar_f64(-1.7239444525614835e-13), lnm));
 }
 
 // sqrt(v) for v in [2^-33, 64]: reciprocal square-root seed and two Newton
@@ -174,48 +196,50 @@ __device__ __forceinline__ double inv_sqrt_f64(double v) {
   return r;
 }
 
-// sin(pi t) and cos(pi t) for t in [0, 2]: t = k/2 + y with k = rint(2t) and
-// |y| <= 1/4 exactly; the Taylor series of sin(pi y) and cos(pi y) to the
-// 17th and 16th power, then the quarter-turn k mod 4 rotates the pair.
-__device__ __forceinline__ void sincospi_f64(double t, double& sn, double& cs) {
-  const double k = rint(2.0 * t);
-  const double y = fma(-0.5, k, t);  // exact
-  const double w = y * y;
-  double ps = 7.952054001475513e-07;
-  ps = fma(ps, w, -2.1915353447830217e-05);
-  ps = fma(ps, w, 0.00046630280576761255);
-  ps = fma(ps, w, -0.0073704309457143504);
-  ps = fma(ps, w, 0.08214588661112823);
-  ps = fma(ps, w, -0.5992645293207921);
-  ps = fma(ps, w, 2.5501640398773455);
-  ps = fma(ps, w, -5.16771278004997);
-  const double sp = fma(y * w, ps, 3.141592653589793 * y);
-  double pc = 4.303069587032947e-06;
-  pc = fma(pc, w, -0.0001046381049248457);
-  pc = fma(pc, w, 0.0019295743094039231);
-  pc = fma(pc, w, -0.02580689139001406);
-  pc = fma(pc, w, 0.2353306303588932);
-  pc = fma(pc, w, -1.3352627688545895);
-  pc = fma(pc, w, 4.0587121264167685);
-  pc = fma(pc, w, -4.934802200544679);
-  const double cp = fma(w, pc, 1.0);
-  const int q = (int)k & 3;
-  const double a = (q & 1) ? cp : sp;  // sin of the rotated angle, up to sign
-  const double b = (q & 1) ? sp : cp;  // cos of the rotated angle, up to sign
-  sn = (q & 2) ? -a : a;
-  cs = ((q + 1) & 2) ? -b : b;
+// v with its sign flipped where bit 31 of `flip` is set.
+__device__ __forceinline__ double flip_sign(double v, uint32_t flip) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  return __longlong_as_double(
+      (long long)(b ^ ((unsigned long long)(flip & 0x80000000u) << 32)));
+}
+
+// sin(2 pi u) and cos(2 pi u) for u = (w + 1/2) 2^-32.  The quarter turn k
+// nearest to u and the distance from it come from w as an integer: 2u =
+// k/2 + y with y the low 30 bits of w, signed, plus 1/2 in units of 2^-31
+// (exact, |y| <= 1/4).  sin(pi y) = pi y + y^3 ps(y^2) and cos(pi y) = 1 + y^2
+// pc(y^2), ps and pc interpolating the series at six and seven Chebyshev nodes
+// (errors 1.3e-17 and 1.2e-19); k mod 4 then rotates the pair.
+__device__ __forceinline__ void sincos_uniform_f64(uint32_t w, double& sn, double& cs) {
+  const double y = fma((double)((int32_t)(w << 2) >> 2), 0x1p-31, 0x1p-32);
+  const double z = y * y;
+  double ps = 0.00046221110224187623;
+  ps = fma(ps, z, scalar_f64(-0.0073701436435937495));
+  ps = fma(ps, z, scalar_f64(0.08214587730641625));
+  ps = fma(ps, z, scalar_f64(-0.5992645291845385));
+  ps = fma(ps, z, scalar_f64(2.5501640398766154));
+  ps = fma(ps, z, scalar_f64(-5.167712780049969));
+  const double sp = fma(y * z, ps, scalar_f64(3.141592653589793) * y);
+  double pc = -0.00010370082971594627;
+  pc = fma(pc, z, scalar_f64(0.001929493874894941));
+  pc = fma(pc, z, scalar_f64(-0.025806887964701878));
+  pc = fma(pc, z, scalar_f64(0.23533063028399223));
+  pc = fma(pc, z, scalar_f64(-1.3352627688538095));
+  pc = fma(pc, z, scalar_f64(4.058712126416765));
+  pc = fma(pc, z, scalar_f64(-4.934802200544679));
+  const double cp = fma(z, pc, 1.0);
+  const uint32_t r = w + 0x20000000u;  // k in the top two bits
+  const bool odd = (r & 0x40000000u) != 0u;
+  sn = flip_sign(odd ? cp : sp, r);
+  cs = flip_sign(odd ? sp : cp, r + 0x40000000u);
 }
 
 // FP64 normals from the four words: u = (x + 1/2) 2^-32 in (0,1).
 __device__ __forceinline__ void box_muller_f64(const uint32_t w[4], double G[3]) {
-  const double s = 2.3283064365386963e-10;  // 2^-32
   const double r1 = sqrt_pos_f64(-2.0 * ln_uniform_f64(w[0]));
   const double r2 = sqrt_pos_f64(-2.0 * ln_uniform_f64(w[2]));
-  const double t1 = (2.0 * (double)w[1] + 1.0) * s;  // 2 u1, exact
-  const double t3 = (2.0 * (double)w[3] + 1.0) * s;
   double sn, cs, sn3, cs3;
-  sincospi_f64(t1, sn, cs);
-  sincospi_f64(t3, sn3, cs3);
+  sincos_uniform_f64(w[1], sn, cs);
+  sincos_uniform_f64(w[3], sn3, cs3);
   G[0] = r1 * cs;
   G[1] = r1 * sn;
   G[2] = r2 * cs3;
@@ -223,10 +247,9 @@ __device__ __forceinline__ void box_muller_f64(const uint32_t w[4], double G[3])
 
 // The first normal only (the scalar noise of the projected model).
 __device__ __forceinline__ double normal1_f64(const uint32_t w[4]) {
-  const double r1 = sqrt_pos_f64(-2.0 * ln_uniform_f64(w[0]));
   double sn, cs;
-  sincospi_f64((2.0 * (double)w[1] + 1.0) * 2.3283064365386963e-10, sn, cs);
-  return r1 * cs;
+  sincos_uniform_f64(w[1], sn, cs);
+  return sqrt_pos_f64(-2.0 * ln_uniform_f64(w[0])) * cs;
 }
 
 // ln u for u = (x + 1/2) 2^-32 in FP32.  Far from 1 the float of x keeps 24

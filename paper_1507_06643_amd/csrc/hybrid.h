@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kPairBlockMax) void k_ssa_pairs(
         const double r = r2 * inv_sqrt_f64(r2);
         const double w = 1.0 - r * P.inv_rc;
         uint32_t wd[4];
-        pair_words(g, id, idk[j], step, wd);  // i is the lower identifier
+        pair_words<!BATCH>(g, id, idk[j], step, wd);  // i is the lower identifier
         double G[3];
         box_muller_f64(wd, G);
         sp.idx[tt] = make_uint2(li, lslot[j]);

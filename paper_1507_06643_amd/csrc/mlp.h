@@ -220,7 +220,7 @@ __global__ void k_mlp_samples(uint64_t seed, int64_t n, double lnlo, double lnhi
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   uint32_t w0 = (uint32_t)k, w1 = (uint32_t)(k >> 32), w2 = 0x534D504Cu, w3 = 0u;
-  philox4x32_10(w0, w1, w2, w3, (uint32_t)seed, (uint32_t)(seed >> 32));
+  philox4x32_10<true>(w0, w1, w2, w3, (uint32_t)seed, (uint32_t)(seed >> 32));
   const double u = ((double)w0 + 0.5) * 2.3283064365386963e-10;
   const double lt = lnlo + u * (lnhi - lnlo);
   const double th = exp(lt);

@@ -714,14 +714,14 @@ struct PairOut {
 // e_ij = d_ij / r with one scalar normal xi_ij = xi_ji per pair,
 //   dp_ij = (-gamma_ij chi (e_ij . v_ij) dt + sigma w xi_ij sqrt(dt)) e_ij,
 // antisymmetric through e_ji = -e_ij; a coincident pair does not interact.
-template <int PREC, int MODEL>
+template <bool BATCH, int PREC, int MODEL>
 __device__ __forceinline__ void ser_pair(const Phys& P, const Geo& g, double dx, double dy,
                                          double dz, double r2, double vx, double vy, double vz,
                                          double invT_sum, uint32_t idi, uint32_t idj,
                                          uint64_t step, PairOut& o) {
   const bool i_lo = idi < idj;
   uint32_t wd[4];
-  pair_words(g, i_lo ? idi : idj, i_lo ? idj : idi, step, wd);
+  pair_words<!BATCH>(g, i_lo ? idi : idj, i_lo ? idj : idi, step, wd);
   if constexpr (PREC == PREC_F64) {
     const double ir = inv_sqrt_f64(r2);
     const double r = r2 * ir;
@@ -797,7 +797,7 @@ __device__ __forceinline__ void ser_pair(const Phys& P, const Geo& g, double dx,
 }
 
 // dp_ij of neighbour j seen from the record of particle i.
-template <int PREC, int MODEL>
+template <bool BATCH, int PREC, int MODEL>
 __device__ __forceinline__ void pair_from_records(const Phys& P, const Geo& g, bool mi,
                                                   const Rec& a, const Rec& b, uint64_t step,
                                                   double& vx, double& vy, double& vz,
@@ -808,7 +808,7 @@ __device__ __forceinline__ void pair_from_records(const Phys& P, const Geo& g, b
   vx = a.px * P.inv_mass - b.px * P.inv_mass;
   vy = a.py * P.inv_mass - b.py * P.inv_mass;
   vz = a.pz * P.inv_mass - b.pz * P.inv_mass;
-  ser_pair<PREC, MODEL>(P, g, dx, dy, dz, r2, vx, vy, vz, a.invT + b.invT, a.id, b.id, step, o);
+  ser_pair<BATCH, PREC, MODEL>(P, g, dx, dy, dz, r2, vx, vy, vz, a.invT + b.invT, a.id, b.id, step, o);
 }
 
 // Stored increments dp_ij: FP64, or FP32 for the FP32 pair terms, whose
@@ -1101,7 +1101,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
     }
     double vx, vy, vz;
     PairOut o;
-    pair_from_records<PREC, MODEL>(P, g, mi, a, b, step, vx, vy, vz, o);
+    pair_from_records<BATCH, PREC, MODEL>(P, g, mi, a, b, step, vx, vy, vz, o);
     ax += o.dp[0];
     ay += o.dp[1];
     az += o.dp[2];
@@ -1343,7 +1343,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
   }
   const uint32_t cap = (uint32_t)P.cap;
   long long XF0 = 0, XF1 = 0, XF2 = 0, XU = 0, XLh = 0, XLl = 0;  // raw fixed-point words
-  long long terms = 0;
+  uint32_t terms = 0u;
   uint32_t hi_l = 0u;
   uint32_t nn = 0;
   // The walk of the lanes in `mine` over their lists, with the geometry g of
@@ -1453,7 +1453,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
   } else {
     walk(geo[0], live);
   }
-  const long long m = terms * kFixMagicBits;
+  const long long m = (long long)terms * kFixMagicBits;
   XF0 -= m;
   XF1 -= m;
   XF2 -= m;
@@ -1519,14 +1519,14 @@ __device__ __forceinline__ int overflow_owner(const uint32_t* first, uint32_t x)
   return lo;
 }
 
-// Occupancy: the batched FP64 vector-model instance, which holds its
-// replica's geometry per lane, fits 6 waves per SIMD only when asked (79
-// VGPRs, no spills); asked the same, the FP32 and projected-model instances
-// would spill, and keep the compiler's choice.
+// Occupancy: the FP64 vector-model instance fits 6 waves per SIMD only when
+// asked (77 VGPRs), the batched one, which holds its replica's geometry per
+// lane, 5 (81; at 6 it spills), without spills; the FP32 and projected-model
+// instances keep the compiler's choice.
 template <bool BATCH, int PREC, int MODEL, int T, int LPP>
 __global__ __launch_bounds__(LPP * T)
 __attribute__((amdgpu_waves_per_eu(
-    BATCH && PREC == PREC_F64 && MODEL == 0 && LPP == 2 ? 6 : 1, 8)))
+    PREC == PREC_F64 && MODEL == 0 && LPP == 2 ? (BATCH ? 5 : 6) : 1, 8)))
 void k_pass_b_uniq(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, Vec4* __restrict__ dpi, H3* __restrict__ hv, int store,
@@ -1548,7 +1548,7 @@ void k_pass_b_uniq(
   const Rec* __restrict__ R = s.r;
   const int64_t cap = nl.cap;
   long long X0 = 0, X1 = 0, X2 = 0;  // raw sums of fixed-point bit patterns
-  long long terms = 0;
+  uint32_t terms = 0u;
   uint32_t hi_max = 0u;
   Rec a{};
   uint32_t nn = 0;
@@ -1570,7 +1570,7 @@ void k_pass_b_uniq(
     const GeoRef<BATCH> g = geo[BATCH ? ra.rep : 0u];
     double vx, vy, vz;
     PairOut o;
-    pair_from_records<PREC, MODEL>(P, g, mi, ra, b, step, vx, vy, vz, o);
+    pair_from_records<BATCH, PREC, MODEL>(P, g, mi, ra, b, step, vx, vy, vz, o);
     if (store) store_dp<PREC>(nl, e, o.dp[0], o.dp[1], o.dp[2]);
     f0 = pair_fix_raw(o.dp[0]);
     f1 = pair_fix_raw(o.dp[1]);
@@ -1627,9 +1627,9 @@ void k_pass_b_uniq(
       atomicAdd(&acc[2][slot], (unsigned long long)(f2 - kFixMagicBits));
     }
   }
-  X0 -= terms * kFixMagicBits;
-  X1 -= terms * kFixMagicBits;
-  X2 -= terms * kFixMagicBits;
+  X0 -= (long long)terms * kFixMagicBits;
+  X1 -= (long long)terms * kFixMagicBits;
+  X2 -= (long long)terms * kFixMagicBits;
 #pragma unroll
   for (int off = 1; off < LPP; off <<= 1) {
     X0 += __shfl_xor(X0, off, kWave);
@@ -1709,7 +1709,7 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
         const Rec b = R[j];
         double vx, vy, vz;
         PairOut o;
-        pair_from_records<PREC, MODEL>(P, g, mi, a, b, step, vx, vy, vz, o);
+        pair_from_records<BATCH, PREC, MODEL>(P, g, mi, a, b, step, vx, vy, vz, o);
         ex = o.dp[0];
         ey = o.dp[1];
         ez = o.dp[2];
@@ -1829,7 +1829,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
   const Rec* __restrict__ R = s.r;
   const int64_t cap = nl.cap;
   long long X = 0;  // raw sum of fixed-point bit patterns
-  long long terms = 0;
+  uint32_t terms = 0u;
   uint32_t hi_max = 0u;
   Rec a{};
   Vec4 di{};
@@ -1874,7 +1874,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
       const GeoRef<BATCH> g = geo[BATCH ? ra.rep : 0u];
       double vx, vy, vz;
       PairOut o;
-      pair_from_records<PREC, MODEL>(P, g, mi, ra, b, step, vx, vy, vz, o);
+      pair_from_records<BATCH, PREC, MODEL>(P, g, mi, ra, b, step, vx, vy, vz, o);
       ex = o.dp[0];
       ey = o.dp[1];
       ez = o.dp[2];
@@ -1941,7 +1941,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
       atomicAdd(&acc[slot], (unsigned long long)(f - kFixMagicBits));
     }
   }
-  X -= terms * kFixMagicBits;
+  X -= (long long)terms * kFixMagicBits;
 #pragma unroll
   for (int off = 1; off < LPP; off <<= 1) X += __shfl_xor(X, off, kWave);
   if (hi_max >= kFixRangeHi) atomicOr(status, ST_RANGE);
@@ -2309,7 +2309,7 @@ __global__ void k_debug_rng(uint32_t key0, uint32_t key1, uint64_t step,
   geo.key0 = key0;
   geo.key1 = key1;
   uint32_t w[4];
-  pair_words(geo, lo[k], hi[k], step, w);
+  pair_words<true>(geo, lo[k], hi[k], step, w);
   if (raw)
     for (int c = 0; c < 4; ++c) raw[4 * k + c] = w[c];
   if (g) {

@@ -91,7 +91,6 @@ struct dpde_handle {
   double *Fx = nullptr, *Fy = nullptr, *Fz = nullptr;
   Vec4* dpi = nullptr;  // dp_i of SER sweep 1
   H3* hv = nullptr;   // (p_i + dp_i/2) / m
-  uint32_t* idk = nullptr;
   double* Ui = nullptr;
   uint32_t *key = nullptr, *ticket = nullptr;
   CellBins bins{};  // cells of the list build (its key is `key`)
@@ -114,12 +113,13 @@ struct dpde_handle {
   int64_t min_rep_n = 0;  // particles of the smallest replica
   double* E0 = nullptr;   // per-replica target energy of the projection
   double* Li = nullptr;   // per-particle Laplacian share of U
-  // Hybrid: domain of each particle, domain order, bucket offsets
+  // Hybrid: domains, domain order, bucket offsets
   bool hybrid = false;
   int64_t ndoms = 0;
   int dscan_tiles = 0;
-  uint32_t* dom = nullptr;
-  uint32_t* dbucket = nullptr;  // particles by domain, in ticket order
+  uint2* did = nullptr;         // domain and identifier of each particle
+  uint32_t* dids = nullptr;     // identifiers by domain, in ticket order
+  NList inter{};                // list entries in other domains (Hybrid)
   uint32_t* dperm = nullptr;    // particles by domain, by identifier inside each
   uint32_t* lslot = nullptr;    // rank of a particle inside its domain
   uint32_t* dcount = nullptr;
@@ -386,9 +386,10 @@ int allocate(dpde_handle* h) {
     // each intra-domain pair is counted once, from its lower identifier: at
     // most half the list entries
     h->ssa.cap = ((int64_t)h->phys.cap * n + 1) / 2;
-    if ((rc = dalloc(h, &h->ticket, n)) || (rc = dalloc(h, &h->idk, n)) ||
-        (rc = dalloc(h, &h->dom, n)) || (rc = dalloc(h, &h->dperm, n)) ||
-        (rc = dalloc(h, &h->dbucket, n)) || (rc = dalloc(h, &h->lslot, n)) ||
+    if ((rc = dalloc(h, &h->ticket, n)) || (rc = dalloc(h, &h->did, n)) ||
+        (rc = dalloc(h, &h->inter.idx, entries)) || (rc = dalloc(h, &h->inter.count, n)) ||
+        (rc = dalloc(h, &h->dperm, n)) || (rc = dalloc(h, &h->dids, n)) ||
+        (rc = dalloc(h, &h->lslot, n)) ||
         (rc = dalloc(h, &h->dcount, h->ndoms + 1)) || (rc = dalloc(h, &h->dstart, h->ndoms + 1)) ||
         (rc = dalloc(h, &h->dscan_tmp, (size_t)h->dscan_tiles + 1)) ||
         (rc = dalloc(h, &h->pcnt, n)) || (rc = dalloc(h, &h->poff, n + 1)) ||
@@ -408,6 +409,8 @@ int allocate(dpde_handle* h) {
   HIPCHK(hipMemset(h->builds, 0, sizeof(unsigned long long)));
   h->nl.de = nullptr;
   if (!h->regen && (rc = dalloc(h, &h->nl.de, 3 * entries))) return rc;
+  h->inter.cap = h->nl.cap;
+  h->inter.de = h->nl.de;
   if ((rc = dalloc(h, &h->status, 4)) || (rc = dalloc(h, &h->d_step, 1)) ||
       (rc = dalloc(h, &h->d_hist_count, 1)) || (rc = dalloc(h, &h->counter, 1)) ||
       (rc = dalloc(h, &h->stats_ticket, 1)))
@@ -667,29 +670,27 @@ void enqueue_hybrid_ssa(dpde_handle* h) {
   const int b = h->aux_block;
   const int64_t n = h->n;
   const BuildCtl* now = h->always;
-  launch(h, "dom_key", k_dom_key<B>, blocks(n, b), b, h->cur, n, (const Geo*)h->geo, h->dom,
-         h->key, h->ticket, h->idk, h->dcount, (const uint32_t*)h->status);
+  launch(h, "dom_key", k_dom_key<B>, blocks(n, b), b, h->cur, n, (const Geo*)h->geo, h->did,
+         h->ticket, h->dcount, (const uint32_t*)h->status);
   // the scan writes dstart[0..ndoms), and dstart[ndoms] = n closes the last domain
   launch(h, "dom_scan_tiles", k_scan_tiles, h->dscan_tiles, kScanThreads,
          (const uint32_t*)h->dcount, h->ndoms, h->dscan_tmp, now, 0.0);
   launch(h, "dom_scan_apply", k_scan_apply, h->dscan_tiles, kScanThreads, h->dcount, h->ndoms,
          (const uint32_t*)h->dscan_tmp, h->dstart, now, 0.0);
-  launch(h, "dom_scatter", k_scatter, blocks(n, b), b, (const uint32_t*)h->key,
-         (const uint32_t*)h->ticket, (const uint32_t*)h->dstart, n, h->dbucket, now, 0.0,
+  launch(h, "dom_scatter", k_dom_scatter, blocks(n, b), b, (const uint2*)h->did,
+         (const uint32_t*)h->ticket, (const uint32_t*)h->dstart, n, h->dids,
          (const uint32_t*)h->status);
-  launch(h, "dom_rank", k_dom_rank, blocks(n, b), b, (const uint32_t*)h->dbucket,
-         (const uint32_t*)h->dstart, (const uint32_t*)h->dom, (const uint32_t*)h->idk, n, h->nl,
-         h->dperm, h->lslot, h->pcnt, (const uint32_t*)h->status);
+  launch(h, "dom_rank", k_dom_rank, blocks(n * kSub, 256), 256, (const uint32_t*)h->dids,
+         (const uint32_t*)h->dstart, (const uint2*)h->did, n, h->nl, h->inter, h->dperm, h->lslot,
+         h->pcnt, (const uint32_t*)h->status);
   // poff[k] = first pair of sorted slot k, poff[n] = all pairs
   launch(h, "ssa_scan_tiles", k_scan_tiles, h->pscan_tiles, kScanThreads,
          (const uint32_t*)h->pcnt, n, h->pscan_tmp, now, 0.0);
   launch(h, "ssa_scan_apply", k_scan_apply, h->pscan_tiles, kScanThreads, h->pcnt, n,
          (const uint32_t*)h->pscan_tmp, h->poff, now, 0.0);
-  const int pb = h->pair_block;
-  launch(h, "ssa_pairs", k_ssa_pairs<B>, blocks(n * kSub, pb), pb, h->cur, h->nl, (const uint32_t*)h->dperm,
-         (const uint32_t*)h->lslot, n, (const uint32_t*)h->dom, (const uint32_t*)h->idk,
-         (const uint32_t*)h->poff, (const Geo*)h->geo, h->phys, (const uint64_t*)h->d_step, h->ssa,
-         h->status);
+  launch(h, "ssa_pairs", k_ssa_pairs<B>, blocks(n, kSsaSlots), kSsaThreads, h->cur, h->inter,
+         (const uint32_t*)h->dperm, (const uint32_t*)h->lslot, n, (const uint32_t*)h->poff,
+         (const Geo*)h->geo, h->phys, (const uint64_t*)h->d_step, h->ssa, h->status);
   auto walk = [&](auto kern) {
     launch(h, "ssa_domains", kern, blocks(h->ndoms, kWave), kWave, h->cur,
            (const uint32_t*)h->dperm, (const uint32_t*)h->dstart, h->ndoms,
@@ -715,11 +716,12 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
                       h->nslots_u,
                       tm == kTailNone ? 0 : h->phys.project ? kTailNoTheta : kTailAll,
                       tm == kTailStatsKick ? 1 : 0};
-  const uint32_t* dom = h->hybrid ? (const uint32_t*)h->dom : nullptr;
+  // Hybrid: the pairs inside one domain are SSA's, the sweeps take the others
+  const NList nl = h->hybrid ? h->inter : h->nl;
   if (h->hybrid) enqueue_hybrid_ssa<B>(h);
   if (h->phys.scheme == DPDE_SCHEME_SEM) {
-    launch(h, "pass_b_sem", k_pass_b<B, PR, 1, MD>, blocks(n * kSubSer, b), b, h->cur, h->nl, n,
-           (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, 0, dom, inl_now, h->alt.r, tail,
+    launch(h, "pass_b_sem", k_pass_b<B, PR, 1, MD>, blocks(n * kSubSer, b), b, h->cur, nl, n,
+           (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, 0, inl_now, h->alt.r, tail,
            h->status);
   } else {
     const bool uq = uniq_form(h);
@@ -727,24 +729,24 @@ void enqueue_fd_t(dpde_handle* h, TailMode tm) {
       with_tile_shape(h, [&](auto sh) {
         constexpr TileShape S = kTiles[decltype(sh)::value];
         launch(h, "pass_b_ser", k_pass_b_uniq<B, PR, MD, S.tile, S.lanes>, blocks(n, S.tile),
-               S.lanes * S.tile, h->cur, h->nl, n, (const Geo*)h->geo, h->phys, d_step, h->dpi,
+               S.lanes * S.tile, h->cur, nl, n, (const Geo*)h->geo, h->phys, d_step, h->dpi,
                h->hv, store, h->status);
       });
     } else {
-      launch(h, "pass_b_ser", k_pass_b<B, PR, 0, MD>, blocks(n * kSubSer, b), b, h->cur, h->nl,
-             n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, store, dom, inl_now,
+      launch(h, "pass_b_ser", k_pass_b<B, PR, 0, MD>, blocks(n * kSubSer, b), b, h->cur, nl,
+             n, (const Geo*)h->geo, h->phys, d_step, h->dpi, h->hv, store, inl_now,
              h->alt.r, tail, h->status);
     }
     // the surrogate's 1/T_i is computed inside sweep 2 (learned-EOS modes)
     const MlpDev m = mlp_dev(h->mlp);
     const int mode = h->mlp.trained ? h->phys.theta_mode : 0;
     auto pass_c = [&](auto kern, unsigned grid, unsigned block) {
-      launch(h, "pass_c_ser", kern, grid, block, h->cur, h->nl, n, (const Geo*)h->geo,
+      launch(h, "pass_c_ser", kern, grid, block, h->cur, nl, n, (const Geo*)h->geo,
              h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now, m, mode, h->alt.r,
              tail, h->status);
     };
     auto pass_c_uniq = [&](auto kern, int tile, int lanes) {
-      launch(h, "pass_c_ser", kern, blocks(n, tile), lanes * tile, h->cur, h->nl, n,
+      launch(h, "pass_c_ser", kern, blocks(n, tile), lanes * tile, h->cur, nl, n,
              (const Geo*)h->geo, h->phys, d_step, (const Vec4*)h->dpi, (const H3*)h->hv, inl_now,
              m, mode, h->alt.r, tail, h->status);
     };

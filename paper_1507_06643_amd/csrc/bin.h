@@ -398,17 +398,6 @@ __global__ void k_scan_apply(uint32_t* __restrict__ in, int64_t n,
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = offset + total;
 }
 
-// perm[offset[key] + ticket] = old slot.
-__global__ void k_scatter(const uint32_t* __restrict__ key, const uint32_t* __restrict__ ticket,
-                          const uint32_t* __restrict__ start, int64_t n,
-                          uint32_t* __restrict__ perm, const BuildCtl* ctl, double half_skin2,
-                          const uint32_t* status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;
-  perm[start[key[i]] + ticket[i]] = (uint32_t)i;
-}
-
 // ---- the list build's binning -------------------------------------------------
 // Cells: the histogram and, per cell, a chain of its particles (link[i] = the
 // identifier and the next particle; `first` heads it), both left cleared by the

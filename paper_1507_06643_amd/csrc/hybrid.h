@@ -20,13 +20,12 @@ __device__ __forceinline__ uint32_t domain_index(const Geo& g, double x, double 
   return (uint32_t)(g.dom_base + c[0] + (int64_t)g.ndom[0] * (c[1] + (int64_t)g.ndom[1] * c[2]));
 }
 
-// Domain of every particle (positions at the start of the fluctuation/
-// dissipation step), bucket histogram and ticket (one atomic per run of
-// equal domains in a wave), identifier for the per-domain ranking.
+// Domain and identifier of every particle (positions at the start of the
+// fluctuation/dissipation step), bucket histogram and ticket (one atomic per
+// run of equal domains in a wave).
 template <bool BATCH>
 __global__ void k_dom_key(PState s, int64_t n, const Geo* __restrict__ geo,
-                          uint32_t* __restrict__ dom, uint32_t* __restrict__ key,
-                          uint32_t* __restrict__ ticket, uint32_t* __restrict__ idk,
+                          uint2* __restrict__ did, uint32_t* __restrict__ ticket,
                           uint32_t* __restrict__ count, const uint32_t* status) {
   if (status_set(status)) return;  // uniform
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -36,105 +35,135 @@ __global__ void k_dom_key(PState s, int64_t n, const Geo* __restrict__ geo,
     const Rec& rc = s.r[i];
     const Geo& g = geo[BATCH ? rc.rep : 0u];
     d = domain_index(g, rc.qx, rc.qy, rc.qz);
-    dom[i] = d;
-    key[i] = d;
-    idk[i] = rc.id;
+    did[i] = make_uint2(d, rc.id);
   }
   const uint32_t t = run_ticket(d, live, count);
   if (live) ticket[i] = t;
 }
 
-// Rank of every particle inside its domain by identifier (the order the SSA
-// sweep takes the domain's particles), out of place: one thread per bucket
-// slot counts the smaller identifiers of its bucket.  lslot[i] is the rank.
-// The thread also counts the particle's pairs of the sweep (below) for its
-// sorted slot.
+// The identifiers of each domain's particles, in ticket order.
+__global__ void k_dom_scatter(const uint2* __restrict__ did, const uint32_t* __restrict__ ticket,
+                              const uint32_t* __restrict__ dstart, int64_t n,
+                              uint32_t* __restrict__ ids, const uint32_t* status) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (status_set(status)) return;
+  const uint2 di = did[i];
+  ids[dstart[di.x] + ticket[i]] = di.y;
+}
+
+// One lane group per particle.  Its rank inside its domain by identifier (the
+// order the SSA sweep takes the domain's particles) is the number of smaller
+// identifiers in the domain: sorted[] and lslot[] are the order and its
+// inverse.  The group then splits the particle's list in list order: the
+// neighbours in other domains go to `inter`, the list of the SER sweeps; those
+// of higher identifier in the same domain, from which the SSA pairs are made,
+// to the far end of the same row (entry cap - 1 downwards; together they are
+// at most the list); their number to pcnt[] of the sorted slot.
 //
+// Bound by the gathers of the neighbours' domains.  The sweeps and k_ssa_pairs
+// each tested every entry before, though 57% of the neighbours are in the own
+// domain at 32 particles per domain: N = 1,048,576, sweep 1 240 -> 156 us,
+// sweep 2 181 -> 140, k_ssa_pairs 209 -> 95, this kernel (one lane per
+// particle, count only, domain and identifier gathered apart) 116 -> 110.
+__global__ __launch_bounds__(kPairBlockMax) void k_dom_rank(
+    const uint32_t* __restrict__ ids, const uint32_t* __restrict__ dstart,
+    const uint2* __restrict__ did, int64_t n, NList nl, NList inter,
+    uint32_t* __restrict__ sorted, uint32_t* __restrict__ lslot, uint32_t* __restrict__ pcnt,
+    const uint32_t* status) {
+  const Lanes L = lanes();
+  if (L.i >= n) return;  // uniform in the group
+  if (status_set(status)) return;
+  const int64_t i = L.i;
+  const uint2 me = did[i];
+  const uint32_t b = dstart[me.x], e = dstart[me.x + 1];
+  uint32_t r = 0;
+  for (uint32_t m = b + L.sub; m < e; m += kSub) r += ids[m] < me.y ? 1u : 0u;
+#pragma unroll
+  for (int o = 1; o < kSub; o <<= 1) r += (uint32_t)__shfl_xor((int)r, o, kWave);
+  const uint32_t nn = nl.count[i];
+  const uint32_t below = (1u << L.sub) - 1u;
+  uint32_t ni = 0, nh = 0;
+  for (uint32_t base = 0; base < nn; base += kSub) {
+    const uint32_t m = base + L.sub;
+    uint32_t j = 0;
+    bool out = false, high = false;
+    if (m < nn) {
+      j = nl.idx[list_entry(i, m, nl.cap)];
+      const uint2 dj = did[j];
+      out = dj.x != me.x;
+      high = !out && dj.y > me.y;
+    }
+    const uint32_t ob = group_ballot(L, out), hb = group_ballot(L, high);
+    if (out) inter.idx[list_entry(i, ni + __popc(ob & below), inter.cap)] = j;
+    if (high) inter.idx[list_entry(i, inter.cap - 1 - (nh + __popc(hb & below)), inter.cap)] = j;
+    ni += __popc(ob);
+    nh += __popc(hb);
+  }
+  if (L.sub == 0) {
+    inter.count[i] = ni;
+    sorted[b + r] = (uint32_t)i;
+    lslot[i] = r;
+    pcnt[b + r] = nh;
+  }
+}
+
 // The intra-domain pairs in the order of the SSA sweep: the domain's
 // particles by increasing identifier, each with its list neighbours (in
 // identifier order) of higher identifier in the same domain.  After a scan
 // of the counts, k_ssa_pairs writes each pair's local slots, its weight
 // chi = w(r)^2 and its noise G_ij (positions are fixed during the sweep, so
 // both are known before it starts).
-__global__ void k_dom_rank(const uint32_t* __restrict__ bucket, const uint32_t* __restrict__ dstart,
-                           const uint32_t* __restrict__ dom, const uint32_t* __restrict__ idk,
-                           int64_t n, NList nl, uint32_t* __restrict__ sorted,
-                           uint32_t* __restrict__ lslot, uint32_t* __restrict__ pcnt,
-                           const uint32_t* status) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  if (status_set(status)) return;
-  const uint32_t i = bucket[k];
-  const uint32_t d = dom[i];
-  const uint32_t b = dstart[d], e = dstart[d + 1];
-  const uint32_t my = idk[i];
-  uint32_t r = 0;
-  for (uint32_t m = b; m < e; ++m) r += idk[bucket[m]] < my ? 1u : 0u;
-  sorted[b + r] = i;
-  lslot[i] = r;
-  uint32_t c = 0;
-  const uint32_t nn = nl.count[i];
-  for (uint32_t m = 0; m < nn; ++m) {
-    const uint32_t j = nl.idx[list_entry(i, m, nl.cap)];
-    c += (dom[j] == d && idk[j] > my) ? 1u : 0u;
-  }
-  pcnt[b + r] = c;
-}
-
 struct SsaPairs {
   uint2* idx;   // local slots (lower identifier first)
   Vec4* gc;     // G_ij in x, y, z and chi in w
   int64_t cap;
 };
 
-// One lane group per sorted slot: the group's lanes test the list entries
-// in turn, and the pairs found in a trip take consecutive places in list order.
+// A block takes kSsaSlots sorted slots, whose pairs are consecutive, a lane per
+// pair whatever slot it belongs to (found among the slots' first pairs).
+constexpr int kSsaSlots = 64;
+constexpr int kSsaThreads = 256;
+
 template <bool BATCH>
-__global__ __launch_bounds__(kPairBlockMax) void k_ssa_pairs(
-    PState s, NList nl, const uint32_t* __restrict__ sorted, const uint32_t* __restrict__ lslot,
-    int64_t n, const uint32_t* __restrict__ dom, const uint32_t* __restrict__ idk,
-    const uint32_t* __restrict__ poff, const Geo* __restrict__ geo, Phys P,
-    const uint64_t* __restrict__ d_step, SsaPairs sp, uint32_t* status) {
-  const Lanes L = lanes();
-  if (L.i >= n) return;  // uniform in the group
-  if (status_set(status)) return;
-  const int64_t k = L.i;
+__global__ __launch_bounds__(kSsaThreads) void k_ssa_pairs(
+    PState s, NList inter, const uint32_t* __restrict__ sorted,
+    const uint32_t* __restrict__ lslot, int64_t n, const uint32_t* __restrict__ poff,
+    const Geo* __restrict__ geo, Phys P, const uint64_t* __restrict__ d_step, SsaPairs sp,
+    uint32_t* status) {
+  __shared__ uint32_t first[kSsaSlots + 1];
+  __shared__ uint32_t st_flag;
+  if (block_status_set(status, &st_flag)) return;  // uniform in the block
+  const int64_t k0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kSsaSlots;
+  if (threadIdx.x <= kSsaSlots) {
+    const int64_t k = k0 + threadIdx.x;
+    first[threadIdx.x] = poff[k < n ? k : n];  // poff[n]: all pairs
+  }
+  __syncthreads();
   const uint64_t step = *d_step;
   const Rec* __restrict__ R = s.r;
-  const uint32_t i = sorted[k];
-  const uint32_t d = dom[i], id = idk[i], li = lslot[i];
-  const double xi = R[i].qx, yi = R[i].qy, zi = R[i].qz;
-  const Geo& g = geo[BATCH ? R[i].rep : 0u];
-  const uint32_t nn = nl.count[i];
-  int64_t t = poff[k];
-  for (uint32_t base = 0; base < nn; base += kSub) {
-    const uint32_t m = base + L.sub;
-    uint32_t j = 0;
-    bool take = false;
-    if (m < nn) {
-      j = nl.idx[list_entry(i, m, nl.cap)];
-      take = dom[j] == d && idk[j] > id;  // the same test as k_dom_rank
+  const uint32_t end = first[kSsaSlots];
+  for (uint32_t t = first[0] + threadIdx.x; t < end; t += kSsaThreads) {
+    if ((int64_t)t >= sp.cap) {
+      atomicOr(status, ST_OVERFLOW);
+      break;
     }
-    const uint32_t bits = group_ballot(L, take);
-    if (take) {
-      const int64_t tt = t + __popc(bits & ((1u << L.sub) - 1u));
-      if (tt >= sp.cap) {
-        atomicOr(status, ST_OVERFLOW);
-      } else {
-        double dx, dy, dz;
-        separation(g, xi, yi, zi, R[j].qx, R[j].qy, R[j].qz, dx, dy, dz);
-        const double r2 = dist2(dx, dy, dz);
-        const double r = r2 * inv_sqrt_f64(r2);
-        const double w = 1.0 - r * P.inv_rc;
-        uint32_t wd[4];
-        pair_words<!BATCH>(g, id, idk[j], step, wd);  // i is the lower identifier
-        double G[3];
-        box_muller_f64(wd, G);
-        sp.idx[tt] = make_uint2(li, lslot[j]);
-        sp.gc[tt] = Vec4{G[0], G[1], G[2], w * w};
-      }
-    }
-    t += __popc(bits);
+    const int o = overflow_owner<kSsaSlots>(first, t);
+    const uint32_t i = sorted[k0 + o];
+    const uint32_t j =
+        inter.idx[list_entry(i, inter.cap - 1 - (int64_t)(t - first[o]), inter.cap)];
+    const Geo& g = geo[BATCH ? R[i].rep : 0u];
+    double dx, dy, dz;
+    separation(g, R[i].qx, R[i].qy, R[i].qz, R[j].qx, R[j].qy, R[j].qz, dx, dy, dz);
+    const double r2 = dist2(dx, dy, dz);
+    const double r = r2 * inv_sqrt_f64(r2);
+    const double w = 1.0 - r * P.inv_rc;
+    uint32_t wd[4];
+    pair_words<!BATCH>(g, R[i].id, R[j].id, step, wd);  // i is the lower identifier
+    double G[3];
+    box_muller_f64(wd, G);
+    sp.idx[t] = make_uint2(lslot[i], lslot[j]);
+    sp.gc[t] = Vec4{G[0], G[1], G[2], w * w};
   }
 }
 

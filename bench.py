@@ -318,10 +318,11 @@ def _profile_lines():
 
 
 # The pair kernels of the headline workload as rocprofv3 names them (batch,
-# precision, model and, for sweep 2, the surrogate fused in: the learned EOS).
-PAIR_KERNEL_SYMBOLS = {"pass_a_forces": "k_pass_a_uniq<false, 0, false>",
-                       "pass_b_ser": "k_pass_b_uniq<false, 0, 0>",
-                       "pass_c_ser": "k_pass_c_uniq<false, 0, 0, 0, 1>"}
+# precision, model and, for sweep 2, the surrogate fused in: the learned EOS;
+# then the tile's particles and the lanes of each).
+PAIR_KERNEL_SYMBOLS = {"pass_a_forces": "k_pass_a_uniq<false, 0, false, 128, 4>",
+                       "pass_b_ser": "k_pass_b_uniq<false, 0, 0, 128, 2>",
+                       "pass_c_ser": "k_pass_c_uniq<false, 0, 0, 0, 1, 128, 2>"}
 
 
 def counter_traffic(kernel):

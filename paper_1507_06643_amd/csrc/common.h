@@ -133,8 +133,7 @@ __device__ __forceinline__ void pair_words(const Geo& g, uint32_t lo, uint32_t h
 // or two beside the vector ones.  Left to itself the compiler keeps the series'
 // constants across the pair loops in vector registers (sweep 1 of the both-sides
 // form: 114 instead of 69, four waves per SIMD instead of seven) and copies
-// them before use.  With this, the uniform round keys and the shorter series a
-// pair term takes 265 vector instructions instead of 330.
+// them before use.
 __device__ __forceinline__ double scalar_f64(double k) {
   asm volatile("" : "+s"(k));
   return k;
@@ -143,8 +142,7 @@ __device__ __forceinline__ double scalar_f64(double k) {
 // ln u for u = (x + 1/2) 2^-32 = (2x + 1) 2^-33.  With 2x + 1 = m 2^e and
 // m in [1/sqrt 2, sqrt 2): ln u = (e - 33) ln 2 + ln m, and
 // ln m = 2 atanh(s) = 2 (s + s^3/3 + s^5/5 + ...), s = (m - 1)/(m + 1),
-// |s| <= 0.172; the series beyond 2s as its interpolant in s^2 at seven
-// Chebyshev nodes (relative error 5e-18; the series itself takes ten terms).
+// |s| <= 0.172 (eleven terms leave a relative remainder below 1e-18).
 __device__ __forceinline__ double ln_uniform_f64(uint32_t x) {
   const double y = 2.0 * (double)x + 1.0;  // exact
   double m = __builtin_amdgcn_frexp_mant(y);  // [1/2, 1)
@@ -161,13 +159,16 @@ __device__ __forceinline__ double ln_uniform_f64(uint32_t x) {
   double s = f * r;
   s = fma(r, fma(-s, d, f), s);
   const double z = s * s;
-  double p = 0.14616449685043387;
-  p = fma(p, z, scalar_f64(0.15331721600556042));
-  p = fma(p, z, scalar_f64(0.18182889125261723));
-  p = fma(p, z, scalar_f64(0.2222221113479508));
-  p = fma(p, z, scalar_f64(0.28571428625975487));
-  p = fma(p, z, scalar_f64(0.39999999999899505));
-  p = fma(p, z, scalar_f64(0.666666666666667));
+  double p = 0.09523809523809523;  // 2/21
+  p = fma(p, z, scalar_f64(0.10526315789473684));
+  p = fma(p, z, scalar_f64(0.11764705882352941));
+  p = fma(p, z, scalar_f64(0.13333333333333333));
+  p = fma(p, z, scalar_f64(0.15384615384615385));
+  p = fma(p, z, scalar_f64(0.18181818181818182));
+  p = fma(p, z, scalar_f64(0.2222222222222222));
+  p = fma(p, z, scalar_f64(0.2857142857142857));
+  p = fma(p, z, scalar_f64(0.4));
+  p = fma(p, z, scalar_f64(0.6666666666666666));
   const double lnm = fma(s * z, p, 2.0 * s);  // 2s + s z (2/3 + ...)
   const double E = (double)(e - 33);
   // ln 2 split so that E * ln2_hi is exact
@@ -206,25 +207,27 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t flip) {
 // sin(2 pi u) and cos(2 pi u) for u = (w + 1/2) 2^-32.  The quarter turn k
 // nearest to u and the distance from it come from w as an integer: 2u =
 // k/2 + y with y the low 30 bits of w, signed, plus 1/2 in units of 2^-31
-// (exact, |y| <= 1/4).  sin(pi y) = pi y + y^3 ps(y^2) and cos(pi y) = 1 + y^2
-// pc(y^2), ps and pc interpolating the series at six and seven Chebyshev nodes
-// (errors 1.3e-17 and 1.2e-19); k mod 4 then rotates the pair.
+// (exact, |y| <= 1/4); the Taylor series of sin(pi y) and cos(pi y) to the
+// 17th and 16th power, then k mod 4 rotates the pair.
 __device__ __forceinline__ void sincos_uniform_f64(uint32_t w, double& sn, double& cs) {
   const double y = fma((double)((int32_t)(w << 2) >> 2), 0x1p-31, 0x1p-32);
   const double z = y * y;
-  double ps = 0.00046221110224187623;
-  ps = fma(ps, z, scalar_f64(-0.0073701436435937495));
-  ps = fma(ps, z, scalar_f64(0.08214587730641625));
-  ps = fma(ps, z, scalar_f64(-0.5992645291845385));
-  ps = fma(ps, z, scalar_f64(2.5501640398766154));
-  ps = fma(ps, z, scalar_f64(-5.167712780049969));
+  double ps = 7.952054001475513e-07;
+  ps = fma(ps, z, scalar_f64(-2.1915353447830217e-05));
+  ps = fma(ps, z, scalar_f64(0.00046630280576761255));
+  ps = fma(ps, z, scalar_f64(-0.0073704309457143504));
+  ps = fma(ps, z, scalar_f64(0.08214588661112823));
+  ps = fma(ps, z, scalar_f64(-0.5992645293207921));
+  ps = fma(ps, z, scalar_f64(2.5501640398773455));
+  ps = fma(ps, z, scalar_f64(-5.16771278004997));
   const double sp = fma(y * z, ps, scalar_f64(3.141592653589793) * y);
-  double pc = -0.00010370082971594627;
-  pc = fma(pc, z, scalar_f64(0.001929493874894941));
-  pc = fma(pc, z, scalar_f64(-0.025806887964701878));
-  pc = fma(pc, z, scalar_f64(0.23533063028399223));
-  pc = fma(pc, z, scalar_f64(-1.3352627688538095));
-  pc = fma(pc, z, scalar_f64(4.058712126416765));
+  double pc = 4.303069587032947e-06;
+  pc = fma(pc, z, scalar_f64(-0.0001046381049248457));
+  pc = fma(pc, z, scalar_f64(0.0019295743094039231));
+  pc = fma(pc, z, scalar_f64(-0.02580689139001406));
+  pc = fma(pc, z, scalar_f64(0.2353306303588932));
+  pc = fma(pc, z, scalar_f64(-1.3352627688545895));
+  pc = fma(pc, z, scalar_f64(4.0587121264167685));
   pc = fma(pc, z, scalar_f64(-4.934802200544679));
   const double cp = fma(z, pc, 1.0);
   const uint32_t r = w + 0x20000000u;  // k in the top two bits

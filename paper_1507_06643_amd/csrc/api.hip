@@ -338,6 +338,49 @@ void physics(const dpde_params* P, Phys& ph) {
   }
 }
 
+// The tile form (the default): pairs inside a 128-particle tile evaluated
+// once, every per-particle pair sum in fixed point.  Not for SEM, whose update
+// is not written as a sum of stored terms here, nor Hybrid, whose SSA part
+// reads full, identifier-ordered lists; and only for the soft potential with
+// a < 1024, whose pair force and potential stay inside the range of pass A's
+// fixed-point sums (the splined LJ force grows without bound as r -> 0).
+bool uniq_applies(const dpde_handle* h) {
+  return h->phys.scheme == DPDE_SCHEME_SER && !h->hybrid && h->phys.potential == DPDE_POT_SOFT &&
+         h->phys.a < 1024.0 && h->phys.fix_ok;
+}
+bool uniq_form(const dpde_handle* h) { return h->pairs_once && uniq_applies(h); }
+
+// Tiles of the tile passes: particles per tile, and lanes per particle of pass
+// A and of the sweeps.  A tile is a block; at N = 1000 eight tiles of 128 use
+// eight of the 256 CUs, and a pass takes as long as a lane's chain of list
+// entries, a gather and a pair term (1.5 us) each.  Smaller tiles with more
+// lanes spread the same terms over more CUs and shorten the chain, but list
+// more pairs on both sides (a smaller share lies inside a tile), so a system
+// that fills the chip keeps tiles of 128 and two lanes.  Every sum is exact:
+// the choice changes no bit.  Measured, us per step in FP64 (graph replays,
+// density 3), tiles of 128 / 64 / 32:
+//   N =  1000   50.6 / 45.3 / 41.4     N =  48000   71.7 / 66.7 / 72.4
+//   N =  8000   51.7 / 46.6 / 42.3     N =  65536   73.9 / 73.9 / 88.0
+//   N = 16000   54.0 / 48.0 / 47.2     N =  98304   88.4 / 90.9 / 110.7
+//   N = 32768   59.2 / 56.6 / 59.4     N = 131072  102.8 / 112.2 / 135.2
+struct TileShape {
+  int tile, lanes_a, lanes;
+};
+constexpr TileShape kTiles[3] = {{128, 4, 2}, {64, 4, 4}, {32, 8, 8}};
+constexpr int64_t kTileMidN = 73728, kTileSmallN = 16384;  // largest N of the smaller tiles
+
+int tile_index(const dpde_handle* h) {
+  return h->n <= kTileSmallN ? 2 : h->n <= kTileMidN ? 1 : 0;
+}
+TileShape tile_shape(const dpde_handle* h) { return kTiles[tile_index(h)]; }
+
+// Entries a list needs beyond the capacity asked for, which is that of tiles of
+// 128 (k_build_skin): of the 128 - T particles outside a particle's own smaller
+// tile, those lists leave out half.
+int tile_headroom(const dpde_handle* h) {
+  return uniq_applies(h) ? (kUniqTile - tile_shape(h).tile) / 2 : 0;
+}
+
 int alloc_pstate(dpde_handle* h, PState& s) {
   int rc;
   if ((rc = dalloc(h, &s.r, h->n)) || (rc = dalloc(h, &s.eps, h->n))) return rc;
@@ -364,8 +407,8 @@ int allocate(dpde_handle* h) {
   h->scan_tiles = (int)((h->ncells + kScanTile - 1) / kScanTile);
   if (h->scan_tiles > 1024 * 8) return fail(DPDE_EINVAL, "too many cells (%lld)", (long long)h->ncells);
   if ((rc = dalloc(h, &h->scan_tmp, h->scan_tiles + 1))) return rc;
-  h->nl.cap = h->phys.cap;
-  const size_t entries = list_size(n, h->phys.cap);
+  h->nl.cap = h->phys.cap + tile_headroom(h);
+  const size_t entries = list_size(n, h->nl.cap);
   if ((rc = dalloc(h, &h->nl.idx, entries)) || (rc = dalloc(h, &h->nl.count, n)))
     return rc;
   if ((rc = dalloc(h, &h->qid, n)) ||
@@ -375,7 +418,7 @@ int allocate(dpde_handle* h) {
       (rc = dalloc(h, &h->slot, n)) ||
       (rc = dalloc(h, &h->skin.count, n)))
     return rc;
-  h->skin.cap = h->phys.cap;
+  h->skin.cap = h->nl.cap;
   if (h->hybrid) {
     h->dscan_tiles = (int)((h->ndoms + kScanTile - 1) / kScanTile);
     if (h->dscan_tiles > 1024 * 8) return fail(DPDE_EINVAL, "too many domains");
@@ -475,17 +518,6 @@ int status_to_code(uint32_t st) {
 }
 
 // ---- the launch sequence -----------------------------------------------------
-// The tile form (the default): pairs inside a 128-particle tile evaluated
-// once, every per-particle pair sum in fixed point.  Not for SEM, whose update
-// is not written as a sum of stored terms here, nor Hybrid, whose SSA part
-// reads full, identifier-ordered lists; and only for the soft potential with
-// a < 1024, whose pair force and potential stay inside the range of pass A's
-// fixed-point sums (the splined LJ force grows without bound as r -> 0).
-bool uniq_form(const dpde_handle* h) {
-  return h->pairs_once && h->phys.scheme == DPDE_SCHEME_SER && !h->hybrid &&
-         h->phys.potential == DPDE_POT_SOFT && h->phys.a < 1024.0 && h->phys.fix_ok;
-}
-
 // 1/T from the new energies inside the pass that updates them (not by the
 // surrogate).
 bool eos_inline(const dpde_handle* h) {
@@ -503,30 +535,6 @@ bool fused_tail(const dpde_handle* h) {
   const bool later = h->phys.project || h->phys.scheme == DPDE_SCHEME_SEM;
   return (eos_inline(h) || !later) && (!h->batch || h->min_rep_n >= kUniqTile);
 }
-
-// Tiles of the tile passes: particles per tile, and lanes per particle of pass
-// A and of the sweeps.  A tile is a block; at N = 1000 eight tiles of 128 use
-// eight of the 256 CUs, and a pass takes as long as a lane's chain of list
-// entries, a gather and a pair term (1.5 us) each.  Smaller tiles with more
-// lanes spread the same terms over more CUs and shorten the chain, but list
-// more pairs on both sides (a smaller share lies inside a tile), so a system
-// that fills the chip keeps tiles of 128 and two lanes.  Every sum is exact:
-// the choice changes no bit.  Measured, us per step in FP64 (graph replays,
-// density 3), tiles of 128 / 64 / 32:
-//   N =  1000   50.6 / 45.3 / 41.4     N =  48000   71.7 / 66.7 / 72.4
-//   N =  8000   51.7 / 46.6 / 42.3     N =  65536   73.9 / 73.9 / 88.0
-//   N = 16000   54.0 / 48.0 / 47.2     N =  98304   88.4 / 90.9 / 110.7
-//   N = 32768   59.2 / 56.6 / 59.4     N = 131072  102.8 / 112.2 / 135.2
-struct TileShape {
-  int tile, lanes_a, lanes;
-};
-constexpr TileShape kTiles[3] = {{128, 4, 2}, {64, 4, 4}, {32, 8, 8}};
-constexpr int64_t kTileMidN = 73728, kTileSmallN = 16384;  // largest N of the smaller tiles
-
-int tile_index(const dpde_handle* h) {
-  return h->n <= kTileSmallN ? 2 : h->n <= kTileMidN ? 1 : 0;
-}
-TileShape tile_shape(const dpde_handle* h) { return kTiles[tile_index(h)]; }
 
 // f with the handle's tile shape as a compile-time index into kTiles.
 template <class F>
@@ -601,14 +609,14 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   // per CU (48 and 96 rows: 306 and 829 us per build at N = 1M; 36 and 80: 234
   // and 597).  Small systems take more waves per tile, so that each has a
   // piece or two (N = 65,536, 512 threads: 41 -> 29 us).
-  const int rows = std::min((int)h->skin.cap, uniq ? 32 : h->skin.cap > 96 ? 80 : 36);
+  const int rows = std::min((int)h->skin.cap, uniq ? 32 : h->phys.cap > 96 ? 80 : 36);
   const unsigned tiles = blocks(n, kUniqTile);
   const int threads = tiles >= 2048 ? 256 : (tiles >= 512 || rows > 48) ? 512 : 1024;
   auto build = [&](auto kern) {
     launch_lds(h, "build_skin", kern, tiles, threads, build_lds(rows, threads), h->alt, h->cur,
                (const QIdF*)h->qid, (const uint32_t*)h->bins.start, n, (const Geo*)h->geo,
                std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile_shape(h).tile,
-               h->bins, h->status);
+               (uint32_t)h->phys.cap, h->bins, h->status);
   };
   if (h->batch) {
     if (uniq) build(k_build_skin<true, true>);
@@ -619,7 +627,7 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   }
   // the tile form adds every pair term in fixed point: its lists need no order
   if (!uniq)
-    launch(h, "sort_skin", h->skin.cap > 96 ? k_sort_skin<128> : k_sort_skin<64>,
+    launch(h, "sort_skin", h->phys.cap > 96 ? k_sort_skin<128> : k_sort_skin<64>,
            blocks(n, 256), 256, n, h->skin, (const uint32_t*)h->slot, ctl, hs2,
            (const uint32_t*)h->status);
 }

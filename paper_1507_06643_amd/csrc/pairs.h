@@ -223,6 +223,11 @@ struct SkinList {
 // read it add their pair terms in fixed point, in any order.  Otherwise it
 // holds identifier rows (first + id) until k_sort_skin has ordered them and
 // turned them into memory indices.
+// A list longer than `limit`, the capacity the caller asked for, is an
+// overflow.  Tiles below 128 list more of the pairs on both sides (at most
+// (128 - tile) / 2 per particle, for which the lists have room: sl.cap), so
+// what counts there is the list that tiles of 128 would hold: whether a system
+// fits does not depend on the tile.
 // A run reached across a periodic face holds images one box length away: its
 // candidates are compared after that shift (d - s with s = +-L), which for
 // every candidate within the list radius is the minimum image itself, with
@@ -246,7 +251,7 @@ template <bool BATCH, bool UNIQ>
 __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
     int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
-    const BuildCtl* ctl, double half_skin2, int rows, int tile, CellBins cells,
+    const BuildCtl* ctl, double half_skin2, int rows, int tile, uint32_t limit, CellBins cells,
     uint32_t* status) {
   extern __shared__ uint32_t dyn[];  // see build_lds
   __shared__ uint32_t cell_s[kUniqTile];
@@ -375,6 +380,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     pre -= cn;
     const QIdF own = qid[tb + (lane < p1 - p0 ? p0 + lane : p0)];  // lane q: particle p0 + q
     uint32_t counts = 0;  // lane q: entries of particle p0 + q so far
+    uint32_t wide = 0;    // lane q: those of them that tiles of 128 would list too
     const uint32_t first = (uint32_t)g.first;
     for (uint32_t w0 = 0; w0 < total; w0 += kBuildWindow) {
       // the cells' two lanes write the window's candidate indices in turn
@@ -419,6 +425,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
         const float yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.y), q));
         const float zi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.z), q));
         uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)counts, q);
+        uint32_t base_wide = (uint32_t)__builtin_amdgcn_readlane((int)wide, q);
         const uint32_t tq = (uint32_t)(p0 + q);
 #pragma unroll
         for (int c = 0; c < kBuildChunks; ++c) {
@@ -436,7 +443,10 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
             const unsigned long long out = __ballot((rel[c] ^ tq) >= (uint32_t)tile);
             const unsigned long long below = __ballot(rel[c] < tq), above = __ballot(rel[c] > tq);
             const unsigned long long same = (tq & 1u) ? odd[c] : ~odd[c];
-            m &= out | (same & below) | (~same & above);
+            const unsigned long long mine = (same & below) | (~same & above);
+            if (tile < kUniqTile)  // uniform
+              base_wide += (uint32_t)__popcll(m & (__ballot(rel[c] >= (uint32_t)kUniqTile) | mine));
+            m &= out | mine;
           } else {
             m &= __ballot(rel[c] != tq);
           }
@@ -452,6 +462,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
           }
         }
         counts = lane == q ? base : counts;
+        wide = lane == q ? base_wide : wide;
       };
       if (images) {
         for (int q = 0; q < p1 - p0; ++q) test(q, std::true_type{});
@@ -461,10 +472,8 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
       __builtin_amdgcn_wave_barrier();  // the next window overwrites src
     }
     if (lane < p1 - p0) {
-      if (counts > cap) {
-        atomicOr(status, ST_OVERFLOW);
-        counts = cap;
-      }
+      if ((UNIQ && tile < kUniqTile ? wide : counts) > limit) atomicOr(status, ST_OVERFLOW);
+      counts = counts < cap ? counts : cap;
       count_s[p0 + lane] = counts;
       atomicMax(&most_s, counts);
     }
@@ -1333,7 +1342,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
     ns = sl.count[i];
     if constexpr (BATCH) rep = R[i].rep;
   }
-  const uint32_t cap = (uint32_t)P.cap;
+  const uint32_t cap = (uint32_t)nl.cap;
   long long XF0 = 0, XF1 = 0, XF2 = 0, XU = 0, XLh = 0, XLl = 0;  // raw fixed-point words
   uint32_t terms = 0u;
   uint32_t hi_l = 0u;

@@ -64,3 +64,23 @@ def test_list_capacity_is_that_of_tiles_of_128(dp, n):
     assert ex.value.code == dp._lib.DPDE_EOVERFLOW
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n", [400, 26000])
+def test_capacity_below_the_staged_rows(dp, n):
+    """Lists of fewer entries than pass A stages in LDS (28 and more): a
+    dilute system with room for six neighbours steps like one with room for
+    ninety-six, and like the oracle."""
+    box = [(n / 0.2) ** (1 / 3)] * 3
+    q, p, e = W.equilibrium_state(n, box, seed=n)
+    runs = []
+    for cap in (96, 16):
+        s = dp.System(dp.Config(n=n, box=box, dt=0.01, neighbor_cap=cap), q, p, e)
+        s.step(1)
+        runs.append(_state(s))
+        s.close()
+    assert _same(*runs)
+    S = O.State(O.make_params(n, box, dt=0.01), q, p, e)
+    assert S.step(1)[0] == 0
+    assert np.abs(runs[1][1] - S.p).max() < TOL
+    assert np.abs(runs[1][2] - S.eps).max() < TOL * np.abs(S.eps).mean()

@@ -177,10 +177,12 @@ int dpde_init(const dpde_params* params, const double* q, const double* p, const
  * second sweep, as in Sec. 3.2.1; the same bits either way).  Between calls
  * the state is the end of a step: states and records do not depend on how
  * the steps are split over calls (inside a call the next step's kick may run
- * at the end of the previous step's sweep 2).
+ * at the end of the previous step's last pair pass, in every scheme).
  * Returns the first failure of the run (DPDE_ENEG_EINT, DPDE_EOVERFLOW,
  * DPDE_ENONFINITE, DPDE_EEOS); the state is then that of the failing step,
- * partially updated, and can still be read.
+ * partially updated, and can still be read: a kick of the step after it that
+ * ran already is taken back (SEM: momenta to rounding), and the step counter,
+ * the history and the record are those of the failing step.
  */
 int dpde_step(dpde_handle* h, int64_t nsteps);
 

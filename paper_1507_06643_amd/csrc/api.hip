@@ -71,6 +71,7 @@ struct dpde_handle {
   int64_t n = 0;
   int64_t ncells = 0;
   int64_t step = 0;
+  bool failed = false;  // a stepping call failed since the state was set
   int pair_block = 256;
   int aux_block = 256;
   // SER sweeps with a pair inside a 128-particle tile evaluated once
@@ -821,8 +822,7 @@ void enqueue_stats_only(dpde_handle* h, int advance, int finish, bool swept = fa
          swept ? h->partials_u : h->partials, swept ? clear : (int)kClearNone,
          (const int32_t*)(swept ? h->rep_tile0_u : h->rep_tile0), (const Geo*)h->geo, h->d_step,
          advance, h->rec, h->hist, h->hist_cap, h->d_hist_count, h->nrep, finish,
-         h->stats_ticket, h->ctl, h->ctl_next, h->builds, h->half_skin2,
-         (const uint32_t*)h->status);
+         h->stats_ticket, h->ctl, h->ctl_next, h->builds, h->half_skin2, h->status);
 }
 
 // Observables of the step; with the projection (Sec. 4.2) the record of the
@@ -892,6 +892,7 @@ int load(dpde_handle* h, const double* q, const double* p, const double* eps) {
   if (!q || !p || !eps) return fail(DPDE_EINVAL, "q, p and eps must be device pointers");
   HIPCHK(hipStreamSynchronize(h->user_stream));
   HIPCHK(hipMemsetAsync(h->status, 0, sizeof(uint32_t), h->stream));
+  h->failed = false;
   launch(h, "load_state", k_load_state, blocks(h->n, 256), 256, q, p, eps, (const Geo*)h->geo,
          h->nrep, h->n, h->cur, h->status);
   uint32_t st = 0;
@@ -1078,6 +1079,38 @@ int read_status(dpde_handle* h) {
   return DPDE_OK;
 }
 
+// The end of a stepping call that enqueued `total` steps in sequences of `per`:
+// its status, the step counter, and after a failure the state and record of the
+// failing step.  Where its last pair pass also kicked (StepTail) the kick is
+// taken back, and the record, of which the pass holds part of the sums at most,
+// is taken from the state.
+int end_call(dpde_handle* h, int64_t total, int64_t per) {
+  const int rc = read_status(h);
+  // device step counter is the truth (a failing step stops the counter)
+  uint64_t st = 0;
+  HIPCHK(hipMemcpy(&st, h->d_step, sizeof(uint64_t), hipMemcpyDeviceToHost));
+  const int64_t done = (int64_t)st - h->step;  // steps completed; step `done` failed
+  h->step = (int64_t)st;
+  if (rc == DPDE_OK || rc == DPDE_EHIP) return rc;
+  const bool again = h->failed;  // had failed before: nothing ran
+  h->failed = true;
+  if (!fused_tail(h) || total == 0) return rc;
+  // every enqueued step swaps the record arrays, so the failing step's output
+  // is the present state after an even number of further ones, its input after
+  // an odd number
+  const bool kicked = done % per != per - 1;
+  if (!again && kicked && (total - 1 - done) % 2 == 0)
+    launch(h, "unkick", k_unkick, blocks(h->n, h->aux_block), h->aux_block, h->cur.r,
+           (const Rec*)h->alt.r,
+           h->phys.scheme == DPDE_SCHEME_SEM ? (const Vec4*)nullptr : (const Vec4*)h->dpi,
+           (const double*)h->Fx, (const double*)h->Fy, (const double*)h->Fz, h->n,
+           (const Geo*)h->geo, h->phys);
+  enqueue_stats_only(h, 1, 0);
+  HIPCHK(hipStreamSynchronize(h->stream));
+  HIPCHK(hipGetLastError());
+  return rc;
+}
+
 // ---- the surrogate gradient without allocation ------------------------------
 // One batch's block partials, summed gradient and loss in a fixed device
 // array instead of buffers allocated on first use.  In host code `scratch`
@@ -1154,12 +1187,7 @@ int dpde_step(dpde_handle* h, int64_t nsteps) {
   if (nsteps < 0) return fail(DPDE_EINVAL, "nsteps < 0");
   enqueue_steps(h, nsteps);
   HIPCHK(hipGetLastError());
-  int rc = read_status(h);
-  // device step counter is the truth (a failing step stops the counter)
-  uint64_t st = 0;
-  HIPCHK(hipMemcpy(&st, h->d_step, sizeof(uint64_t), hipMemcpyDeviceToHost));
-  h->step = (int64_t)st;
-  return rc;
+  return end_call(h, nsteps, nsteps);
 }
 
 int dpde_step_graph(dpde_handle* h, int64_t nsteps, int64_t reps) {
@@ -1190,11 +1218,7 @@ int dpde_step_graph(dpde_handle* h, int64_t nsteps, int64_t reps) {
     h->graph_steps = nsteps;
   }
   for (int64_t r = 0; r < reps; ++r) HIPCHK(hipGraphLaunch(h->graph_exec, h->stream));
-  int rc = read_status(h);
-  uint64_t st = 0;
-  HIPCHK(hipMemcpy(&st, h->d_step, sizeof(uint64_t), hipMemcpyDeviceToHost));
-  h->step = (int64_t)st;
-  return rc;
+  return end_call(h, nsteps * reps, nsteps);
 }
 
 int dpde_energies(dpde_handle* h, double out[DPDE_REC_LEN]) {

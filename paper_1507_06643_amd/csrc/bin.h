@@ -50,9 +50,12 @@ struct BuildCtl {
 // spread over a wave's worth of slots (a cache line each) that the end of that
 // step takes the maximum of.
 constexpr int kNextSlots = kWave;
+// What such a kick finds wrong belongs to the step it begins, so it waits here
+// until the present one is counted.
 struct alignas(128) NextMax {
   unsigned long long dmax_bits;
   unsigned long long qmax_bits;
+  uint32_t status;
 };
 
 __device__ __forceinline__ bool rebuild_now(const BuildCtl* c, double half_skin2) {
@@ -152,6 +155,11 @@ __global__ void k_store_list_length(PState s, const Geo* __restrict__ geo, int64
 
 constexpr int kAuxMaxThreads = 1024;  // largest block of the per-particle kernels
 
+// A coordinate moved by one step at momentum p.
+__device__ __forceinline__ double drifted(double q, double p, const Phys& P) {
+  return q + P.dt * p / P.mass;
+}
+
 // First half of velocity-Verlet (Sec. 3.1) on one record: p += dt/2 F and
 // q += dt p / m (kick != 0), then the periodic wrap into [0, L).  Returns in
 // d2 the square of an upper bound on the displacement since the last list
@@ -169,7 +177,7 @@ __device__ __forceinline__ void kick_record(Rec& rc, const double F[3], const Ge
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       p[d] = p[d] + P.half_dt * F[d];
-      q[d] = q[d] + P.dt * p[d] / P.mass;
+      q[d] = drifted(q[d], p[d], P);
     }
     rc.px = p[0]; rc.py = p[1]; rc.pz = p[2];
     if (!(isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]))) atomicOr(status, ST_NONFINITE);

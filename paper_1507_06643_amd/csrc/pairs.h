@@ -1033,19 +1033,19 @@ struct TailSums {
 };
 
 // The kick and drift of the record o (on its particle's own lane), and the
-// wave's maxima into one of the slots: one address for all of them made the
-// raises queue up behind each other (N = 65,536: sweep 2 23.9 us, 18.4 so).
+// wave's maxima into one of the slots, with its status: one address for all of
+// them made the raises queue up behind each other (N = 65,536: sweep 2 23.9 us,
+// 18.4 so).
 template <bool BATCH>
 __device__ __forceinline__ void tail_kick(const StepTail& tail, bool own, Rec& o,
                                           const double F[3], const Geo* __restrict__ geo,
-                                          const Phys& P, int64_t i, int64_t tile,
-                                          uint32_t* status) {
+                                          const Phys& P, int64_t i, int64_t tile) {
   double d2 = 0.0, qa = 0.0;
+  NextMax* next = tail.next + tile % kNextSlots;
   if (own) {
     const GeoRef<BATCH> g = geo[BATCH ? o.rep : 0u];
-    kick_record(o, F, g, P, 1, tail.ref, i, d2, qa, status);
+    kick_record(o, F, g, P, 1, tail.ref, i, d2, qa, &next->status);
   }
-  NextMax* next = tail.next + tile % kNextSlots;
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) d2 = fmax(d2, __shfl_xor(d2, off, kWave));
   if (threadIdx.x % kWave == 0) raise_max_bits(&next->dmax_bits, d2);
@@ -1140,7 +1140,7 @@ __attribute__((amdgpu_waves_per_eu(SCHEME == 1 && PREC == PREC_F64 && MODEL == 0
       F[2] = tail.Fz[i];
     }
     if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
-    if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+    if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile);  // uniform
     // the new 1/T_i once the record (with the old one) is written, so that
     // only e and i stay live across the EOS
     if (own) out[i] = o;
@@ -1749,7 +1749,7 @@ __attribute__((amdgpu_waves_per_eu(!REGEN && THETA ? 6 : 1, 8))) void k_pass_c(
     F[2] = tail.Fz[i];
   }
   if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
-  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile);  // uniform
   // The record (with the old 1/T_i) is written before the EOS, so that only e
   // and i stay live across it; the new 1/T_i follows.
   if (own) out[i] = o;
@@ -1976,7 +1976,7 @@ __attribute__((amdgpu_waves_per_eu(REGEN || LPP != 2 ? 1 : 6, 8))) void k_pass_c
     F[2] = tail.Fz[i];
   }
   if (tail.stats) ts.state(tail, o, e, F, P.mass, i);  // uniform
-  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile, status);  // uniform
+  if (tail.kick) tail_kick<BATCH>(tail, own, o, F, geo, P, i, tile);  // uniform
   // The record (with the old 1/T_i) is written before the EOS, so that only e
   // and i stay live across it; the new 1/T_i follows.
   if (own) out[i] = o;
@@ -2063,12 +2063,13 @@ struct StepNow {
   int64_t hist;
   unsigned long long builds;
   unsigned long long next_d, next_q;  // the next step's maxima
+  uint32_t next_status;               // and what its kick found wrong
   bool rebuilt, failed;
 };
 
 __device__ __forceinline__ void step_end(const StepNow& c, uint64_t* d_step, int64_t* d_hist_count,
                                          BuildCtl* ctl, unsigned long long* builds,
-                                         int advance) {
+                                         uint32_t* status, int advance) {
   if (c.failed) return;
   if (c.rebuilt) *builds = c.builds + 1ull;
   // the next step's maxima (nonzero when its kick ran at the end of this
@@ -2080,6 +2081,7 @@ __device__ __forceinline__ void step_end(const StepNow& c, uint64_t* d_step, int
     *d_step = c.step + 1;
     *d_hist_count = c.hist + 1;
   }
+  if (c.next_status) atomicOr(status, c.next_status);  // the next step is the one that fails
 }
 
 // Per replica: sum the tile partials, write the record (and the history
@@ -2096,12 +2098,12 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
     const Geo* __restrict__ geo, uint64_t* d_step, int advance,
     double* __restrict__ rec, double* __restrict__ hist, int64_t hist_cap,
     int64_t* d_hist_count, int nrep, int finish, uint32_t* ticket, BuildCtl* ctl,
-    NextMax* next, unsigned long long* builds, double half_skin2, const uint32_t* status) {
+    NextMax* next, unsigned long long* builds, double half_skin2, uint32_t* status) {
   const int r = blockIdx.x;
   const int t0 = rep_tile0[r], t1 = rep_tile0[r + 1];
   // the values the record and the end of the step need, requested before
   // the reduction so that their latency overlaps it
-  StepNow now{*d_step, *d_hist_count, 0ull, 0ull, 0ull, false, false};
+  StepNow now{*d_step, *d_hist_count, 0ull, 0ull, 0ull, 0u, false, false};
   if (finish) {
     now.builds = *builds;
     now.rebuilt = rebuild_now(ctl, half_skin2);
@@ -2110,12 +2112,14 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
       const NextMax v = next[threadIdx.x];
       now.next_d = v.dmax_bits;
       now.next_q = v.qmax_bits;
+      now.next_status = v.status;
 #pragma unroll
       for (int off = kWave / 2; off > 0; off >>= 1) {
         const unsigned long long d = __shfl_xor(now.next_d, off, kWave);
         const unsigned long long q = __shfl_xor(now.next_q, off, kWave);
         now.next_d = d > now.next_d ? d : now.next_d;
         now.next_q = q > now.next_q ? q : now.next_q;
+        now.next_status |= (uint32_t)__shfl_xor((int)now.next_status, off, kWave);
       }
     }
   }
@@ -2180,7 +2184,7 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
       if (gridDim.x > 1u) __threadfence();
       if (gridDim.x == 1u || atomicAdd(ticket, 1u) == gridDim.x - 1u) {
         if (gridDim.x > 1u) __threadfence();
-        step_end(now, d_step, d_hist_count, ctl, builds, advance);
+        step_end(now, d_step, d_hist_count, ctl, builds, status, advance);
         atomicExch(ticket, 0u);
         ends = 1u;
       }
@@ -2191,6 +2195,7 @@ __global__ __launch_bounds__(kStatFinalThreads) void k_stats_final(
   if (ends && threadIdx.x < kNextSlots) {  // the slots are left cleared
     next[threadIdx.x].dmax_bits = 0ull;
     next[threadIdx.x].qmax_bits = 0ull;
+    next[threadIdx.x].status = 0u;
   }
 }
 
@@ -2246,6 +2251,41 @@ __global__ void k_project(PState s, int64_t n, const Geo* __restrict__ geo, Phys
   } else {
     sums(live, 0u);
   }
+}
+
+// After a call whose failing step's last pair pass kicked the records it wrote
+// (to `out`, from `src`): the state goes back to that step.  A record that the
+// pass wrote is where its own momentum takes it from the step's position; it
+// gets that position and the momentum before the kick again (p + dp_i of the
+// sweeps; SEM, which keeps no dp_i: by the kick backwards, to rounding).  The
+// pass leaves out the particles of blocks that already met the raised status:
+// they keep the record it read.
+__global__ void k_unkick(Rec* out, const Rec* __restrict__ src, const Vec4* __restrict__ dpi,
+                         const double* __restrict__ Fx, const double* __restrict__ Fy,
+                         const double* __restrict__ Fz, int64_t n, const Geo* __restrict__ geo,
+                         Phys P) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const Rec o = out[i];
+  Rec a = src[i];
+  const Geo& g = geo[a.rep];
+  double q[3] = {drifted(a.qx, o.px, P), drifted(a.qy, o.py, P), drifted(a.qz, o.pz, P)};
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    if (g.periodic[d]) q[d] = wrap_coord(q[d], g.box[d]);
+  if (o.id == a.id && o.rep == a.rep && o.qx == q[0] && o.qy == q[1] && o.qz == q[2]) {
+    if (dpi) {
+      a.px = a.px + dpi[i].x;
+      a.py = a.py + dpi[i].y;
+      a.pz = a.pz + dpi[i].z;
+    } else {
+      a.px = o.px - P.half_dt * Fx[i];
+      a.py = o.py - P.half_dt * Fy[i];
+      a.pz = o.pz - P.half_dt * Fz[i];
+    }
+    a.invT = o.invT;
+  }
+  out[i] = a;
 }
 
 // Target energy of the projection: the energy in the current record.

@@ -84,3 +84,81 @@ def test_capacity_below_the_staged_rows(dp, n):
     assert S.step(1)[0] == 0
     assert np.abs(runs[1][1] - S.p).max() < TOL
     assert np.abs(runs[1][2] - S.eps).max() < TOL * np.abs(S.eps).mean()
+
+
+def _failing(dp, form):
+    """A system whose strong friction drives an internal energy below zero
+    after one to four steps (as the CPU oracle finds for these heat capacities)."""
+    n = 2000
+    L = W.cubic_side(n)
+    cv = {"sem": 4.6, "sem_projected": 7.0, "hybrid": 8.0}.get(form, 20.0)
+    q, p, e = W.equilibrium_state(n, [L] * 3, seed=71, eps0=cv)
+    kw = dict(n=n, box=[L] * 3, cv=cv, gamma=20.0, dt=0.02)
+    kw.update({"tile": {}, "both_sides": {}, "sem": dict(scheme=dp.SCHEME_SEM),
+               "sem_projected": dict(scheme=dp.SCHEME_SEM, project=True),
+               "hybrid": dict(scheme=dp.SCHEME_HYBRID, ndom=(2, 2, 2)),
+               "projected": dict(project=True)}[form])
+    s = dp.System(dp.Config(**kw), q, p, e)
+    if form == "both_sides":
+        s.set_shape(pairs=dp.PAIRS_BOTH_SIDES)
+    return s, kw
+
+
+@pytest.mark.parametrize("form", ["tile", "both_sides", "sem", "sem_projected", "hybrid",
+                                  "projected"])
+@pytest.mark.parametrize("how", ["even", "odd", "graph"])
+def test_failed_call_leaves_the_failing_step(dp, form, how):
+    """After a call that fails in step k, positions are those of step k (the
+    kick and drift from the state after k steps) whether an even or odd number
+    of steps were still to come, and the record and the counter belong to that
+    state."""
+    s, kw = _failing(dp, form)
+    for k in range(20):  # single steps up to the failure
+        before, F = _state(s), s.forces()[0].cpu().numpy()
+        if s.step_raw(1):
+            break
+    assert 1 <= k < 19
+    s.close()
+    s, _ = _failing(dp, form)
+    if how == "graph":
+        with pytest.raises(dp.DpdeError) as ex:
+            s.step_graph(k + 2 + k % 2, 2)
+        assert ex.value.code == dp._lib.DPDE_ENEG_EINT
+    else:
+        assert s.step_raw(k + (3 if how == "even" else 2)) == dp._lib.DPDE_ENEG_EINT
+    q, p, e, step = _state(s)
+    assert step == k and len(s.history()) == k
+    L = kw["box"][0]
+    want = before[0] + kw["dt"] * (before[1] + 0.5 * kw["dt"] * F)
+    d = q - want
+    assert np.abs(d - L * np.rint(d / L)).max() < TOL * L
+    rec = s.energies()
+    assert rec[1] == pytest.approx(0.5 * (p ** 2).sum(), rel=1e-12)
+    assert rec[2] == pytest.approx(e.sum(), rel=1e-12)
+    s.close()
+
+
+@pytest.mark.parametrize("form", ["tile", "both_sides", "sem", "hybrid"])
+def test_a_kick_that_overflows_fails_its_own_step(dp, form):
+    """A particle flying off at 1e308 per step leaves the range of FP64 in the
+    kick of the second step: one call of five steps completes the first one,
+    records it and fails in the second, as single steps do."""
+    n, box = 40, [20.0] * 3
+    q, p, e = W.equilibrium_state(n, box, seed=5)
+    p[7, 0] = 1e308
+    kw = dict(n=n, box=box, periodic=[0, 0, 0], a=0.0, gamma=0.0, dt=1.0)
+    kw.update({"sem": dict(scheme=dp.SCHEME_SEM),
+               "hybrid": dict(scheme=dp.SCHEME_HYBRID, ndom=(2, 2, 2))}.get(form, {}))
+    runs = []
+    for calls in ([1, 1], [5]):
+        s = dp.System(dp.Config(**kw), q, p, e)
+        if form == "both_sides":
+            s.set_shape(pairs=dp.PAIRS_BOTH_SIDES)
+        for c in calls[:-1]:
+            s.step(c)
+        assert s.step_raw(calls[-1]) == dp._lib.DPDE_ENONFINITE
+        runs.append((_state(s)[3], s.history()))
+        s.close()
+    assert runs[0][0] == runs[1][0] == 1
+    assert runs[0][1].shape == runs[1][1].shape == (1, 12)
+    assert np.array_equal(runs[0][1], runs[1][1], equal_nan=True)

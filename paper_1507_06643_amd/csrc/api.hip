@@ -398,8 +398,7 @@ int allocate(dpde_handle* h) {
     return rc;
   if ((rc = dalloc(h, &h->key, n)) || (rc = dalloc(h, &h->bins.link, n)) || (rc = dalloc(h, &h->bin_ticket, 1)))
     return rc;
-  // (the histogram's last words may be read four at a time)
-  if ((rc = dalloc(h, &h->bins.count, h->ncells + 3)) ||
+  if ((rc = dalloc(h, &h->bins.count, h->ncells)) ||
       (rc = dalloc(h, &h->bins.first, h->ncells)) ||
       (rc = dalloc(h, &h->bins.start, h->ncells + 1)))
     return rc;
@@ -497,7 +496,7 @@ int allocate(dpde_handle* h) {
   if ((rc = dalloc(h, &h->geo, h->nrep))) return rc;
   HIPCHK(hipMemcpy(h->geo, h->geo_h.data(), h->nrep * sizeof(Geo), hipMemcpyHostToDevice));
   HIPCHK(hipMemset(h->status, 0, 4 * sizeof(uint32_t)));
-  HIPCHK(hipMemset(h->bins.count, 0, (h->ncells + 3) * sizeof(uint32_t)));
+  HIPCHK(hipMemset(h->bins.count, 0, h->ncells * sizeof(uint32_t)));
   HIPCHK(hipMemset(h->bins.first, 0xFF, h->ncells * sizeof(uint32_t)));
   HIPCHK(hipMemset(h->bin_ticket, 0, sizeof(uint32_t)));
   HIPCHK(hipMemset(h->d_hist_count, 0, sizeof(int64_t)));

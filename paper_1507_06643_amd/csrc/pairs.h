@@ -264,19 +264,19 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   __shared__ uint32_t run_s, stop_s;
   if (threadIdx.x == 0) {
     run_s = rebuild_now(ctl, half_skin2);
-    stop_s = status_set(status);
+    stop_s = *status;
     next_s = 0;
     most_s = 0u;
   }
   __syncthreads();
-  if (!run_s) return;  // uniform in the block
-  // the histogram and the chains cleared for the next build (start stays),
-  // also where another block has raised the status
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells.ncells;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    cells.count[c] = 0u;
-    cells.first[c] = kChainEnd;
-  }
+  // a status from before the binning kept that from running too
+  if (!run_s || (stop_s & ~ST_OVERFLOW)) return;  // uniform in the block
+  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
+  const int np = (int)(n - tb < kUniqTile ? n - tb : kUniqTile);
+  const int t = threadIdx.x;
+  // the histogram and the chains cleared (start stays), also where another
+  // block has found an overflow
+  if (t < kUniqTile) clear_cell(cells, tb + t, t < np);
   if (stop_s) return;  // uniform in the block
   uint32_t* lst = dyn;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -284,12 +284,9 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   uint8_t* src_cell = reinterpret_cast<uint8_t*>(dyn + rows * kUniqTile +
                                                  (blockDim.x / kWave) * kBuildWindow) +
                       w * kBuildWindow;
-  const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
-  const int np = (int)(n - tb < kUniqTile ? n - tb : kUniqTile);
   const Rec* __restrict__ R = s.r + tb;
   // the tile's cells: a piece starts where the cell changes, and every kPiece
   // particles inside one
-  const int t = threadIdx.x;
   if (t < kUniqTile) {
     uint32_t c = 0xFFFFFFFFu;
     if (t < np) {

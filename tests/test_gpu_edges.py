@@ -162,3 +162,59 @@ def test_a_kick_that_overflows_fails_its_own_step(dp, form):
     assert runs[0][0] == runs[1][0] == 1
     assert runs[0][1].shape == runs[1][1].shape == (1, 12)
     assert np.array_equal(runs[0][1], runs[1][1], equal_nan=True)
+
+
+def _kernel_us(s, steps):
+    """Mean time of every kernel over some single steps."""
+    s.step(2)
+    s.profile(True)
+    s.profile_read()
+    for _ in range(steps):
+        s.step(1)
+    out = {k: 1e3 * ms / count for k, (ms, count) in s.profile_read().items()}
+    s.profile(False)
+    return out
+
+
+def test_list_build_of_a_sparse_box_depends_on_its_particles(dp):
+    """7 million cells, a build on every step: a hundred particles are listed
+    no slower than twenty thousand (both take a few microseconds; clearing the
+    cells by the few blocks of the hundred took 560), and the pairs stay those
+    of the oracle."""
+    us = {}
+    box = [200.0] * 3
+    for n in (100, 20000):
+        q, p, e = W.equilibrium_state(n, box, seed=n)
+        if n == 100:
+            q = np.mod(q * 0.02 + 199.0, 200.0)  # close together, across the corner
+        s = dp.System(dp.Config(n=n, box=box, dt=0.01, skin=0.05), q, p, e)
+        us[n] = _kernel_us(s, 5)["build_skin"]
+        s.step(5)
+        assert s.list_builds() > 5
+        s.set_state(*s.get_state())
+        qs = _state(s)[0]
+        assert np.array_equal(s.debug_pairs(), O.pairs(O.make_params(n, box), qs, "cells"))
+        s.close()
+    assert us[100] < 2.0 * us[20000], us
+
+
+@pytest.mark.parametrize("n", [1500, 9000, 40000])
+def test_an_overflow_leaves_the_binning_clear(dp, n):
+    """A state whose lists overflow is refused; the next one is binned as on a
+    fresh handle (n in one block, with the scan in the last block, and with a
+    scan of its own)."""
+    L = W.cubic_side(n)
+    q, p, e = W.equilibrium_state(n, [L] * 3, seed=n)
+    s = dp.System(dp.Config(n=n, box=[L] * 3, dt=0.01), q, p, e)
+    for crowd in (q * 0.3, q * 0.15 + 0.7 * L):
+        with pytest.raises(dp.DpdeError) as ex:
+            s.set_state(crowd, p, e, 0)
+        assert ex.value.code == dp._lib.DPDE_EOVERFLOW
+    s.set_state(q, p, e, 0)
+    ref = dp.System(dp.Config(n=n, box=[L] * 3, dt=0.01), q, p, e)
+    for x in (s, ref):
+        x.step(6)
+    assert _same(_state(s), _state(ref))
+    assert np.array_equal(s.debug_order().cpu().numpy(), ref.debug_order().cpu().numpy())
+    s.close()
+    ref.close()

@@ -571,6 +571,19 @@ BinPlan bin_plan(const dpde_handle* h) {
   return {blocks(h->n, b), b, scan, 0};
 }
 
+// Where cells hold few particles on average, four lanes per particle list faster
+// than a wave per piece of a cell (k_build_lanes, k_build_skin).  Measured, us
+// per build, lanes / pieces, with m particles to a cell (SER; the both-sides
+// lists cross at the same places):
+//   N =    16,000  m = 1.0 16.8 / 20.3   1.5  19.1 /  18.8   2.3  21.5 /  17.9
+//   N =    65,536  m = 2.2 25.3 / 30.7   3.3  29.9 /  29.7   4.2  32.6 /  29.4
+//   N =   262,144  m = 2.1 62.2 / 87.9   3.5  77.0 /  83.7   4.1  82.1 /  80.4
+//   N = 1,000,000  m = 0.7  143 / 342    2.0   194 /   248   3.0   230 /   237
+//                  3.6  252 /  227
+bool few_per_cell(const dpde_handle* h) {
+  return 2 * h->n < (h->n <= 32768 ? 3 : 7) * h->ncells;
+}
+
 // Kick and drift (unless the end of the previous step did them: with_kick
 // false); on list-build steps (decided on the device) the binning, the
 // reorder and the skin lists.  Buffer roles are the same either way.
@@ -611,19 +624,39 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   // piece or two (N = 65,536, 512 threads: 41 -> 29 us).
   const int rows = std::min((int)h->skin.cap, uniq ? 32 : h->phys.cap > 96 ? 80 : 36);
   const unsigned tiles = blocks(n, kUniqTile);
+  const int tile = tile_shape(h).tile;
+  const bool narrow = tile < kUniqTile;
   const int threads = tiles >= 2048 ? 256 : (tiles >= 512 || rows > 48) ? 512 : 1024;
   auto build = [&](auto kern) {
     launch_lds(h, "build_skin", kern, tiles, threads, build_lds(rows, threads), h->alt, h->cur,
                (const QIdF*)h->qid, (const uint32_t*)h->bins.start, n, (const Geo*)h->geo,
-               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile_shape(h).tile,
+               std::sqrt(h->rs2), h->box_max, h->skin, ctl, hs2, rows, tile,
                (uint32_t)h->phys.cap, h->bins, h->status);
   };
-  if (h->batch) {
-    if (uniq) build(k_build_skin<true, true>);
-    else build(k_build_skin<true, false>);
+  if (few_per_cell(h)) {
+    const int pb = h->pair_block;
+    auto lanes = [&](auto kern) {
+      launch(h, "build_skin", kern, blocks(n * kSub, pb), pb, h->alt, h->cur, (const QIdF*)h->qid,
+             (const uint32_t*)h->bins.start, n, (const Geo*)h->geo, std::sqrt(h->rs2), h->box_max,
+             h->skin, ctl, hs2, tile, (uint32_t)h->phys.cap, h->bins, h->status);
+    };
+    if (h->batch) {
+      if (!uniq) lanes(k_build_lanes<true, false, false>);
+      else if (narrow) lanes(k_build_lanes<true, true, true>);
+      else lanes(k_build_lanes<true, true, false>);
+    } else {
+      if (!uniq) lanes(k_build_lanes<false, false, false>);
+      else if (narrow) lanes(k_build_lanes<false, true, true>);
+      else lanes(k_build_lanes<false, true, false>);
+    }
+  } else if (h->batch) {
+    if (!uniq) build(k_build_skin<true, false, false>);
+    else if (narrow) build(k_build_skin<true, true, true>);
+    else build(k_build_skin<true, true, false>);
   } else {
-    if (uniq) build(k_build_skin<false, true>);
-    else build(k_build_skin<false, false>);
+    if (!uniq) build(k_build_skin<false, false, false>);
+    else if (narrow) build(k_build_skin<false, true, true>);
+    else build(k_build_skin<false, true, false>);
   }
   // the tile form adds every pair term in fixed point: its lists need no order
   if (!uniq)

@@ -420,19 +420,6 @@ struct CellBins {
 };
 constexpr uint32_t kChainEnd = 0xFFFFFFFFu;
 
-// The histogram entry and the chain head of particle i's cell cleared for the
-// next build, once per run of equal cells in a wave (every lane of the wave
-// calls).  By particle, not by cell: a sparse box has many more cells, and the
-// few blocks of its list build took 560 us to clear 6.9M of them (100 particles).
-__device__ __forceinline__ void clear_cell(const CellBins& cb, int64_t i, bool live) {
-  const uint32_t c = live ? cb.key[i] : 0xFFFFFFFFu;
-  const uint32_t prev = __shfl_up(c, 1, kWave);
-  if (live && (threadIdx.x % kWave == 0 || prev != c)) {
-    cb.count[c] = 0u;
-    cb.first[c] = kChainEnd;
-  }
-}
-
 // Digit 2 and the move into the new order: particle i counts the smaller
 // identifiers of its cell's chain, which is its place in the cell, and its
 // record and internal energy go there in the spare buffer, with the build-time

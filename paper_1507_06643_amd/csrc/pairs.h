@@ -203,6 +203,18 @@ struct SkinList {
   int64_t cap;    // capacity per particle
 };
 
+// Square of the FP32 test radius: rs plus a bound on the rounding of the FP32
+// distance (conversions of coordinates up to Q = max(|q|, box), their
+// difference, the minimum image and the squared sum stay below
+// 8 2^-24 (Q + rs); twice that is added), rounded up.
+__device__ __forceinline__ float build_radius2(const BuildCtl* ctl, double rs, double box_max) {
+  const double Q = fmax(__longlong_as_double((long long)ctl->qmax_bits), box_max);
+  const double thr = rs + 16.0 * 0x1p-24 * (Q + rs);
+  float thr2 = (float)(thr * thr);
+  if ((double)thr2 < thr * thr) thr2 = nextafterf(thr2, INFINITY);
+  return thr2;
+}
+
 // The build's block serves a tile of 128 consecutive particles.  Particles of
 // one cell share their 27-cell stencil, so the unit of work is a piece: up to
 // kPiece particles of the tile in one cell, taken by one wave.  The wave lists
@@ -227,7 +239,7 @@ struct SkinList {
 // overflow.  Tiles below 128 list more of the pairs on both sides (at most
 // (128 - tile) / 2 per particle, for which the lists have room: sl.cap), so
 // what counts there is the list that tiles of 128 would hold: whether a system
-// fits does not depend on the tile.
+// fits does not depend on the tile (NARROW: tile < 128).
 // A run reached across a periodic face holds images one box length away: its
 // candidates are compared after that shift (d - s with s = +-L), which for
 // every candidate within the list radius is the minimum image itself, with
@@ -247,7 +259,7 @@ inline size_t build_lds(int rows, int threads) {
          (size_t)(threads / kWave) * kBuildWindow * (sizeof(uint32_t) + sizeof(uint8_t));
 }
 
-template <bool BATCH, bool UNIQ>
+template <bool BATCH, bool UNIQ, bool NARROW>
 __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
     int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
@@ -274,10 +286,6 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kUniqTile;
   const int np = (int)(n - tb < kUniqTile ? n - tb : kUniqTile);
   const int t = threadIdx.x;
-  // the histogram and the chains cleared (start stays), also where another
-  // block has found an overflow
-  if (t < kUniqTile) clear_cell(cells, tb + t, t < np);
-  if (stop_s) return;  // uniform in the block
   uint32_t* lst = dyn;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   uint32_t* src = dyn + rows * kUniqTile + w * kBuildWindow;  // the window's candidates
@@ -302,11 +310,22 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     cell_s[t] = c;
   }
   // records back to the working buffer, 16 bytes per thread and turn
-  for (int c = t; c < 4 * np; c += blockDim.x)
-    reinterpret_cast<uint4*>(work.r + tb)[c] = reinterpret_cast<const uint4*>(R)[c];
-  for (int c = t; c < np; c += blockDim.x) work.eps[tb + c] = s.eps[tb + c];
+  if (!stop_s) {
+    for (int c = t; c < 4 * np; c += blockDim.x)
+      reinterpret_cast<uint4*>(work.r + tb)[c] = reinterpret_cast<const uint4*>(R)[c];
+    for (int c = t; c < np; c += blockDim.x) work.eps[tb + c] = s.eps[tb + c];
+  }
   __syncthreads();
   const bool head = t < np && (t == 0 || cell_s[t] != cell_s[t - 1]);
+  // the cells' histogram entries and chains cleared for the next build (start
+  // stays), also where another block has found an overflow; by the tile's own
+  // cells, since a sparse box has many more (the few blocks of 100 particles
+  // took 560 us to clear its 6.9M)
+  if (head) {
+    cells.count[cell_s[t]] = 0u;
+    cells.first[cell_s[t]] = kChainEnd;
+  }
+  if (stop_s) return;  // uniform in the block
   const unsigned long long heads = __ballot(head);
   if (w < 2 && lane == 0) head_s[w] = heads;
   __syncthreads();
@@ -327,14 +346,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
   }
   if (t == 0) first_s[npieces] = np;
   __syncthreads();
-  // FP32 test radius: rs plus a bound on the rounding of the FP32 distance
-  // (conversions of coordinates up to Q = max(|q|, box), their difference,
-  // the minimum image and the squared sum stay below 8 2^-24 (Q + rs); twice
-  // that is added), rounded up
-  const double Q = fmax(__longlong_as_double((long long)ctl->qmax_bits), box_max);
-  const double thr = rs + 16.0 * 0x1p-24 * (Q + rs);
-  float thr2 = (float)(thr * thr);
-  if ((double)thr2 < thr * thr) thr2 = nextafterf(thr2, INFINITY);
+  const float thr2 = build_radius2(ctl, rs, box_max);
   const uint32_t cap = (uint32_t)sl.cap;
   for (;;) {
     int pc = 0;
@@ -422,7 +434,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
         const float yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.y), q));
         const float zi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.z), q));
         uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)counts, q);
-        uint32_t base_wide = (uint32_t)__builtin_amdgcn_readlane((int)wide, q);
+        uint32_t base_wide = NARROW ? (uint32_t)__builtin_amdgcn_readlane((int)wide, q) : 0u;
         const uint32_t tq = (uint32_t)(p0 + q);
 #pragma unroll
         for (int c = 0; c < kBuildChunks; ++c) {
@@ -441,7 +453,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
             const unsigned long long below = __ballot(rel[c] < tq), above = __ballot(rel[c] > tq);
             const unsigned long long same = (tq & 1u) ? odd[c] : ~odd[c];
             const unsigned long long mine = (same & below) | (~same & above);
-            if (tile < kUniqTile)  // uniform
+            if constexpr (NARROW)
               base_wide += (uint32_t)__popcll(m & (__ballot(rel[c] >= (uint32_t)kUniqTile) | mine));
             m &= out | mine;
           } else {
@@ -459,7 +471,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
           }
         }
         counts = lane == q ? base : counts;
-        wide = lane == q ? base_wide : wide;
+        if constexpr (NARROW) wide = lane == q ? base_wide : wide;
       };
       if (images) {
         for (int q = 0; q < p1 - p0; ++q) test(q, std::true_type{});
@@ -469,7 +481,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
       __builtin_amdgcn_wave_barrier();  // the next window overwrites src
     }
     if (lane < p1 - p0) {
-      if ((UNIQ && tile < kUniqTile ? wide : counts) > limit) atomicOr(status, ST_OVERFLOW);
+      if ((NARROW ? wide : counts) > limit) atomicOr(status, ST_OVERFLOW);
       counts = counts < cap ? counts : cap;
       count_s[p0 + lane] = counts;
       atomicMax(&most_s, counts);
@@ -482,6 +494,238 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     if ((int)p < np && k < count_s[p]) sl.idx[list_entry(tb + p, k, sl.cap)] = lst[c];
   }
   if (t < np) sl.count[tb + t] = count_s[t];
+}
+
+// ---- the same lists where cells hold few particles ----------------------------
+// With one or two particles to a cell a piece leaves most of its wave idle in the
+// candidate tests and every particle pays for a stencil by itself.  There four
+// lanes per particle walk the stencil each for their own particle (the rule
+// stands at the launch).
+// Up to two contiguous cell ranges along x for the stencil row (y, z).
+struct Row {
+  int a0, b0, a1, b1;  // inclusive cell x-ranges; a1 > b1 means "no second range"
+};
+
+__device__ __forceinline__ Row stencil_row(int cx, int nc, int periodic) {
+  Row r;
+  r.a1 = 1;
+  r.b1 = 0;
+  if (periodic) {
+    if (cx == 0) { r.a0 = 0; r.b0 = 1; r.a1 = nc - 1; r.b1 = nc - 1; }
+    else if (cx == nc - 1) { r.a0 = nc - 2; r.b0 = nc - 1; r.a1 = 0; r.b1 = 0; }
+    else { r.a0 = cx - 1; r.b0 = cx + 1; }
+  } else {
+    r.a0 = cx > 0 ? cx - 1 : 0;
+    r.b0 = cx < nc - 1 ? cx + 1 : nc - 1;
+  }
+  return r;
+}
+
+// Visit the 27-cell stencil.  Its cells come as runs of consecutive memory
+// (three cells of an x-row in row-major order; one run per cell block an
+// x-row crosses in blocked order; a periodic wrap splits a row), which the
+// group first lists in LDS (`runs`: the runs' first indices, then their
+// cumulative ends with the run's periodic image in the top bits); the
+// group's lanes then take the concatenated candidates four at a time (lane
+// sub takes position F + sub), so a trip is cut short only at the end of the
+// stencil, not at the end of every run.  A run reached across a periodic face
+// holds images one box length away: its candidates are compared after that
+// shift (d - s with s = +-L), which for every candidate within the list
+// radius is the minimum image itself, with the same two roundings.
+// `sink(take, j, id_j)` is called on every trip, `take` being r^2 < thr2 and
+// j != i; the trips are uniform across the group, so `sink` may ballot.
+constexpr int kRunsMax = 28;  // runs per stencil: 9 rows x at most 3 pieces
+constexpr int kRunEndBits = 26;  // cumulative end; above it 2 bits per axis: 1 = +L, 2 = -L
+
+template <bool MI, typename Sink>
+__device__ __forceinline__ bool scan_candidates(const Lanes& L, const Geo& g,
+                                                const uint32_t* __restrict__ start,
+                                                const QIdF* __restrict__ qid, float xi, float yi,
+                                                float zi, int cx, int cy, int cz, float thr2,
+                                                uint32_t* runs, Sink&& sink) {
+  const float bx = (float)g.box[0], by = (float)g.box[1], bz = (float)g.box[2];
+  // the runs, in stencil order (uniform across the group; lane 0 records)
+  uint32_t nr = 0, tot = 0;
+  bool whole = true;  // false: the stencil holds more candidates than the run ends can count
+  constexpr uint32_t kEndMask = (1u << kRunEndBits) - 1u;
+  auto add = [&](uint32_t jb, uint32_t je, uint32_t image) {
+    if (je > jb && je - jb > kEndMask - tot) whole = false;
+    if (je > jb && whole) {
+      tot += je - jb;
+      if (L.sub == 0) {
+        runs[nr] = jb;
+        runs[kRunsMax + nr] = tot | (image << kRunEndBits);
+      }
+      ++nr;
+    }
+  };
+  // the image code of a neighbour cell index before wrapping: +L from above,
+  // -L from below (2 bits)
+  auto code = [](int c, int nc) -> uint32_t { return c >= nc ? 1u : (c < 0 ? 2u : 0u); };
+  const Row row = stencil_row(cx, g.nc[0], g.periodic[0]);
+  const int B = g.oblk;
+  // the x image of the second range of a periodic row: the cell left of
+  // cx = 0 or right of cx = nc - 1
+  const uint32_t cx1 = cx == 0 ? 2u : 1u;
+  for (int dz = -1; dz <= 1; ++dz) {
+    int z = cz + dz;
+    const uint32_t iz = code(z, g.nc[2]) << 4;
+    if (!wrap_cell(z, g.nc[2], g.periodic[2])) continue;
+    for (int dy = -1; dy <= 1; ++dy) {
+      int y = cy + dy;
+      const uint32_t iyz = iz | (code(y, g.nc[1]) << 2);
+      if (!wrap_cell(y, g.nc[1], g.periodic[1])) continue;
+      if (B == 1) {  // row-major cells: each x range is one run of memory
+        const int64_t base = g.cell_base + (int64_t)g.nc[0] * (y + (int64_t)g.nc[1] * z);
+        add(start[base + row.a0], start[base + row.b0 + 1], iyz);
+        if (row.a1 <= row.b1) add(start[base + row.a1], start[base + row.b1 + 1], iyz | cx1);
+      } else {
+        // blocked order: an x range is one run per cell block it crosses
+        auto xrun = [&](int a, int b, uint32_t image) {
+          for (int x = a; x <= b;) {
+            const int e = min(b, block_of(x, g) * B + B - 1);
+            const int64_t k0 = g.cell_base + cell_key(g, x, y, z);
+            add(start[k0], start[k0 + (e - x) + 1], image);
+            x = e + 1;
+          }
+        };
+        xrun(row.a0, row.b0, iyz);
+        if (row.a1 <= row.b1) xrun(row.a1, row.b1, iyz | cx1);
+      }
+    }
+  }
+  // the group's lanes read what lane 0 wrote (one wave: a fence suffices)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  auto shift = [](uint32_t c2, float l) { return c2 == 1u ? l : (c2 == 2u ? -l : 0.0f); };
+  // lane-local cursor: run r covers concatenated positions [prev, end) and
+  // holds images shifted by (sx, sy, sz)
+  uint32_t r = 0, prev = 0, word = nr ? runs[kRunsMax] : 0u;
+  uint32_t end = word & kEndMask;
+  float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+  auto image = [&]() {
+    if constexpr (MI) {
+      const uint32_t c = word >> kRunEndBits;
+      sx = shift(c & 3u, bx);
+      sy = shift((c >> 2) & 3u, by);
+      sz = shift(c >> 4, bz);
+    }
+  };
+  image();
+  for (uint32_t F = 0; F < tot; F += kSub) {
+    const uint32_t f = F + L.sub;
+    bool take = false;
+    uint32_t j = 0, idj = 0;
+    if (f < tot) {
+      if (f >= end) {
+        do {
+          prev = end;
+          ++r;
+          word = runs[kRunsMax + r];
+          end = word & kEndMask;
+        } while (f >= end);
+        image();
+      }
+      j = runs[r] + (f - prev);
+      const QIdF c = qid[j];
+      float dx = xi - c.x, dy = yi - c.y, dz = zi - c.z;
+      if constexpr (MI) {
+        dx -= sx;
+        dy -= sy;
+        dz -= sz;
+      }
+      idj = c.id;
+      take = (dx * dx + dy * dy) + dz * dz < thr2 && j != (uint32_t)L.i;
+    }
+    sink(take, j, idj);
+  }
+  return whole;
+}
+
+__device__ __forceinline__ bool interior_dim(int c, int nc, int periodic) {
+  // cells c-1..c+1 exist without wrapping
+  return !periodic || (c >= 1 && c <= nc - 2);
+}
+
+// Lists, limit and the records returned as in k_build_skin.
+constexpr int kBuildLds = 32;  // list entries per particle staged in LDS
+
+template <bool BATCH, bool UNIQ, bool NARROW>
+__global__ __launch_bounds__(kPairBlockMax) void k_build_lanes(
+    PState s, PState work, const QIdF* __restrict__ qid, const uint32_t* __restrict__ start,
+    int64_t n, const Geo* __restrict__ geo, double rs, double box_max, SkinList sl,
+    const BuildCtl* ctl, double half_skin2, int tile, uint32_t limit, CellBins cells,
+    uint32_t* status) {
+  __shared__ uint32_t lst[kBuildLds * (kPairBlockMax / kSub)];
+  __shared__ uint32_t runs_s[2 * kRunsMax * (kPairBlockMax / kSub)];
+  const uint32_t st = *status;  // another block may find an overflow: uniform in the wave only
+  if (!rebuild_now(ctl, half_skin2) || (st & ~ST_OVERFLOW)) return;
+  const Lanes L = lanes();
+  if (L.i >= n) return;  // uniform in the group
+  uint32_t* runs = runs_s + 2 * kRunsMax * L.pib;
+  const int64_t i = L.i;
+  const Rec* __restrict__ R = s.r;
+  const Geo& g = geo[BATCH ? R[i].rep : 0u];
+  const int cx = cell_coord(R[i].qx, g.scale[0], g.nc[0]);
+  const int cy = cell_coord(R[i].qy, g.scale[1], g.nc[1]);
+  const int cz = cell_coord(R[i].qz, g.scale[2], g.nc[2]);
+  if (L.sub == 0) {  // the cell cleared, as in k_build_skin
+    const int64_t c = g.cell_base + cell_key(g, cx, cy, cz);
+    cells.count[c] = 0u;
+    cells.first[c] = kChainEnd;
+  }
+  if (st) return;
+  if (L.sub == 0) {
+    work.r[i] = R[i];
+    work.eps[i] = s.eps[i];
+  }
+  const float thr2 = build_radius2(ctl, rs, box_max);
+  const QIdF own = qid[i];
+  uint32_t nn = 0;
+  uint32_t wide = 0;  // this lane's entries that tiles of 128 would list too
+  const uint32_t cap = (uint32_t)sl.cap;
+  const uint32_t first = (uint32_t)g.first;
+  auto sink = [&](bool take, uint32_t j, uint32_t idj) {
+    if constexpr (UNIQ) {
+      const uint32_t x = (uint32_t)i ^ j;
+      const bool mine = (x & 1u) ? (uint32_t)i < j : (uint32_t)i > j;
+      if constexpr (NARROW) wide += take && (x >= (uint32_t)kUniqTile || mine) ? 1u : 0u;
+      take = take && (x >= (uint32_t)tile || mine);
+    }
+    const uint32_t bits = group_ballot(L, take);
+    if (take) {
+      const uint32_t pos = nn + __popc(bits & ((1u << L.sub) - 1u));
+      const uint32_t row = UNIQ ? j : first + idj;
+      if (pos < (uint32_t)kBuildLds) lst[pos * L.ppb + L.pib] = row;
+      else if (pos < cap) sl.idx[list_entry(i, pos, sl.cap)] = row;
+    }
+    nn += __popc(bits);
+  };
+  // waves whose particles all sit away from the periodic faces meet no
+  // image across them
+  const bool interior = interior_dim(cx, g.nc[0], g.periodic[0]) &&
+                        interior_dim(cy, g.nc[1], g.periodic[1]) &&
+                        interior_dim(cz, g.nc[2], g.periodic[2]);
+  const bool whole =
+      __all(interior)
+          ? scan_candidates<false>(L, g, start, qid, own.x, own.y, own.z, cx, cy, cz, thr2, runs,
+                                   sink)
+          : scan_candidates<true>(L, g, start, qid, own.x, own.y, own.z, cx, cy, cz, thr2, runs,
+                                  sink);
+  if constexpr (NARROW) {
+#pragma unroll
+    for (int off = 1; off < kSub; off <<= 1) wide += (uint32_t)__shfl_xor((int)wide, off, kWave);
+  }
+  // a stencil too full to count is a list overflow
+  if (!whole || (NARROW ? wide : nn) > limit) {
+    if (L.sub == 0) atomicOr(status, ST_OVERFLOW);
+  }
+  nn = nn < cap ? nn : cap;
+  const uint32_t staged = nn < (uint32_t)kBuildLds ? nn : (uint32_t)kBuildLds;
+  for (uint32_t k = L.sub; k < staged; k += kSub)
+    sl.idx[list_entry(i, k, sl.cap)] = lst[k * L.ppb + L.pib];
+  if (L.sub == 0) sl.count[i] = nn;
 }
 
 // Sort each skin list by neighbour identifier and replace the identifier

@@ -218,3 +218,67 @@ def test_an_overflow_leaves_the_binning_clear(dp, n):
     assert np.array_equal(s.debug_order().cpu().numpy(), ref.debug_order().cpu().numpy())
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("pairs", [0, 1])
+@pytest.mark.parametrize("n,density", [(61, 0.5), (700, 0.6), (700, 0.8), (16384, 0.65),
+                                       (16385, 0.75), (40000, 1.5), (40000, 1.7), (80001, 0.3)])
+def test_pairs_on_both_sides_of_the_few_per_cell_rule(dp, n, density, pairs):
+    """Where cells hold few particles the lists are built by four lanes per
+    particle, elsewhere by a wave per piece of a cell: pairs of the oracle at
+    densities around the rule (1.5 and 3.5 per cell), in blocked order, with a
+    free boundary and a crowd, for tiles of 32, 64 and 128 and both-sides lists."""
+    side = max((n / density) ** (1 / 3), 3.95)
+    box, per = [1.3 * side, side, side / 1.3 if n > 100 else side], [0, 1, 1]
+    q, p, e = W.equilibrium_state(n, box, seed=n)
+    rng = np.random.default_rng(n)
+    q[::7, 0] += 0.4 * box[0]           # some beyond the open face
+    q[:40] = np.array([1.0, 0.1, 0.1]) + 0.9 * rng.random((40, 3))
+    s = dp.System(dp.Config(n=n, box=box, periodic=per, dt=0.005, neighbor_cap=192), q, p, e)
+    P = O.make_params(n, box, periodic=per)
+    s.set_shape(pairs=pairs, order_block=1 + n % 2)
+    assert np.array_equal(s.debug_pairs(), O.pairs(P, q, "cells"))
+    s.step(8)
+    s.set_state(*s.get_state())
+    assert np.array_equal(s.debug_pairs(), O.pairs(P, _state(s)[0], "cells"))
+    s.close()
+
+
+def test_batched_lists_of_few_per_cell(dp):
+    """Replicas of one particle per cell and fewer (tiles across replicas)."""
+    cfgs, qs, ps, es = [], [], [], []
+    for r, n in enumerate([300, 41, 129, 500, 10]):
+        box = [max((n / 0.4) ** (1 / 3), 3.95)] * 3
+        q, p, e = W.equilibrium_state(n, box, seed=50 + r)
+        cfgs.append(dp.Config(n=n, box=box, dt=0.01, seed=r, replica=r))
+        qs.append(q); ps.append(p); es.append(e)
+    for pairs in (0, 1):
+        b = dp.System(cfgs, np.vstack(qs), np.vstack(ps), np.concatenate(es))
+        b.set_shape(pairs=pairs)
+        b.step(12)
+        got = _state(b)
+        for r, c in enumerate(cfgs):
+            s = dp.System(c, qs[r], ps[r], es[r])
+            s.set_shape(pairs=pairs)
+            s.step(12)
+            rows = slice(b.offsets[r], b.offsets[r + 1])
+            assert _same(_state(s)[:3], [x[rows] for x in got[:3]]), (r, pairs)
+            s.close()
+        b.close()
+
+
+def test_list_build_is_no_dearer_where_cells_hold_few(dp):
+    """N = 262,144 at density 0.3 (0.7 particles to a cell) against density 3:
+    46 against 82 us per build (117 by the pieces of cells)."""
+    n, us = 262144, {}
+    for density in (0.3, 3.0):
+        box = [(n / density) ** (1 / 3)] * 3
+        q, p, e = W.equilibrium_state(n, box, seed=1)
+        s = dp.System(dp.Config(n=n, box=box, dt=0.005), q, p, e)
+        s.profile(True)
+        for _ in range(6):
+            s.set_state(q, p, e, 0)
+        ms, count = s.profile_read()["build_skin"]
+        us[density] = 1e3 * ms / count
+        s.close()
+    assert us[0.3] < us[3.0], us

@@ -559,11 +559,15 @@ enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 // block: N = 1000 38.4 / 37.0 / 35.7, 4000 38.3 / 37.0 / 39.0, 16000 43.8 /
 // 43.0 / 59.4, 32768 53.6 / 53.7 / -, 65536 71.1 / 72.4 / -; with five launches
 // (two for the scan, a scatter into cell buckets) 41.4, 41.7, 47.2, 56.6, 73.9.
+// From 2^17 cells the scan is two launches (tile sums, then the scan): one took, on
+// builds, 23 us at 157,000 cells (N = 2^20 at density 3) and 33 at 298,000 (N =
+// 65,536 at density 0.1) against 14 and 16 for the two, and 12 against 13 averaged
+// over steps of which a third build.
 struct BinPlan {
   unsigned blocks;
   int threads, scan, whole;
 };
-constexpr int64_t kBinWholeN = 2048, kBinScanCells = 4096, kScanWideCells = 1 << 19;
+constexpr int64_t kBinWholeN = 2048, kBinScanCells = 4096, kScanWideCells = 1 << 17;
 BinPlan bin_plan(const dpde_handle* h) {
   const int scan = h->ncells <= kBinScanCells ? 1 : 0;
   if (h->n <= kBinWholeN && scan) return {1u, kAuxMaxThreads, 1, 1};

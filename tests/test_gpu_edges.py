@@ -310,3 +310,28 @@ def test_list_build_of_a_crowded_cell(dp):
             assert np.array_equal(s.debug_pairs(), O.pairs(P, q, "cells"))
         s.close()
     assert us[12000] < 5.5 * us[3000], us
+
+
+def _binning_us(s, state, builds=6):
+    """Mean times of the binning's kernels over forced builds of a state."""
+    s.profile(True)
+    s.profile_read()
+    for _ in range(builds):
+        s.set_state(*state, 0)
+    out = {k: 1e3 * ms / count for k, (ms, count) in s.profile_read().items()}
+    s.profile(False)
+    return out
+
+
+def test_scan_of_many_cells(dp):
+    """300,000 cells against 10,000 (N = 65,536 at density 0.1 and 3): 16
+    against 12 us (33 where every block added up all counts before its own)."""
+    n, us = 65536, {}
+    for density in (0.1, 3.0):
+        box = [(n / density) ** (1 / 3)] * 3
+        q, p, e = W.equilibrium_state(n, box, seed=1)
+        s = dp.System(dp.Config(n=n, box=box), q, p, e)
+        t = _binning_us(s, (q, p, e))
+        us[density] = sum(v for k, v in t.items() if k.startswith("scan"))
+        s.close()
+    assert us[0.1] < 2.0 * us[3.0], us

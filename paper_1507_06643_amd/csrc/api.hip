@@ -563,6 +563,12 @@ enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 // builds, 23 us at 157,000 cells (N = 2^20 at density 3) and 33 at 298,000 (N =
 // 65,536 at density 0.1) against 14 and 16 for the two, and 12 against 13 averaged
 // over steps of which a third build.
+// A set state (kick = 0) is in no cell order: there a large system's chains are
+// scattered loads and its records scattered writes, so it is ranked by buckets of
+// the cells, for one launch more.  Measured, us for binning and ranking, chains /
+// buckets: N = 262,144 68 / 65, 480,000 115 / 94, 2^20 271 / 165; 30,000 of 600,000
+// particles in one cell 13,100 / 2850.
+constexpr int64_t kBucketN = 1 << 18;
 struct BinPlan {
   unsigned blocks;
   int threads, scan, whole;
@@ -602,8 +608,10 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
            (const Geo*)h->geo, h->phys, kick, (const QIdF*)h->qid, h->ctl, h->status);
   // the binning in as few launches as its size allows
   const BinPlan plan = bin_plan(h);
+  CellBins bins = h->bins;
+  if (!kick && n > kBucketN) bins.bucket = reinterpret_cast<uint2*>(h->dpi);  // idle between steps
   launch(h, "bin", h->batch ? k_bin<true> : k_bin<false>, plan.blocks, plan.threads, h->cur, h->alt,
-         n, (const Geo*)h->geo, h->bins, plan.scan, plan.whole, h->bin_ticket, h->qid, h->slot, ctl,
+         n, (const Geo*)h->geo, bins, plan.scan, plan.whole, h->bin_ticket, h->qid, h->slot, ctl,
          hs2, (const uint32_t*)h->status);
   if (!plan.scan && h->ncells <= kScanWideCells) {
     launch(h, "scan_cells", k_scan_cells, blocks(h->ncells, kScanWideTile), kScanWideThreads,
@@ -614,9 +622,12 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
     launch(h, "scan_apply", k_scan_apply, h->scan_tiles, kScanThreads, h->bins.count, h->ncells,
            (const uint32_t*)h->scan_tmp, h->bins.start, ctl, hs2);
   }
+  if (bins.bucket)
+    launch(h, "bin_scatter", k_bin_scatter, blocks(n, b), b, bins, n, ctl, hs2,
+           (const uint32_t*)h->status);
   if (!plan.whole)
     launch(h, "rank_gather", h->batch ? k_rank_gather<true> : k_rank_gather<false>, blocks(n, b), b,
-           h->cur, h->alt, h->bins, n, (const Geo*)h->geo, h->qid, h->slot, ctl, hs2,
+           h->cur, h->alt, bins, n, (const Geo*)h->geo, h->qid, h->slot, ctl, hs2,
            (const uint32_t*)h->status);
   const bool uniq = uniq_form(h);
   // The list build reads the reordered records from the spare buffer and

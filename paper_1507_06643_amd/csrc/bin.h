@@ -10,7 +10,8 @@
 // counting pass: histogram of cells with integer atomics, which also chains
 // each cell's particles, then an exclusive scan to cell offsets); digit 2 is
 // the particle identifier: every particle counts the smaller identifiers of
-// its cell's chain.  The resulting order is a pure function of the positions,
+// its cell's chain (of its bucket, where a large state has just been set).  The
+// resulting order is a pure function of the positions,
 // independent of the previous order and of atomic arrival order, so
 // trajectories are bit reproducible and a resumed run continues exactly.
 #pragma once
@@ -409,13 +410,16 @@ __global__ void k_scan_apply(uint32_t* __restrict__ in, int64_t n,
 // ---- the list build's binning -------------------------------------------------
 // Cells: the histogram and, per cell, a chain of its particles (link[i] = the
 // identifier and the next particle; `first` heads it), both left cleared by the
-// list build.
+// list build.  Ranking along the chains is no slower than along a contiguous list
+// also where cells are crowded, as steps meet them (3000 particles in one cell 302
+// against 390 us, 12,000 1175 against 1500).
 struct CellBins {
   uint32_t* count;
   uint32_t* first;
   uint32_t* start;  // exclusive scan of the histogram, ncells + 1
   uint2* link;
   uint32_t* key;    // cell of every particle
+  uint2* bucket;    // by cell: particle and identifier, or null (chains)
   int64_t ncells;
 };
 constexpr uint32_t kChainEnd = 0xFFFFFFFFu;
@@ -432,6 +436,7 @@ __device__ __forceinline__ void rank_move(const PState& src, const PState& dst, 
                                           int64_t i, const Geo* __restrict__ geo,
                                           QIdF* __restrict__ qid, uint32_t* __restrict__ slot) {
   const uint32_t c = cb.key[i];
+  const uint32_t b = cb.start[c];
   // The record as four 16-byte words: copied as a structure, half of it went
   // through LDS (32 KB per block, bank conflicts on every access; a build at
   // N = 1M 166 -> 150 us here, N = 65,536 75.7 -> 74.8 us per step).
@@ -439,11 +444,16 @@ __device__ __forceinline__ void rank_move(const PState& src, const PState& dst, 
   const uint4 w0 = from[0], w1 = from[1], w2 = from[2], w3 = from[3];
   const uint32_t id = w3.z;
   const double e = src.eps[i];
-  uint32_t p = cb.start[c];
-  for (uint32_t j = cb.first[c]; j != kChainEnd;) {
-    const uint2 l = cb.link[j];
-    p += l.x < id ? 1u : 0u;
-    j = l.y;
+  uint32_t p = b;
+  if (cb.bucket) {  // uniform
+    const uint32_t e = cb.start[c + 1];
+    for (uint32_t m = b; m < e; ++m) p += cb.bucket[m].y < id ? 1u : 0u;
+  } else {
+    for (uint32_t j = cb.first[c]; j != kChainEnd;) {
+      const uint2 l = cb.link[j];
+      p += l.x < id ? 1u : 0u;
+      j = l.y;
+    }
   }
   uint4* to = reinterpret_cast<uint4*>(dst.r + p);
   to[0] = w0;
@@ -491,6 +501,11 @@ __global__ __launch_bounds__(kAuxMaxThreads) void k_bin(
       c = (uint32_t)(g.cell_base + cell_key(g, cx, cy, cz));
       id = rc.id;
       cb.key[i] = c;
+    }
+    if (cb.bucket) {  // uniform
+      const uint32_t t = run_ticket(c, live, cb.count);
+      if (live) cb.link[i] = make_uint2(id, t);
+      continue;
     }
     const int lane = threadIdx.x % kWave;
     const LaneRun r = lane_run(c, live);
@@ -556,14 +571,28 @@ __global__ __launch_bounds__(kScanWideThreads) void k_scan_cells(CellBins cb, co
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cb.start[cb.ncells] = offset + total;
 }
 
+// The buckets: each cell's particles side by side, in the order of their tickets
+// (link = the identifier and the ticket).
+__global__ void k_bin_scatter(CellBins cb, int64_t n, const BuildCtl* ctl, double half_skin2,
+                              const uint32_t* status) {
+  if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint2 l = cb.link[i];
+  cb.bucket[cb.start[cb.key[i]] + l.y] = make_uint2((uint32_t)i, l.x);
+}
+
+// A particle per lane: those of the present memory order, or with buckets those
+// of the new one's cells, so that the records, read wherever they lie, are
+// written side by side.
 template <bool BATCH>
 __global__ void k_rank_gather(PState src, PState dst, CellBins cb, int64_t n,
                               const Geo* __restrict__ geo, QIdF* __restrict__ qid,
                               uint32_t* __restrict__ slot, const BuildCtl* ctl, double half_skin2,
                               const uint32_t* status) {
   if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) rank_move<BATCH>(src, dst, cb, i, geo, qid, slot);
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n) rank_move<BATCH>(src, dst, cb, cb.bucket ? cb.bucket[k].x : k, geo, qid, slot);
 }
 
 }  // namespace dpde

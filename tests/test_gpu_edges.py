@@ -335,3 +335,32 @@ def test_scan_of_many_cells(dp):
         us[density] = sum(v for k, v in t.items() if k.startswith("scan"))
         s.close()
     assert us[0.1] < 2.0 * us[3.0], us
+
+
+def test_ranking_of_a_large_set_state(dp):
+    """A set state lies in identifier order.  N = 600,000 of which 30,000 share a
+    border cell: ranked within twice the time that steps take from the sorted
+    state; the order is that of identifiers inside each cell, the pairs and the
+    next steps those of the state's own resumption."""
+    n, out = 600000, 30000
+    box = [W.cubic_side(n)] * 3
+    q, p, e = W.equilibrium_state(n, box, seed=5)
+    rng = np.random.default_rng(6)
+    k = rng.permutation(n)[:out]
+    q[k, 0] = box[0] + 5.0 + 1e4 * rng.random(out)
+    q[k, 1:] = rng.random((out, 2))
+    p[k] = 0.0
+    s = dp.System(dp.Config(n=n, box=box, periodic=[0, 1, 1], dt=0.005, skin=0.02), q, p, e)
+    forced = _binning_us(s, (q, p, e))["rank_gather"]
+    rows, cells = s.debug_order().cpu().numpy(), s.debug_cells().cpu().numpy()
+    assert np.array_equal(np.lexsort((np.arange(n), cells)), rows)
+    s.step(1)
+    steps = _kernel_us(s, 4)["rank_gather"]
+    assert forced < 2.0 * steps, (forced, steps)
+    a = _state(s)
+    s.step(2)
+    b = _state(s)
+    s.set_state(*a)
+    s.step(2)
+    assert _same(_state(s), b)
+    s.close()

@@ -215,6 +215,19 @@ __device__ __forceinline__ float build_radius2(const BuildCtl* ctl, double rs, d
   return thr2;
 }
 
+// Entries k0, k0 + step, ... of particle i's list of `count` (memory indices)
+// that tiles of 128 would list too.
+__device__ __forceinline__ uint32_t listed_in_128(const SkinList& sl, int64_t i, int count, int k0,
+                                                  int step) {
+  uint32_t listed = 0;
+  for (int k = k0; k < count; k += step) {
+    const uint32_t j = sl.idx[list_entry(i, k, sl.cap)], x = (uint32_t)i ^ j;
+    const bool mine = (x & 1u) ? (uint32_t)i < j : (uint32_t)i > j;
+    listed += x >= (uint32_t)kUniqTile || mine ? 1u : 0u;
+  }
+  return listed;
+}
+
 // The build's block serves a tile of 128 consecutive particles.  Particles of
 // one cell share their 27-cell stencil, so the unit of work is a piece: up to
 // kPiece particles of the tile in one cell, taken by one wave.  The wave lists
@@ -392,7 +405,6 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     pre -= cn;
     const QIdF own = qid[tb + (lane < p1 - p0 ? p0 + lane : p0)];  // lane q: particle p0 + q
     uint32_t counts = 0;  // lane q: entries of particle p0 + q so far
-    uint32_t wide = 0;    // lane q: those of them that tiles of 128 would list too
     const uint32_t first = (uint32_t)g.first;
     for (uint32_t w0 = 0; w0 < total; w0 += kBuildWindow) {
       const uint32_t lo = pre > w0 ? pre : w0;
@@ -452,7 +464,6 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
         const float yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.y), q));
         const float zi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own.z), q));
         uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)counts, q);
-        uint32_t base_wide = NARROW ? (uint32_t)__builtin_amdgcn_readlane((int)wide, q) : 0u;
         const uint32_t tq = (uint32_t)(p0 + q);
 #pragma unroll
         for (int c = 0; c < kBuildChunks; ++c) {
@@ -470,10 +481,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
             const unsigned long long out = __ballot((rel[c] ^ tq) >= (uint32_t)tile);
             const unsigned long long below = __ballot(rel[c] < tq), above = __ballot(rel[c] > tq);
             const unsigned long long same = (tq & 1u) ? odd[c] : ~odd[c];
-            const unsigned long long mine = (same & below) | (~same & above);
-            if constexpr (NARROW)
-              base_wide += (uint32_t)__popcll(m & (__ballot(rel[c] >= (uint32_t)kUniqTile) | mine));
-            m &= out | mine;
+            m &= out | (same & below) | (~same & above);
           } else {
             m &= __ballot(rel[c] != tq);
           }
@@ -489,7 +497,6 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
           }
         }
         counts = lane == q ? base : counts;
-        if constexpr (NARROW) wide = lane == q ? base_wide : wide;
       };
       if (images) {
         for (int q = 0; q < p1 - p0; ++q) test(q, std::true_type{});
@@ -499,7 +506,7 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
       __builtin_amdgcn_wave_barrier();  // the next window overwrites src
     }
     if (lane < p1 - p0) {
-      if ((NARROW ? wide : counts) > limit) atomicOr(status, ST_OVERFLOW);
+      if (counts > (NARROW ? cap : limit)) atomicOr(status, ST_OVERFLOW);
       counts = counts < cap ? counts : cap;
       count_s[p0 + lane] = counts;
       atomicMax(&most_s, counts);
@@ -512,6 +519,15 @@ __global__ __launch_bounds__(kBuildMaxThreads) void k_build_skin(
     if ((int)p < np && k < count_s[p]) sl.idx[list_entry(tb + p, k, sl.cap)] = lst[c];
   }
   if (t < np) sl.count[tb + t] = count_s[t];
+  if constexpr (NARROW) {
+    if (most_s > limit) {  // uniform
+      __threadfence_block();
+      __syncthreads();  // the lists are written
+      if (t < np && count_s[t] > limit &&
+          listed_in_128(sl, tb + t, (int)count_s[t], 0, 1) > limit)
+        atomicOr(status, ST_OVERFLOW);
+    }
+  }
 }
 
 // ---- the same lists where cells hold few particles ----------------------------
@@ -701,14 +717,12 @@ __global__ __launch_bounds__(kPairBlockMax) void k_build_lanes(
   const float thr2 = build_radius2(ctl, rs, box_max);
   const QIdF own = qid[i];
   uint32_t nn = 0;
-  uint32_t wide = 0;  // this lane's entries that tiles of 128 would list too
   const uint32_t cap = (uint32_t)sl.cap;
   const uint32_t first = (uint32_t)g.first;
   auto sink = [&](bool take, uint32_t j, uint32_t idj) {
     if constexpr (UNIQ) {
       const uint32_t x = (uint32_t)i ^ j;
       const bool mine = (x & 1u) ? (uint32_t)i < j : (uint32_t)i > j;
-      if constexpr (NARROW) wide += take && (x >= (uint32_t)kUniqTile || mine) ? 1u : 0u;
       take = take && (x >= (uint32_t)tile || mine);
     }
     const uint32_t bits = group_ballot(L, take);
@@ -731,12 +745,8 @@ __global__ __launch_bounds__(kPairBlockMax) void k_build_lanes(
                                    sink)
           : scan_candidates<true>(L, g, start, qid, own.x, own.y, own.z, cx, cy, cz, thr2, runs,
                                   sink);
-  if constexpr (NARROW) {
-#pragma unroll
-    for (int off = 1; off < kSub; off <<= 1) wide += (uint32_t)__shfl_xor((int)wide, off, kWave);
-  }
   // a stencil too full to count is a list overflow
-  if (!whole || (NARROW ? wide : nn) > limit) {
+  if (!whole || nn > (NARROW ? cap : limit)) {
     if (L.sub == 0) atomicOr(status, ST_OVERFLOW);
   }
   nn = nn < cap ? nn : cap;
@@ -744,6 +754,16 @@ __global__ __launch_bounds__(kPairBlockMax) void k_build_lanes(
   for (uint32_t k = L.sub; k < staged; k += kSub)
     sl.idx[list_entry(i, k, sl.cap)] = lst[k * L.ppb + L.pib];
   if (L.sub == 0) sl.count[i] = nn;
+  if constexpr (NARROW) {
+    if (nn > limit) {  // uniform in the group
+      __threadfence_block();  // the list is written
+      uint32_t listed = listed_in_128(sl, i, (int)nn, L.sub, kSub);
+#pragma unroll
+      for (int off = 1; off < kSub; off <<= 1)
+        listed += (uint32_t)__shfl_xor((int)listed, off, kWave);
+      if (listed > limit && L.sub == 0) atomicOr(status, ST_OVERFLOW);
+    }
+  }
 }
 
 // Sort each skin list by neighbour identifier and replace the identifier

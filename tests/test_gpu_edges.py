@@ -379,3 +379,25 @@ def test_records_of_many_replicas(dp):
     h = s.history()
     assert h.shape[1:] == (3000, 12) and np.array_equal(h[:, :, 9], np.arange(1, 33)[:, None] * np.ones(3000))
     s.close()
+
+
+@pytest.mark.parametrize("n,density", [(1000, 0.5), (4000, 0.6), (30000, 0.6), (40000, 1.4)])
+def test_list_capacity_where_cells_hold_few(dp, n, density):
+    """As test_list_capacity_is_that_of_tiles_of_128, for the lists built by
+    four lanes per particle."""
+    box = [(n / density) ** (1 / 3)] * 3
+    q, p, e = W.equilibrium_state(n, box, seed=n)
+    kw = dict(n=n, box=box, dt=0.01)
+    ref = dp.System(dp.Config(**kw), q, p, e)
+    cap = int(_longest_tile_list(ref, q, box, 1.3, 128))
+    assert _longest_tile_list(ref, q, box, 1.3, 32 if n <= 16384 else 64) > cap
+    s = dp.System(dp.Config(neighbor_cap=cap, **kw), q, p, e)
+    assert np.array_equal(s.debug_pairs(), ref.debug_pairs())
+    s.step(1)
+    ref.step(1)
+    assert _same(_state(ref), _state(s))
+    with pytest.raises(dp.DpdeError) as ex:
+        dp.System(dp.Config(neighbor_cap=cap - 1, **kw), q, p, e)
+    assert ex.value.code == dp._lib.DPDE_EOVERFLOW
+    s.close()
+    ref.close()

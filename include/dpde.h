@@ -77,9 +77,9 @@ extern "C" {
                              /* the paper notes.  Vector model, stored increments */
                              /* only.  SSA is sequential inside a domain, so its  */
                              /* cost grows with the domain size (tens of          */
-                             /* particles per domain suit the GPU); the handle    */
-                             /* reserves room for n * cap / 2 intra-domain pairs  */
-                             /* of 40 bytes each (cap = the list capacity).       */
+                             /* particles per domain suit the GPU); beside SER's  */
+                             /* lists the handle holds n * cap entries of 4 bytes */
+                             /* (cap = the list capacity).                        */
 
 /* Direction of friction and noise (Sec. 2.1). */
 #define DPDE_MODEL_VECTOR 0  /* along v_ij with a 3-d Gaussian G_ij (eq. DPDE,    */

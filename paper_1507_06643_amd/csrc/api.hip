@@ -437,8 +437,6 @@ int allocate(dpde_handle* h) {
         (rc = dalloc(h, &h->dscan_tmp, (size_t)h->dscan_tiles + 1)) ||
         (rc = dalloc(h, &h->pcnt, n)) || (rc = dalloc(h, &h->poff, n + 1)) ||
         (rc = dalloc(h, &h->pscan_tmp, (size_t)h->pscan_tiles + 1)) ||
-        (rc = dalloc(h, &h->ssa.idx, (size_t)h->ssa.cap)) ||
-        (rc = dalloc(h, &h->ssa.gc, (size_t)h->ssa.cap)) ||
         (rc = dalloc(h, &h->always, 1)))
       return rc;
     HIPCHK(hipMemset(h->dcount, 0, (h->ndoms + 1) * sizeof(uint32_t)));
@@ -454,6 +452,12 @@ int allocate(dpde_handle* h) {
   if (!h->regen && (rc = dalloc(h, &h->nl.de, 3 * entries))) return rc;
   h->inter.cap = h->nl.cap;
   h->inter.de = h->nl.de;
+  if (h->hybrid) {
+    // the intra-domain pairs (40 bytes for half an entry each) are done with
+    // when the sweeps write the increments (24 bytes an entry): one memory
+    h->ssa.gc = reinterpret_cast<Vec4*>(h->nl.de);
+    h->ssa.idx = reinterpret_cast<uint2*>(h->ssa.gc + h->ssa.cap);
+  }
   if ((rc = dalloc(h, &h->status, 4)) || (rc = dalloc(h, &h->d_step, 1)) ||
       (rc = dalloc(h, &h->d_hist_count, 1)) || (rc = dalloc(h, &h->counter, 1)) ||
       (rc = dalloc(h, &h->stats_ticket, 1)))

@@ -401,3 +401,23 @@ def test_list_capacity_where_cells_hold_few(dp, n, density):
     assert ex.value.code == dp._lib.DPDE_EOVERFLOW
     s.close()
     ref.close()
+
+
+def test_memory_of_a_hybrid_handle(dp):
+    """Hybrid needs a third list and the intra-domain pairs beside what SER
+    holds; the pairs share the memory of the increments, so that it stays below
+    the 20 bytes an entry that the pairs alone took."""
+    import torch
+    n, cap, used = 200000, 96, {}
+    L = W.cubic_side(n)
+    q, p, e = W.equilibrium_state(n, [L] * 3, seed=3)
+    q, p, e = (torch.as_tensor(x).cuda() for x in (q, p, e))
+    for scheme in (dp.SCHEME_SER, dp.SCHEME_SER, dp.SCHEME_HYBRID):  # (the first loads the code)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        s = dp.System(dp.Config(n=n, box=[L] * 3, dt=0.005, scheme=scheme, ndom=(16, 16, 16)),
+                      q, p, e)
+        used[scheme] = free - torch.cuda.mem_get_info()[0]
+        s.close()
+    more = used[dp.SCHEME_HYBRID] - used[dp.SCHEME_SER]
+    assert more <= 20 * n * cap, used

@@ -269,7 +269,8 @@ int dpde_set_tuning(dpde_handle* h, int32_t pair_block, int32_t aux_block);
  * the same bits, and the two pair forms agree to rounding (their
  * per-particle sums are added in different arithmetic), so the shape can be
  * tuned on the live system.
- *   pair_block  threads per block of the both-sides pair passes (64..256)
+ *   pair_block  threads per block of the both-sides pair passes, and of the
+ *               list build where cells hold few particles (64..256)
  *   aux_block   threads per block of the per-particle passes (64..1024)
  *   pairs       form of the SER sweeps (eqs. SER_p, SER_eint_discretization):
  *     DPDE_PAIRS_BOTH_SIDES     every pair term evaluated on both of its
@@ -277,8 +278,9 @@ int dpde_set_tuning(dpde_handle* h, int32_t pair_block, int32_t aux_block);
  *                               neighbour-identifier order;
  *     DPDE_PAIRS_ONCE_PER_TILE  a pair joining two particles of one tile of
  *                               128 consecutive particles (cell order; fewer
- *                               in small systems) evaluated once for both, a pair joining two
- *                               tiles once per particle; the per-particle
+ *                               in small systems) evaluated once for both, a
+ *                               pair joining two tiles once per particle; the
+ *                               per-particle
  *                               sums exact in 64-bit fixed point (grid 2^-46,
  *                               a term of magnitude >= 32 fails the step with
  *                               DPDE_ERANGE), rounded once.  The default.  It
@@ -311,7 +313,7 @@ int dpde_set_shape(dpde_handle* h, const dpde_shape* shape);
 /* Autotuner: time every launch shape over `steps` steps of this system and
  * keep the fastest.  The candidates are the pair form (both forms where the
  * tile form applies), the cell order (order_block 1..4), the lane-group
- * block (64/128/256 threads: the both-sides passes) and
+ * block (64/128/256 threads; 256 for the tile form where nothing uses it) and
  * the per-particle block (128/256/512).  The winner is applied as by
  * dpde_set_shape, its pair and per-particle blocks and time per step are
  * returned (read the full shape with dpde_get_shape), and it is recorded in

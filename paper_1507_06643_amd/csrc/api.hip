@@ -1507,18 +1507,16 @@ int dpde_autotune(dpde_handle* h, int32_t steps, int32_t* pair_block, int32_t* a
   // the lane-group and per-particle blocks
   const dpde_shape sh0 = get_shape(h);
   std::vector<dpde_shape> cands;
-  const bool two_forms = [&] {
-    const bool keep = h->pairs_once;
-    h->pairs_once = true;
-    const bool u = uniq_form(h);
-    h->pairs_once = keep;
-    return u;
-  }();
+  const bool two_forms = uniq_applies(h);
   for (int form : {DPDE_PAIRS_ONCE_PER_TILE, DPDE_PAIRS_BOTH_SIDES}) {
     if (!two_forms && form != sh0.pairs) continue;
+    // in the tile form only the list build of few particles per cell has
+    // blocks of pair_block threads
+    const bool no_pb = two_forms && form == DPDE_PAIRS_ONCE_PER_TILE && !few_per_cell(h);
     for (int ob = 1; ob <= 4; ++ob)
       for (int pb : {64, 128, 256})
-        for (int ab : {128, 256, 512}) cands.push_back(dpde_shape{pb, ab, form, ob});
+        for (int ab : {128, 256, 512})
+          if (!no_pb || pb == 256) cands.push_back(dpde_shape{pb, ab, form, ob});
   }
   dpde_shape best_sh = sh0;
   double best = 1e300;

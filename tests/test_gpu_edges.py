@@ -421,3 +421,22 @@ def test_memory_of_a_hybrid_handle(dp):
         s.close()
     more = used[dp.SCHEME_HYBRID] - used[dp.SCHEME_SER]
     assert more <= 20 * n * cap, used
+
+
+@pytest.mark.parametrize("density,shapes", [(3.0, 12 + 36), (0.3, 36 + 36)])
+def test_autotune_times_each_shape_once(dp, density, shapes):
+    """The tile form's passes have blocks of their own, so that only where the
+    list build has blocks of pair_block threads (few particles to a cell) do
+    its shapes differ by them.  Each shape takes a forced build, a warm-up and
+    the timed steps; one more build restores the state."""
+    n = 3000
+    box = [(n / density) ** (1 / 3)] * 3
+    s = dp.System(dp.Config(n=n, box=box), *W.equilibrium_state(n, box, seed=91))
+    s.profile(True)
+    s.profile_read()
+    try:
+        s.autotune(1)
+    finally:
+        dp.tuning_clear()
+    assert s.profile_read()["pass_a_forces"][1] == 3 * shapes + 1
+    s.close()

@@ -439,6 +439,10 @@ int dpde_debug_cells(dpde_handle* h, int32_t* cell_of_id);
  * the cells of Sec. 3.1.2) fill consecutive slots in increasing ID order. */
 int dpde_debug_order(dpde_handle* h, int32_t* row_of_slot);
 
+/* Test hook: run the tile form in tiles of `tile` particles (128, or 64 or 32
+ * where the system is small enough to use them itself).  Changes no bit. */
+int dpde_debug_tile(dpde_handle* h, int32_t tile);
+
 /* 1/T_i of every particle as the last step left it (device FP64 n, ID order):
  * the inverse temperature of eq. DPDE_internalEOS that the next step's
  * friction gamma_ij uses (eq. DPDE_fd). */

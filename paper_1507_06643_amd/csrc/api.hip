@@ -78,6 +78,7 @@ struct dpde_handle {
   // (k_pass_b_uniq, k_pass_c_uniq) rather than every pair term on both
   // particles' lanes (k_pass_b, k_pass_c)
   bool pairs_once = true;
+  int tile_most = 2;  // largest index into kTiles (test hook; else the rule on n alone)
 
   PState cur{}, alt{};
   double half_skin2 = 0.0, rs2 = 0.0;
@@ -370,16 +371,17 @@ struct TileShape {
 constexpr TileShape kTiles[3] = {{128, 4, 2}, {64, 4, 4}, {32, 8, 8}};
 constexpr int64_t kTileMidN = 73728, kTileSmallN = 16384;  // largest N of the smaller tiles
 
-int tile_index(const dpde_handle* h) {
+int own_tile_index(const dpde_handle* h) {
   return h->n <= kTileSmallN ? 2 : h->n <= kTileMidN ? 1 : 0;
 }
+int tile_index(const dpde_handle* h) { return std::min(own_tile_index(h), h->tile_most); }
 TileShape tile_shape(const dpde_handle* h) { return kTiles[tile_index(h)]; }
 
 // Entries a list needs beyond the capacity asked for, which is that of tiles of
 // 128 (k_build_skin): of the 128 - T particles outside a particle's own smaller
 // tile, those lists leave out half.
 int tile_headroom(const dpde_handle* h) {
-  return uniq_applies(h) ? (kUniqTile - tile_shape(h).tile) / 2 : 0;
+  return uniq_applies(h) ? (kUniqTile - kTiles[own_tile_index(h)].tile) / 2 : 0;
 }
 
 int alloc_pstate(dpde_handle* h, PState& s) {
@@ -1428,6 +1430,20 @@ int dpde_get_shape(dpde_handle* h, dpde_shape* out) {
   return DPDE_OK;
 }
 
+// The memory order and the lists made anew, and the forces, from the current
+// positions (no kick), after a change of what they depend on.
+static int rebuild(dpde_handle* h) {
+  static const BuildCtl forced{0ull, 1u, 0u, 0ull};
+  static const BuildCtl cleared{0ull, 0u, 0u, 0ull};
+  int rc = upload_geo(h);
+  if (rc) return rc;
+  HIPCHK(hipMemcpyAsync(h->ctl, &forced, sizeof(BuildCtl), hipMemcpyHostToDevice, h->stream));
+  enqueue_bin(h, 0);
+  enqueue_forces(h, 0);
+  HIPCHK(hipMemcpyAsync(h->ctl, &cleared, sizeof(BuildCtl), hipMemcpyHostToDevice, h->stream));
+  return DPDE_OK;
+}
+
 int dpde_set_shape(dpde_handle* h, const dpde_shape* shape) {
   if (!h || !shape) return fail(DPDE_EINVAL, "NULL argument");
   if (shape->pairs != DPDE_PAIRS_BOTH_SIDES && shape->pairs != DPDE_PAIRS_ONCE_PER_TILE)
@@ -1439,17 +1455,10 @@ int dpde_set_shape(dpde_handle* h, const dpde_shape* shape) {
     return fail(DPDE_EINVAL, "block sizes must be multiples of 64 within the kernel limits");
   const dpde_shape cur = get_shape(h);
   put_shape(h, *shape);
-  // the order and the lists follow the shape: rebuild them and the forces
-  // from the current positions (no kick)
+  // the order and the lists follow the shape
   if (cur.pairs != shape->pairs || cur.order_block != shape->order_block) {
-    static const BuildCtl forced{0ull, 1u, 0u, 0ull};
-    static const BuildCtl cleared{0ull, 0u, 0u, 0ull};
-    int rc = upload_geo(h);
+    int rc = rebuild(h);
     if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(h->ctl, &forced, sizeof(BuildCtl), hipMemcpyHostToDevice, h->stream));
-    enqueue_bin(h, 0);
-    enqueue_forces(h, 0);
-    HIPCHK(hipMemcpyAsync(h->ctl, &cleared, sizeof(BuildCtl), hipMemcpyHostToDevice, h->stream));
   }
   HIPCHK(hipStreamSynchronize(h->stream));
   return read_status(h);
@@ -1715,6 +1724,20 @@ int dpde_debug_order(dpde_handle* h, int32_t* row_of_slot) {
   HIPCHK(hipStreamSynchronize(h->stream));
   HIPCHK(hipGetLastError());
   return DPDE_OK;
+}
+
+int dpde_debug_tile(dpde_handle* h, int32_t tile) {
+  if (!h) return fail(DPDE_EINVAL, "handle is NULL");
+  int index = -1;
+  for (int k = 0; k <= own_tile_index(h); ++k)
+    if (kTiles[k].tile == tile) index = k;
+  if (index < 0)
+    return fail(DPDE_EINVAL, "tile must be 128 or a smaller one of this system's size class, got %d",
+                tile);
+  h->tile_most = index;
+  drop_graph(h);
+  int rc = rebuild(h);
+  return rc ? rc : read_status(h);
 }
 
 int dpde_debug_inv_temperature(dpde_handle* h, double* inv_t) {

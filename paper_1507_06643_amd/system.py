@@ -297,6 +297,9 @@ class System:
         L.check(self._lib.dpde_debug_order(self.h, _ptr(out)))
         return out
 
+    def debug_tile(self, tile: int):
+        L.check(self._lib.dpde_debug_tile(self.h, int(tile)))
+
     def debug_inv_temperature(self):
         out = torch.empty(self.n, dtype=torch.float64, device="cuda")
         L.check(self._lib.dpde_debug_inv_temperature(self.h, _ptr(out)))

@@ -440,3 +440,138 @@ def test_autotune_times_each_shape_once(dp, density, shapes):
         dp.tuning_clear()
     assert s.profile_read()["pass_a_forces"][1] == 3 * shapes + 1
     s.close()
+
+
+TILE_CASES = ["plain", "fp32", "projected_model", "projected_model_fp32", "regenerated",
+              "regenerated_fp32", "regenerated_projected_model", "free_x", "projection", "newton",
+              "surrogate", "surrogate_regenerated", "blocked", "dense"]
+
+
+def _tile_case(dp, case):
+    n, kw, box, per = 1517, dict(dt=0.01), None, [1, 1, 1]
+    if "fp32" in case:
+        kw["precision"] = dp.FP32
+    if "projected_model" in case:
+        kw["model"] = dp.MODEL_PROJECTED
+    if case == "projection":
+        kw["project"] = True
+    if case in ("newton", "surrogate", "surrogate_regenerated"):
+        kw["eos"] = dp.EOS_EINSTEIN
+    if "surrogate" in case:
+        kw["theta_mode"] = dp.THETA_MLP
+    box = [W.cubic_side(n)] * 3
+    if case == "free_x":
+        box, per = [1.7 * box[0], box[0] / 1.25, box[0] / 1.35], [0, 1, 1]
+    if case == "dense":
+        kw.update(dt=0.002, neighbor_cap=512)
+    q, p, e = W.equilibrium_state(n, box, seed=77)
+    if case == "dense":  # lists beyond the rows of pass A and of its work lists
+        q[:500] = np.random.default_rng(4).random((500, 3)) * 1.5 + 2.0
+    ckw = dict(n=n, box=box, periodic=per, **kw)
+
+    class Config(dp.Config):
+        def to_c(self):
+            P = super().to_c()
+            if "regenerated" in case:
+                P.flags |= dp._lib.DPDE_FLAG_REGENERATE_NOISE
+            return P
+
+    return Config, ckw, (q, p, e)
+
+
+@pytest.mark.parametrize("case", TILE_CASES)
+def test_every_tile_gives_the_same_bits(dp, case):
+    """Tiles of 32, 64 and 128 (the ones that large systems run) on one small
+    system, ragged in all of them: the same states, records and pairs bit for
+    bit, over steps with list builds; and one step of the oracle."""
+    Config, ckw, state = _tile_case(dp, case)
+    runs = []
+    for tile in (32, 64, 128):
+        s = dp.System(Config(**ckw), *state)
+        if "surrogate" in case:
+            net = np.random.default_rng(3).normal(0, 0.3, 1153).astype(np.float32)
+            s.mlp_set(net, np.array([5.0, 3.0, 0.0, 2.3]))
+        if case == "blocked":
+            s.set_shape(order_block=3)
+        s.debug_tile(tile)
+        s.step(12)
+        runs.append((_state(s), s.history(), s.debug_pairs(), s.list_builds()))
+        if tile == 128 and case not in ("surrogate", "surrogate_regenerated"):
+            q, p, e, st = runs[-1][0]
+            ok = {k: v for k, v in ckw.items()
+                  if k not in ("n", "box", "precision", "neighbor_cap", "theta_mode", "project")}
+            P = O.make_params(ckw["n"], ckw["box"], step=st, **ok)
+            if case == "projection":
+                P.project = 1
+            S = O.State(P, q, p, e)
+            if case == "projection":
+                P.E0 = runs[-1][1][0, 3]
+            assert S.step(1)[0] == 0
+            s.step(1)
+            q, p, e, _ = _state(s)
+            tol = 5e-6 if "fp32" in case else TOL
+            assert np.abs(p - S.p).max() < tol
+            assert np.abs(e - S.eps).max() < tol * np.abs(S.eps).mean()
+        s.close()
+    for other in runs[1:]:
+        assert _same(runs[0][0], other[0])
+        for a, b in zip(runs[0][1:], other[1:]):
+            assert np.array_equal(a, b)
+    assert runs[0][3] > 2 or case == "dense"
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("tile", [64, 128])
+def test_small_replicas_in_every_tile(dp, tile, prec):
+    """Replicas below the particles of a wave of pass A in the larger tiles."""
+    cfgs, qs, ps, es = [], [], [], []
+    for r, n in enumerate([7, 300, 5, 13, 12, 200, 3, 2, 64]):
+        box = [max(W.cubic_side(n), 3.95)] * 3
+        q, p, e = W.equilibrium_state(n, box, seed=50 + r)
+        cfgs.append(dp.Config(n=n, box=box, dt=0.01, seed=r, replica=r, precision=prec))
+        qs.append(q); ps.append(p); es.append(e)
+    runs = []
+    for t in (32, tile):
+        b = dp.System(cfgs, np.vstack(qs), np.vstack(ps), np.concatenate(es))
+        b.debug_tile(t)
+        b.step(12)
+        runs.append((_state(b), b.history()))
+        b.close()
+    assert _same(runs[0][0], runs[1][0])
+    assert np.array_equal(runs[0][1], runs[1][1])
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 73728, 73729])
+def test_at_the_sizes_where_the_tile_changes(dp, n):
+    """The largest systems of the smaller tiles and the smallest of the larger
+    ones: the bits of tiles of 128, one step of the oracle."""
+    L = W.cubic_side(n)
+    q, p, e = W.equilibrium_state(n, [L] * 3, seed=n)
+    runs = []
+    for tile in (None, 128):
+        s = dp.System(dp.Config(n=n, box=[L] * 3, dt=0.01), q, p, e)
+        if tile:
+            s.debug_tile(tile)
+        s.step(6)
+        runs.append((_state(s), s.history()))
+        if not tile:
+            S = O.State(O.make_params(n, [L] * 3, dt=0.01, step=6), *runs[0][0][:3])
+            assert S.step(1)[0] == 0
+            s.step(1)
+            got = _state(s)
+            assert np.abs(got[1] - S.p).max() < TOL
+            assert np.abs(got[2] - S.eps).max() < TOL * np.abs(S.eps).mean()
+        s.close()
+    assert _same(runs[0][0], runs[1][0])
+    assert np.array_equal(runs[0][1], runs[1][1])
+
+
+def test_tile_hook_refuses_other_tiles(dp):
+    n = 17000
+    L = W.cubic_side(n)
+    s = dp.System(dp.Config(n=n, box=[L] * 3), *W.equilibrium_state(n, [L] * 3, seed=1))
+    for tile in (0, 16, 32, 96, 256):
+        with pytest.raises(dp.DpdeError) as ex:
+            s.debug_tile(tile)
+        assert ex.value.code == dp._lib.DPDE_EINVAL
+    s.close()

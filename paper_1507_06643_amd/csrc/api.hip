@@ -365,14 +365,22 @@ bool uniq_form(const dpde_handle* h) { return h->pairs_once && uniq_applies(h); 
 //   N =  8000   51.7 / 46.6 / 42.3     N =  65536   73.9 / 73.9 / 88.0
 //   N = 16000   54.0 / 48.0 / 47.2     N =  98304   88.4 / 90.9 / 110.7
 //   N = 32768   59.2 / 56.6 / 59.4     N = 131072  102.8 / 112.2 / 135.2
+// (FP32, the projected model and batches by their total N cross at the same
+// places.)  Tiles of 128 / 64 in dense systems, m particles to a cell:
+//   m = 13  N = 48000  119 / 107   60000  126 / 122   73000  148 / 138
+//   m = 22  N = 40000  204 / 191   60000  241 / 248   73000  305 / 294
+//   m = 44  N = 16384  318 / 286   24000  379 / 395   60000  787 / 842
 struct TileShape {
   int tile, lanes_a, lanes;
 };
 constexpr TileShape kTiles[3] = {{128, 4, 2}, {64, 4, 4}, {32, 8, 8}};
 constexpr int64_t kTileMidN = 73728, kTileSmallN = 16384;  // largest N of the smaller tiles
+constexpr int64_t kTileMidPairs = 1 << 20;  // and N times the mean particles of a cell for 64
 
 int own_tile_index(const dpde_handle* h) {
-  return h->n <= kTileSmallN ? 2 : h->n <= kTileMidN ? 1 : 0;
+  if (h->n <= kTileSmallN) return 2;
+  // pairs in dense systems fill the chip at fewer particles
+  return h->n <= kTileMidN && h->n * h->n <= kTileMidPairs * h->ncells ? 1 : 0;
 }
 int tile_index(const dpde_handle* h) { return std::min(own_tile_index(h), h->tile_most); }
 TileShape tile_shape(const dpde_handle* h) { return kTiles[tile_index(h)]; }

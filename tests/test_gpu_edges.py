@@ -575,3 +575,21 @@ def test_tile_hook_refuses_other_tiles(dp):
             s.debug_tile(tile)
         assert ex.value.code == dp._lib.DPDE_EINVAL
     s.close()
+
+
+@pytest.mark.parametrize("n,density,tile", [(60000, 3.0, 64), (60000, 6.0, 64),
+                                            (60000, 10.0, 128), (24000, 20.0, 128),
+                                            (16384, 20.0, 32), (73729, 0.5, 128)])
+def test_tile_of_dense_systems(dp, n, density, tile):
+    """Dense systems fill the chip at fewer particles: they take tiles of 128
+    where tiles of 64 are slower (the hook accepts a system's own tile and
+    larger ones)."""
+    box = [(n / density) ** (1 / 3)] * 3
+    s = dp.System(dp.Config(n=n, box=box, neighbor_cap=512), *W.equilibrium_state(n, box, seed=1))
+    for t in (32, 64, 128):
+        if t >= tile:
+            s.debug_tile(t)
+        else:
+            with pytest.raises(dp.DpdeError):
+                s.debug_tile(t)
+    s.close()

@@ -623,7 +623,8 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
   // the binning in as few launches as its size allows
   const BinPlan plan = bin_plan(h);
   CellBins bins = h->bins;
-  if (!kick && n > kBucketN) bins.bucket = reinterpret_cast<uint2*>(h->dpi);  // idle between steps
+  const bool buckets = plan.whole || (!kick && n > kBucketN);
+  if (buckets) bins.bucket = reinterpret_cast<uint2*>(h->dpi);  // idle until the next sweep 1
   launch(h, "bin", h->batch ? k_bin<true> : k_bin<false>, plan.blocks, plan.threads, h->cur, h->alt,
          n, (const Geo*)h->geo, bins, plan.scan, plan.whole, h->bin_ticket, h->qid, h->slot, ctl,
          hs2, (const uint32_t*)h->status);
@@ -636,7 +637,7 @@ void enqueue_bin(dpde_handle* h, int kick, bool with_kick = true) {
     launch(h, "scan_apply", k_scan_apply, h->scan_tiles, kScanThreads, h->bins.count, h->ncells,
            (const uint32_t*)h->scan_tmp, h->bins.start, ctl, hs2);
   }
-  if (bins.bucket)
+  if (buckets && !plan.whole)
     launch(h, "bin_scatter", k_bin_scatter, blocks(n, b), b, bins, n, ctl, hs2,
            (const uint32_t*)h->status);
   if (!plan.whole)

@@ -467,6 +467,13 @@ __device__ __forceinline__ void rank_move(const PState& src, const PState& dst, 
   slot[(BATCH ? (uint32_t)geo[w3.w].first : 0u) + id] = p;
 }
 
+// The buckets: each cell's particles side by side, in the order of their tickets
+// (link = the identifier and the ticket).
+__device__ __forceinline__ void bucket_in(const CellBins& cb, int64_t i) {
+  const uint2 l = cb.link[i];
+  cb.bucket[cb.start[cb.key[i]] + l.y] = make_uint2((uint32_t)i, l.x);
+}
+
 // Digit 1 (list-build steps only): the cell of every particle, the histogram
 // and the chains, with one atomic of each kind per run of equal keys inside a
 // wave (the particles are still nearly in cell order).  Tiles follow the
@@ -534,6 +541,11 @@ __global__ __launch_bounds__(kAuxMaxThreads) void k_bin(
   if (!whole) return;  // uniform
   __threadfence_block();
   __syncthreads();
+  if (cb.bucket) {  // uniform
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) bucket_in(cb, i);
+    __threadfence_block();
+    __syncthreads();
+  }
   for (int64_t i = threadIdx.x; i < n; i += blockDim.x)
     rank_move<BATCH>(s, dst, cb, i, geo, qid, slot);
 }
@@ -571,15 +583,11 @@ __global__ __launch_bounds__(kScanWideThreads) void k_scan_cells(CellBins cb, co
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cb.start[cb.ncells] = offset + total;
 }
 
-// The buckets: each cell's particles side by side, in the order of their tickets
-// (link = the identifier and the ticket).
 __global__ void k_bin_scatter(CellBins cb, int64_t n, const BuildCtl* ctl, double half_skin2,
                               const uint32_t* status) {
   if (status_set(status) || !rebuild_now(ctl, half_skin2)) return;  // uniform
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint2 l = cb.link[i];
-  cb.bucket[cb.start[cb.key[i]] + l.y] = make_uint2((uint32_t)i, l.x);
+  if (i < n) bucket_in(cb, i);
 }
 
 // A particle per lane: those of the present memory order, or with buckets those

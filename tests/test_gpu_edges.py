@@ -593,3 +593,25 @@ def test_tile_of_dense_systems(dp, n, density, tile):
             with pytest.raises(dp.DpdeError):
                 s.debug_tile(t)
     s.close()
+
+
+def test_ranking_of_a_crowded_cell_by_one_block(dp):
+    """A thousand particles in one border cell, set in identifier order: up to
+    2048 particles one block bins and ranks them, in about the time that the
+    separate launches take at N = 8000 (159 and 140 us; 218 along the chain)."""
+    us = {}
+    for n in (1800, 8000):
+        box = [W.cubic_side(n)] * 3
+        q, p, e = W.equilibrium_state(n, box, seed=5)
+        rng = np.random.default_rng(6)
+        k = rng.permutation(n)[:1000]
+        q[k, 0] = box[0] + 5.0 + 1e4 * rng.random(1000)
+        q[k, 1:] = rng.random((1000, 2))
+        p[k] = 0.0
+        s = dp.System(dp.Config(n=n, box=box, periodic=[0, 1, 1], dt=0.005), q, p, e)
+        t = _binning_us(s, (q, p, e))
+        us[n] = t["bin"] + t.get("rank_gather", 0.0)
+        rows, cells = s.debug_order().cpu().numpy(), s.debug_cells().cpu().numpy()
+        assert np.array_equal(np.lexsort((np.arange(n), cells)), rows)
+        s.close()
+    assert us[1800] < 1.35 * us[8000], us

@@ -580,8 +580,8 @@ enum TailMode { kTailNone = 0, kTailStats = 1, kTailStatsKick = 2 };
 // A set state (kick = 0) is in no cell order: there a large system's chains are
 // scattered loads and its records scattered writes, so it is ranked by buckets of
 // the cells, for one launch more.  Measured, us for binning and ranking, chains /
-// buckets: N = 262,144 68 / 65, 480,000 115 / 94, 2^20 271 / 165; 30,000 of 600,000
-// particles in one cell 13,100 / 2850.
+// buckets: N = 131,072 44.3 / 44.8, 262,144 67 / 62, 480,000 115 / 93, 2^20 263 /
+// 175; 30,000 of 600,000 particles in one cell 13,100 / 2850.
 constexpr int64_t kBucketN = 1 << 18;
 struct BinPlan {
   unsigned blocks;

@@ -7,8 +7,8 @@
 //           (eq. SER_eint_discretization), p <- p + dp, eps <- eps + d eps,
 //           next 1/T_i.
 //
-// One lane per particle; each pair term is evaluated on both of its
-// particles' lanes in the canonical orientation (lower identifier first) and
+// A few lanes per particle.  In the both-sides form each pair term is evaluated
+// on both of its particles' lanes in the canonical orientation (lower identifier first) and
 // negated on the higher one, so dp_ji = -dp_ij bit for bit and the particle
 // sums are plain gathers: no atomics, fixed summation order.
 //
@@ -127,7 +127,8 @@ constexpr int kSub = 4;
 constexpr uint32_t kSubMask = (1u << kSub) - 1u;
 // The SER sweeps (passes B and C) use pairs of lanes: with ~12 neighbours
 // their pair terms keep more lanes busy per trip, while the filters over the
-// ~27 skin candidates (pass A, list build) are faster with four.
+// ~27 skin candidates (pass A, and the list build where cells hold few
+// particles) are faster with four.
 constexpr int kSubSer = 2;
 constexpr int kListLds = 64;  // list entries per particle staged in LDS
 // Particles per tile (= block) of the unique-pair passes: 128, and smaller ones
@@ -1491,7 +1492,8 @@ constexpr uint32_t fix_range_hi() {  // high word of 2^(51-G)
   return (uint32_t)(1023 + 51 - G) << 20;
 }
 
-// The tile of particle j relative to the tile starting at tb, or >= 128.
+// Particle j's place in the tile of T particles that starts at tb; T or more
+// outside it.
 __device__ __forceinline__ uint32_t in_tile(uint32_t j, int64_t tb) {
   return j - (uint32_t)tb;
 }
@@ -1568,7 +1570,7 @@ constexpr int kTileSkinLds = 28;  // skin-list entries per particle staged in LD
 
 // In a batch a wave walks its particles one replica at a time, with that
 // replica's geometry uniform (in scalar registers).  Replicas of at least a
-// wave's 16 particles (SMALL false) let a wave meet at most two, walked in
+// wave's kWave / KS particles (SMALL false) let a wave meet at most two, walked in
 // straight-line code; with smaller ones (SMALL) a loop takes as many as the
 // wave meets, at the cost of registers.
 // Tiles of T particles with KS lanes each (see TileShape in api.hip).
@@ -1592,7 +1594,7 @@ __global__ __launch_bounds__(KS * T) __attribute__((
   const int64_t tb = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * T;
   {
     // the first kStage entries of every skin list of the tile, loaded
-    // row by row (128 consecutive words per row), all loads in flight at once
+    // entry by entry (runs of kRow consecutive words), all loads in flight at once
     constexpr int kPer = kStage / KS;
     uint32_t v[kPer];
 #pragma unroll

@@ -1,6 +1,6 @@
 """Compile the C oracle into oracle/liboracle.so (plain gcc, no FMA contraction).
 
-Test infrastructure only: builds the checker, never part of the product path.
+Test infrastructure only: builds the oracle, never part of the product path.
 """
 from __future__ import annotations
 
